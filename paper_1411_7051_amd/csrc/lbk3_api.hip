@@ -14,12 +14,12 @@ namespace {
 
 // Workspace regions: two time levels of (ny nz) row blocks [rho | h_0..h_18]
 // (pitch elements per slot), the medium row blocks [eps | drag | kn0], FP64
-// partials and results.
+// partials.
 struct WsLayout3 {
     int pitch;
     Layout lay;
     MLayout mlay;
-    size_t level_bytes, level[2], med, partials, results, total;
+    size_t level_bytes, level[2], med, partials, total;
     int blocks;
 };
 
@@ -46,7 +46,6 @@ WsLayout3 layout3_of(const lbk_desc3 &d)
     L.med = take(L.mlay.row * rows);
     L.blocks = blocks3_of(Geom3{d.nx, d.ny, d.nz, L.pitch});
     L.partials = take((size_t)8 * L.blocks * sizeof(double));
-    L.results = take(8 * sizeof(double));
     L.total = o;
     return L;
 }
@@ -116,26 +115,31 @@ struct lbk_lattice3 {
     int64_t t;
     int scale_exp;
     double eps_b;
-    double *host;
+    HostSums out; // read-out sums on the host
+    double *host; // = out.sums
 
     char *state(int l) const { return ws + L.level[l]; }
     char *med() const { return ws + L.med; }
     float s() const { return ldexpf(1.0f, scale_exp); }
     float inv_s() const { return ldexpf(1.0f, -scale_exp); }
     double *partials() const { return reinterpret_cast<double *>(ws + L.partials); }
-    double *results() const { return reinterpret_cast<double *>(ws + L.results); }
 };
 
 namespace {
 
 lbk_status fetch3(lbk_lattice3 *lat, int slots, unsigned max_mask)
 {
-    HIP_TRY(launch_finish(lat->partials(), slots, lat->L.blocks, max_mask, lat->results(),
-                          lat->stream));
-    HIP_TRY(hipMemcpyAsync(lat->host, lat->results(), slots * sizeof(double),
-                           hipMemcpyDeviceToHost, lat->stream));
-    HIP_TRY(hipStreamSynchronize(lat->stream));
-    return LBK_OK;
+    return lat->out.fetch(lat->partials(), slots, lat->L.blocks, max_mask, lat->stream);
+}
+
+// Read-out sums (MAC_* slots) of the current state into lat->host.
+lbk_status macro_sums3(lbk_lattice3 *lat, bool mass)
+{
+    const lbk_desc3 &d = lat->d;
+    HIP_TRY(launch_macro3_sums(d.storage, d.bc_x, d.bc_y, d.bc_z, lat->state(lat->cur),
+                               lat->L.lay, lat->med(), lat->L.mlay, lat->g, lat->p3, lat->s(),
+                               lat->inv_s(), mass, lat->partials(), lat->stream));
+    return fetch3(lat, MAC_SLOTS, 0);
 }
 
 lbk_status check_state3(lbk_lattice3 *lat)
@@ -229,13 +233,13 @@ lbk_status lbk3_create(const lbk_desc3 *d, const float *eps, const float *k, con
     lat->cur = 0;
     lat->t = 0;
     lat->scale_exp = d->storage == LBK_F16 ? 20 : 0;
-    if (hipHostMalloc((void **)&lat->host, 8 * sizeof(double), hipHostMallocDefault) !=
-        hipSuccess) {
+    if (!lat->out.alloc()) {
         delete lat;
         return fail(LBK_ERR_DEVICE, "pinned host allocation failed");
     }
+    lat->host = lat->out.sums;
     auto cleanup = [&](lbk_status st) {
-        (void)hipHostFree(lat->host);
+        lat->out.release();
         delete lat;
         return st;
     };
@@ -312,7 +316,7 @@ lbk_status lbk3_destroy(lbk_lattice3 *lat)
 {
     if (!lat)
         return LBK_OK;
-    (void)hipHostFree(lat->host);
+    lat->out.release();
     delete lat;
     return LBK_OK;
 }
@@ -366,7 +370,7 @@ lbk_status lbk3_read_macroscopic(lbk_lattice3 *lat, float *rho, float *ux, float
     const lbk_desc3 &d = lat->d;
     HIP_TRY(launch_macro3(d.storage, d.bc_x, d.bc_y, d.bc_z, lat->state(lat->cur), lat->L.lay,
                           lat->med(), lat->L.mlay, lat->g, lat->p3, lat->s(), lat->inv_s(), rho,
-                          ux, uy, uz, lat->partials(), lat->stream));
+                          ux, uy, uz, lat->stream));
     return LBK_OK;
 }
 
@@ -386,8 +390,8 @@ lbk_status lbk3_apparent_permeability(lbk_lattice3 *lat, double *k_app)
     if (lat->d.bc_x == LBK_BC_PRESSURE ? lat->d.rho_in == lat->d.rho_out : lat->d.gx == 0.0)
         return fail(LBK_ERR_INVALID_ARG, "the global permeability needs rho_in != rho_out "
                                          "(pressure drive) or gx != 0");
-    lbk_status s = lbk3_read_macroscopic(lat, nullptr, nullptr, nullptr, nullptr);
-    if (s != LBK_OK || (s = fetch3(lat, MAC_SLOTS, 0)) != LBK_OK)
+    lbk_status s = macro_sums3(lat, false);
+    if (s != LBK_OK)
         return s;
     const lbk_desc3 &d = lat->d;
     const double n = (double)d.nx * d.ny * d.nz, nu = (d.tau - 0.5) / 3.0;
@@ -403,20 +407,15 @@ lbk_status lbk3_diagnostics(lbk_lattice3 *lat, double *mass, double *flux_x)
 {
     if (!lat)
         return fail(LBK_ERR_INVALID_ARG, "lattice is NULL");
-    lbk_status s;
-    if (flux_x) {
-        if ((s = lbk3_read_macroscopic(lat, nullptr, nullptr, nullptr, nullptr)) != LBK_OK ||
-            (s = fetch3(lat, MAC_SLOTS, 0)) != LBK_OK)
-            return s;
+    if (!flux_x && !mass)
+        return LBK_OK;
+    lbk_status s = macro_sums3(lat, mass != nullptr);
+    if (s != LBK_OK)
+        return s;
+    if (flux_x)
         *flux_x = lat->host[MAC_FLUX];
-    }
-    if (mass) {
-        HIP_TRY(launch_state_sums3(lat->d.storage, lat->state(lat->cur), lat->L.lay, lat->g,
-                                   lat->inv_s(), lat->partials(), lat->stream));
-        if ((s = fetch3(lat, ST_SLOTS, 1u << ST_HMAX)) != LBK_OK)
-            return s;
-        *mass = lat->host[ST_MASS];
-    }
+    if (mass)
+        *mass = lat->host[MAC_MASS];
     return LBK_OK;
 }
 

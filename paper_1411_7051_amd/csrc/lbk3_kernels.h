@@ -30,12 +30,18 @@ hipError_t launch_sweep3(int storage, int bcx, int bcy, int bcz, const char *src
                          const Geom3 &g, const Physics3 &p3, float s, float inv_s,
                          hipStream_t st);
 
-// Read-out of rho and u ([nz][ny][nx], any may be NULL) and per-block FP64
-// partials [MAC_SLOTS][blocks3_of(g)].
+// Fields rho and u ([nz][ny][nx], any may be NULL).
 hipError_t launch_macro3(int storage, int bcx, int bcy, int bcz, const char *src,
                          const Layout &lay, const char *med, const MLayout &mlay,
                          const Geom3 &g, const Physics3 &p3, float s, float inv_s, float *rho,
-                         float *ux, float *uy, float *uz, double *partials, hipStream_t st);
+                         float *ux, float *uy, float *uz, hipStream_t st);
+
+// Read-out sums: per-block FP64 partials [MAC_SLOTS][blocks3_of(g)]; MAC_MASS
+// is summed when `mass` asks for it.
+hipError_t launch_macro3_sums(int storage, int bcx, int bcy, int bcz, const char *src,
+                              const Layout &lay, const char *med, const MLayout &mlay,
+                              const Geom3 &g, const Physics3 &p3, float s, float inv_s, bool mass,
+                              double *partials, hipStream_t st);
 
 // Mass / max|h| / non-finite partials [ST_SLOTS][blocks].
 hipError_t launch_state_sums3(int storage, const char *src, const Layout &lay, const Geom3 &g,

@@ -39,28 +39,6 @@ __host__ __device__ constexpr float w3(int i)
     return i == 0 ? 1.0f / 3.0f : (i <= 6 ? 1.0f / 18.0f : 1.0f / 36.0f);
 }
 
-// Fixed-order block reductions (wave shuffles, then the waves in order).
-__device__ __forceinline__ double block_red(double v, double *sh, bool is_max)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double o = __shfl_xor(v, off, 64);
-        v = is_max ? (o > v ? o : v) : v + o;
-    }
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    __syncthreads();
-    if (lane == 0)
-        sh[wave] = v;
-    __syncthreads();
-    double r = sh[0];
-#pragma unroll
-    for (int w = 1; w < kBlock3 / 64; ++w)
-        r = is_max ? (sh[w] > r ? sh[w] : r) : r + sh[w];
-    return r;
-}
-__device__ __forceinline__ double block_sum(double v, double *sh) { return block_red(v, sh, false); }
-__device__ __forceinline__ double block_max(double v, double *sh) { return block_red(v, sh, true); }
-
 __device__ __forceinline__ int xcd_remap3(int b, int nb)
 {
     const int q = nb >> 3, r = nb & 7;
@@ -413,17 +391,43 @@ __global__ __launch_bounds__(kBlock3) void sweep3_kernel(const char *src, char *
         Elem<T>::st(out, nd.x * es, lay.h_off + i * lay.h_slot, hs[i]);
 }
 
-// Read-out: rho, u into [nz][ny][nx] buffers (any may be NULL) and per-block
-// FP64 partials [MAC_SLOTS][blocks] (MAC_DU2 unused).
+// Fields: rho, u into [nz][ny][nx] buffers (any may be NULL).
 template <typename T, int BCX, int BCY, int BCZ>
 __global__ __launch_bounds__(kBlock3) void macro3_kernel(const char *src, Layout lay,
                                                           const char *med, MLayout mlay,
                                                           Geom3 g, Physics3 p3, float s,
                                                           float inv_s, int bpr, float *rho_out,
                                                           float *ux_out, float *uy_out,
-                                                          float *uz_out, double *partials)
+                                                          float *uz_out)
 {
-    __shared__ double sh[kBlock3 / 64];
+    const Node3 nd = node3_of(g, bpr);
+    if (nd.x >= (uint32_t)g.nx)
+        return;
+    float u[3], r;
+    const float rho = macro_node3<T, BCX, BCY, BCZ>(src, lay, med, mlay, g, p3, s, inv_s, nd.y,
+                                                    nd.z, nd.x, u, r);
+    const uint64_t o = row3(g, nd.y, nd.z) * (uint64_t)g.nx + nd.x;
+    if (rho_out)
+        rho_out[o] = (float)((double)rho + (double)r);
+    if (ux_out)
+        ux_out[o] = u[0];
+    if (uy_out)
+        uy_out[o] = u[1];
+    if (uz_out)
+        uz_out[o] = u[2];
+}
+
+// Read-out sums: per-block FP64 partials [MAC_SLOTS][blocks] (MAC_DU2
+// unused).  With `mass` also the sum of the node's own stored populations,
+// whose lines the neighbouring nodes' pulls bring in anyway (a pass of its
+// own took 213 us on 256^3 at FP32).
+template <typename T, int BCX, int BCY, int BCZ>
+__global__ __launch_bounds__(kBlock3) void macro3_sums_kernel(const char *src, Layout lay,
+                                                               const char *med, MLayout mlay,
+                                                               Geom3 g, Physics3 p3, float s,
+                                                               float inv_s, int bpr, int mass,
+                                                               double *partials)
+{
     const Node3 nd = node3_of(g, bpr);
     double v[MAC_SLOTS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (nd.x < (uint32_t)g.nx) {
@@ -431,28 +435,21 @@ __global__ __launch_bounds__(kBlock3) void macro3_kernel(const char *src, Layout
         const float rho = macro_node3<T, BCX, BCY, BCZ>(src, lay, med, mlay, g, p3, s, inv_s,
                                                         nd.y, nd.z, nd.x, u, r);
         const double rp = (double)rho + (double)r;
-        const uint64_t o = row3(g, nd.y, nd.z) * (uint64_t)g.nx + nd.x;
-        if (rho_out)
-            rho_out[o] = (float)rp;
-        if (ux_out)
-            ux_out[o] = u[0];
-        if (uy_out)
-            uy_out[o] = u[1];
-        if (uz_out)
-            uz_out[o] = u[2];
         v[MAC_FLUX] = rp * (double)u[0];
         v[MAC_UX] = u[0];
         v[MAC_U2] = (double)u[0] * u[0] + (double)u[1] * u[1] + (double)u[2] * u[2];
-        v[MAC_RHO] = rp;
         v[MAC_QOUT] = (nd.x == (uint32_t)g.nx - 1) ? rp * (double)u[0] : 0.0;
-    }
-    const int L = xcd_remap3(blockIdx.x, gridDim.x);
+        if (mass) {
+            const Rsrc row = make_rsrc(src + row3(g, nd.y, nd.z) * lay.row, (uint32_t)lay.row);
+            double hs = 0.0;
 #pragma unroll
-    for (int k = 0; k < MAC_SLOTS; ++k) {
-        const double rr = block_sum(v[k], sh);
-        if (threadIdx.x == 0)
-            partials[(int64_t)k * gridDim.x + L] = rr;
+            for (int i = 0; i < 19; ++i)
+                hs += (double)Elem<T>::template ld<kAux3>(row, nd.x * sizeof(T),
+                                                          lay.h_off + i * lay.h_slot);
+            v[MAC_MASS] = (double)ld_f32(row, nd.x * 4, 0) + hs * inv_s;
+        }
     }
+    block_sums<MAC_SLOTS>(v, partials, xcd_remap3(blockIdx.x, gridDim.x), gridDim.x);
 }
 
 // FP64 mass sum (rho + sum h / s), max |h| and the count of non-finite
@@ -462,34 +459,26 @@ __global__ __launch_bounds__(kBlock3) void state_sums3_kernel(const char *src, L
                                                                Geom3 g, float inv_s, int bpr,
                                                                double *partials)
 {
-    __shared__ double sh[kBlock3 / 64];
     const Node3 nd = node3_of(g, bpr);
-    double mass = 0.0, hmax = 0.0, bad = 0.0;
+    double mass = 0.0;
+    float hmax = 0.0f;
+    int bad = 0;
     if (nd.x < (uint32_t)g.nx) {
         const Rsrc row = make_rsrc(src + row3(g, nd.y, nd.z) * lay.row, (uint32_t)lay.row);
         const float rho = ld_f32(row, nd.x * 4, 0);
         double hs = 0.0;
-        bad += isfinite(rho) ? 0.0 : 1.0;
+        bad += isfinite(rho) ? 0 : 1;
 #pragma unroll
         for (int i = 0; i < 19; ++i) {
             const float h = Elem<T>::template ld<kAux3>(row, nd.x * sizeof(T), lay.h_off + i * lay.h_slot);
-            bad += isfinite(h) ? 0.0 : 1.0;
+            bad += isfinite(h) ? 0 : 1;
             hs += (double)h;
-            const double a = fabs((double)h * inv_s);
+            const float a = fabsf(h * inv_s); // exact: inv_s is a power of two
             hmax = a > hmax ? a : hmax;
         }
         mass = (double)rho + hs * inv_s;
     }
-    const int L = xcd_remap3(blockIdx.x, gridDim.x);
-    double r = block_sum(mass, sh);
-    if (threadIdx.x == 0)
-        partials[(int64_t)ST_MASS * gridDim.x + L] = r;
-    r = block_max(hmax, sh);
-    if (threadIdx.x == 0)
-        partials[(int64_t)ST_HMAX * gridDim.x + L] = r;
-    r = block_sum(bad, sh);
-    if (threadIdx.x == 0)
-        partials[(int64_t)ST_BAD * gridDim.x + L] = r;
+    block_state(mass, hmax, bad, partials, xcd_remap3(blockIdx.x, gridDim.x), gridDim.x);
 }
 
 // Rest (or the linear density ramp along x) with the FP64 density split
@@ -557,22 +546,18 @@ __global__ __launch_bounds__(kBlock3) void rescale3_kernel(char *st, Layout lay,
 __global__ __launch_bounds__(kBlock3) void fields3_kernel(char *med, MLayout mlay, Geom3 g,
                                                            double nu, double *partials, int bpr)
 {
-    __shared__ double sh[kBlock3 / 64];
     const Node3 nd = node3_of(g, bpr);
-    double bad = 0.0;
+    double bad[1] = {0.0};
     if (nd.x < (uint32_t)g.nx) {
         const Rsrc row = make_rsrc(med + row3(g, nd.y, nd.z) * mlay.row, (uint32_t)mlay.row);
         const float e = ld_f32(row, nd.x * 4, 0), k = ld_f32(row, nd.x * 4, mlay.slot),
                     kn = ld_f32(row, nd.x * 4, 2 * mlay.slot);
         const bool ok = (e >= 0.0f && e <= 1.0f) && (k > 0.0f) && (kn >= 0.0f && isfinite(kn));
-        bad = ok ? 0.0 : 1.0;
+        bad[0] = ok ? 0.0 : 1.0;
         const float drag = (!ok || isinf(k) || e == 0.0f) ? 0.0f : (float)((double)e * nu / k);
         st_f32(row, nd.x * 4, mlay.slot, drag, false);
     }
-    const int L = xcd_remap3(blockIdx.x, gridDim.x);
-    const double r = block_sum(bad, sh);
-    if (threadIdx.x == 0)
-        partials[(int64_t)FLD_BAD * gridDim.x + L] = r;
+    block_sums<FLD_SLOTS>(bad, partials, xcd_remap3(blockIdx.x, gridDim.x), gridDim.x);
 }
 
 } // namespace
@@ -638,11 +623,23 @@ template <typename T, int BCX, int BCY, int BCZ>
 static hipError_t macro3_t(const char *src, const Layout &lay, const char *med,
                            const MLayout &mlay, const Geom3 &g, const Physics3 &p3, float s,
                            float inv_s, float *rho, float *ux, float *uy, float *uz,
-                           double *partials, hipStream_t st)
+                           hipStream_t st)
 {
     const int bpr = (g.nx + kBlock3 - 1) / kBlock3;
     hipLaunchKernelGGL((macro3_kernel<T, BCX, BCY, BCZ>), dim3(blocks3_of(g)), dim3(kBlock3), 0,
-                       st, src, lay, med, mlay, g, p3, s, inv_s, bpr, rho, ux, uy, uz, partials);
+                       st, src, lay, med, mlay, g, p3, s, inv_s, bpr, rho, ux, uy, uz);
+    return hipGetLastError();
+}
+
+template <typename T, int BCX, int BCY, int BCZ>
+static hipError_t macro3_sums_t(const char *src, const Layout &lay, const char *med,
+                                const MLayout &mlay, const Geom3 &g, const Physics3 &p3, float s,
+                                float inv_s, bool mass, double *partials, hipStream_t st)
+{
+    const int bpr = (g.nx + kBlock3 - 1) / kBlock3;
+    hipLaunchKernelGGL((macro3_sums_kernel<T, BCX, BCY, BCZ>), dim3(blocks3_of(g)),
+                       dim3(kBlock3), 0, st, src, lay, med, mlay, g, p3, s, inv_s, bpr,
+                       mass ? 1 : 0, partials);
     return hipGetLastError();
 }
 
@@ -657,9 +654,17 @@ hipError_t launch_sweep3(int storage, int bcx, int bcy, int bcz, const char *src
 hipError_t launch_macro3(int storage, int bcx, int bcy, int bcz, const char *src,
                          const Layout &lay, const char *med, const MLayout &mlay,
                          const Geom3 &g, const Physics3 &p3, float s, float inv_s, float *rho,
-                         float *ux, float *uy, float *uz, double *partials, hipStream_t st)
+                         float *ux, float *uy, float *uz, hipStream_t st)
 {
-    LBK3_DISPATCH(macro3_t, src, lay, med, mlay, g, p3, s, inv_s, rho, ux, uy, uz, partials, st)
+    LBK3_DISPATCH(macro3_t, src, lay, med, mlay, g, p3, s, inv_s, rho, ux, uy, uz, st)
+}
+
+hipError_t launch_macro3_sums(int storage, int bcx, int bcy, int bcz, const char *src,
+                              const Layout &lay, const char *med, const MLayout &mlay,
+                              const Geom3 &g, const Physics3 &p3, float s, float inv_s, bool mass,
+                              double *partials, hipStream_t st)
+{
+    LBK3_DISPATCH(macro3_sums_t, src, lay, med, mlay, g, p3, s, inv_s, mass, partials, st)
 }
 
 hipError_t launch_state_sums3(int storage, const char *src, const Layout &lay, const Geom3 &g,

@@ -10,6 +10,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <new>
 #include <string>
 
@@ -60,7 +61,6 @@ WsLayout layout_of(const lbk_desc &d)
     Geom g{d.nx, d.ny, L.pitch};
     L.blocks = launch_of(g).blocks;
     L.partials = take((size_t)8 * L.blocks * sizeof(double));
-    L.results = take(8 * sizeof(double));
     L.total = o;
     return L;
 }
@@ -163,15 +163,51 @@ lbk_status lbk::advance(lbk_lattice *lat, int64_t n, hipStream_t st)
     return LBK_OK;
 }
 
-// Run a reduction's finish kernel and copy `slots` doubles to lat->host.
+bool lbk::HostSums::alloc()
+{
+    if (hipHostMalloc((void **)&sums, 16 * sizeof(double), hipHostMallocCoherent) != hipSuccess) {
+        sums = nullptr;
+        return false;
+    }
+    memset(sums, 0, 16 * sizeof(double));
+    done = reinterpret_cast<uint64_t *>(sums + 8);
+    return true;
+}
+
+void lbk::HostSums::release()
+{
+    (void)hipHostFree(sums);
+    sums = nullptr;
+}
+
+lbk_status lbk::HostSums::fetch(const double *partials, int slots, int blocks,
+                                unsigned max_mask, hipStream_t st)
+{
+    HIP_TRY(launch_finish(partials, slots, blocks, max_mask, sums, done, ++seq, st));
+    auto arrived = [&] {
+        for (int k = 0; k < slots; ++k)
+            if (__atomic_load_n(&done[k], __ATOMIC_ACQUIRE) != seq)
+                return false;
+        return true;
+    };
+    // poll for a bounded time, then wait for the stream (which also reports
+    // an error that kept the kernel from running)
+    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+    while (!arrived()) {
+        for (int i = 0; i < 32; ++i)
+            __builtin_ia32_pause();
+        if (std::chrono::steady_clock::now() > until) {
+            HIP_TRY(hipStreamSynchronize(st));
+            break;
+        }
+    }
+    return LBK_OK;
+}
+
+// Run a reduction's finish kernel and bring `slots` doubles to lat->host.
 lbk_status lbk::fetch(lbk_lattice *lat, int slots, unsigned max_mask)
 {
-    HIP_TRY(launch_finish(lat->partials(), slots, lat->L.blocks, max_mask, lat->results(),
-                          lat->stream));
-    HIP_TRY(hipMemcpyAsync(lat->host, lat->results(), slots * sizeof(double),
-                           hipMemcpyDeviceToHost, lat->stream));
-    HIP_TRY(hipStreamSynchronize(lat->stream));
-    return LBK_OK;
+    return lat->out.fetch(lat->partials(), slots, lat->L.blocks, max_mask, lat->stream);
 }
 
 // NaN/Inf check of the current state; for FP16 also re-centre the scale so
@@ -273,13 +309,13 @@ lbk_status lbk_create(const lbk_desc *d, const float *eps, const float *k, const
     lat->version = 0;
     lat->scale_exp = d->storage == LBK_F16 ? 20 : 0;
     lat->have_prev = false;
-    if (hipHostMalloc((void **)&lat->host, 8 * sizeof(double), hipHostMallocDefault) !=
-        hipSuccess) {
+    if (!lat->out.alloc()) {
         delete lat;
         return fail(LBK_ERR_DEVICE, "pinned host allocation failed");
     }
+    lat->host = lat->out.sums;
     auto cleanup = [&](lbk_status st) {
-        (void)hipHostFree(lat->host);
+        lat->out.release();
         delete lat;
         return st;
     };
@@ -360,7 +396,7 @@ lbk_status lbk_destroy(lbk_lattice *lat)
 {
     if (!lat)
         return LBK_OK;
-    (void)hipHostFree(lat->host);
+    lat->out.release();
     delete lat;
     return LBK_OK;
 }
@@ -412,7 +448,7 @@ lbk_status lbk_read_macroscopic(lbk_lattice *lat, float *rho, float *ux, float *
     const lbk_desc &d = lat->d;
     HIP_TRY(launch_macro(d.storage, d.bc_x, d.bc_y, lat->state(lat->cur), lat->L.lay,
                          lat->med(), lat->L.mlay, lat->g, lat->ph, lat->s(), lat->inv_s(), rho, ux, uy,
-                         nullptr, nullptr, lat->partials(), lat->stream));
+                         lat->stream));
     return LBK_OK;
 }
 
@@ -444,15 +480,15 @@ double lbk::k_app_of(const lbk_lattice *lat, const double *sums)
     return nu * (sums[MAC_UX] / n) / d.gx;
 }
 
-lbk_status lbk::macro_sums(lbk_lattice *lat, bool residual)
+lbk_status lbk::macro_sums(lbk_lattice *lat, bool residual, bool mass)
 {
     const lbk_desc &d = lat->d;
     char *ws = lat->ws;
     float *uxp = residual ? reinterpret_cast<float *>(ws + lat->L.uxp) : nullptr;
     float *uyp = residual ? reinterpret_cast<float *>(ws + lat->L.uyp) : nullptr;
-    HIP_TRY(launch_macro(d.storage, d.bc_x, d.bc_y, lat->state(lat->cur), lat->L.lay,
-                         lat->med(), lat->L.mlay, lat->g, lat->ph, lat->s(), lat->inv_s(), nullptr, nullptr,
-                         nullptr, uxp, uyp, lat->partials(), lat->stream));
+    HIP_TRY(launch_macro_sums(d.storage, d.bc_x, d.bc_y, lat->state(lat->cur), lat->L.lay,
+                              lat->med(), lat->L.mlay, lat->g, lat->ph, lat->s(), lat->inv_s(),
+                              uxp, uyp, mass, lat->partials(), lat->stream));
     return fetch(lat, MAC_SLOTS, 0);
 }
 
@@ -465,7 +501,7 @@ lbk_status lbk_apparent_permeability(lbk_lattice *lat, double *k_app)
     if (!has_drive(lat->d))
         return fail(LBK_ERR_INVALID_ARG, "the global permeability needs rho_in != rho_out "
                                          "(pressure drive) or gx != 0");
-    lbk_status s = macro_sums(lat, false);
+    lbk_status s = macro_sums(lat, false, false);
     if (s != LBK_OK)
         return s;
     *k_app = k_app_of(lat, lat->host);
@@ -476,7 +512,7 @@ lbk_status lbk_diagnostics(lbk_lattice *lat, double *mass, double *flux_x, doubl
 {
     if (!lat)
         return fail(LBK_ERR_INVALID_ARG, "lattice is NULL");
-    lbk_status s = macro_sums(lat, true);
+    lbk_status s = macro_sums(lat, true, mass != nullptr);
     if (s != LBK_OK)
         return s;
     const double flux = lat->host[MAC_FLUX];
@@ -493,13 +529,8 @@ lbk_status lbk_diagnostics(lbk_lattice *lat, double *mass, double *flux_x, doubl
         *flux_x = flux;
     if (residual)
         *residual = res;
-    if (mass) {
-        HIP_TRY(launch_state_sums(lat->d.storage, lat->state(lat->cur), lat->L.lay, lat->g,
-                                  lat->inv_s(), lat->partials(), lat->stream));
-        if ((s = fetch(lat, ST_SLOTS, 1u << ST_HMAX)) != LBK_OK)
-            return s;
-        *mass = lat->host[ST_MASS];
-    }
+    if (mass)
+        *mass = lat->host[MAC_MASS];
     return LBK_OK;
 }
 
@@ -776,7 +807,7 @@ extern "C" lbk_status lbk_adjoint_forward(lbk_lattice *lat, int objective, int64
                 return s;
         }
     }
-    if ((s = macro_sums(lat, false)) != LBK_OK)
+    if ((s = macro_sums(lat, false, false)) != LBK_OK)
         return s;
     P.objective = objective;
     *J = objective_weights(lat, objective, lat->host, P.a1, P.a2, P.outlet);

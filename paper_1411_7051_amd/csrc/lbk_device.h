@@ -508,4 +508,84 @@ __device__ __forceinline__ void collide(const Physics &ph, float rho, float inc,
     }
 }
 
+// ----------------------------------------------------------- reductions
+
+// FP64 sums of N <= 8 values over a workgroup of 256 threads (4 waves), in a
+// fixed order: out[k * stride + at] receives value k.  Every thread must call
+// it.  Inside a wave the values are halved with the lanes: at offset 32 each
+// half-wave keeps four of the values and hands over the other four, at 16
+// two, at 8 one, so eight sums take 10 shuffles instead of 48 (the additions,
+// and so the result, are those of a butterfly per value); lane 8 k then holds
+// value k, and one exchange through LDS adds the four waves in order.
+template <int N>
+__device__ __forceinline__ void block_sums(const double (&v)[N], double *__restrict__ out,
+                                           int64_t at, int64_t stride)
+{
+    static_assert(N >= 1 && N <= 8, "slots of one packed reduction");
+    __shared__ double sh[4][8];
+    const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
+    double a[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        a[k] = k < N ? v[k] : 0.0;
+    // keep the upper or the lower half of the values by the lane's bit
+#pragma unroll
+    for (int off = 32, n = 4; off >= 8; off >>= 1, n >>= 1) {
+        const bool up = (lane & off) != 0;
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+            const double mine = up ? a[k + n] : a[k], other = up ? a[k] : a[k + n];
+            a[k] = mine + __shfl_xor(other, off, 64);
+        }
+    }
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1)
+        a[0] += __shfl_xor(a[0], off, 64);
+    if ((lane & 7) == 0)
+        sh[wave][lane >> 3] = a[0];
+    __syncthreads();
+    if (threadIdx.x < N) {
+        const int k = (int)threadIdx.x;
+        double r = sh[0][k];
+        for (int w = 1; w < 4; ++w)
+            r += sh[w][k];
+        out[(int64_t)k * stride + at] = r;
+    }
+}
+
+// The state check's reductions over a workgroup of 256 threads: the FP64 mass
+// sum, the largest magnitude and the count of non-finite values, into
+// out[0], out[stride] and out[2 stride] (+ at).  Every thread must call it.
+__device__ __forceinline__ void block_state(double mass, float hmax, int bad,
+                                            double *__restrict__ out, int64_t at, int64_t stride)
+{
+    __shared__ double shm[4];
+    __shared__ float shh[4];
+    __shared__ int shb[4];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        mass += __shfl_xor(mass, off, 64);
+        const float o = __shfl_xor(hmax, off, 64);
+        hmax = o > hmax ? o : hmax;
+        bad += __shfl_xor(bad, off, 64);
+    }
+    const int wave = (int)(threadIdx.x >> 6);
+    if ((threadIdx.x & 63) == 0) {
+        shm[wave] = mass;
+        shh[wave] = hmax;
+        shb[wave] = bad;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w) {
+            mass += shm[w];
+            hmax = shh[w] > hmax ? shh[w] : hmax;
+            bad += shb[w];
+        }
+        out[at] = mass;
+        out[stride + at] = (double)hmax;
+        out[2 * stride + at] = (double)bad;
+    }
+}
+
 } // namespace lbk

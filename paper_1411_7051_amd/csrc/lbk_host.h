@@ -47,7 +47,7 @@ struct WsLayout {
     size_t level_bytes;   // bytes of one time level
     size_t level[2];      // two time levels
     size_t med, uxp, uyp; // medium; previous velocity for the residual
-    size_t partials, results;
+    size_t partials;
     size_t total;
     int blocks;
 };
@@ -69,6 +69,22 @@ struct AdjPlan {
     const void *ws;
     double a1, a2;
     int outlet;
+};
+
+// A handle's read-out results on the host: eight sums and a mark per sum in
+// coherent pinned memory.  The finish kernel writes a sum, then its mark; the
+// host polls the marks, which spares a small lattice the copy of the sums
+// and the wait for the stream (together longer than the read-out itself).
+struct HostSums {
+    double *sums = nullptr;
+    uint64_t *done = nullptr;
+    uint64_t seq = 0;
+    bool alloc();
+    void release();
+    // finish kernel over partials [slots][blocks], then the sums on the host;
+    // everything queued on the stream before has run when it returns
+    lbk_status fetch(const double *partials, int slots, int blocks, unsigned max_mask,
+                     hipStream_t st);
 };
 
 } // namespace lbk
@@ -93,7 +109,8 @@ struct lbk_lattice {
     int scale_exp; // FP16: stored = h * 2^scale_exp
     bool have_prev;
     double eps_b;  // mean porosity of the two pressure columns
-    double *host;  // pinned scratch for results (8 doubles)
+    lbk::HostSums out; // read-out sums on the host
+    double *host;      // = out.sums
     AdjPlan adj;
 
     char *state(int l) const { return ws + L.level[l]; }
@@ -101,7 +118,6 @@ struct lbk_lattice {
     float s() const { return ldexpf(1.0f, scale_exp); }
     float inv_s() const { return ldexpf(1.0f, -scale_exp); }
     double *partials() const { return reinterpret_cast<double *>(ws + L.partials); }
-    double *results() const { return reinterpret_cast<double *>(ws + L.results); }
 };
 
 namespace lbk {
@@ -222,8 +238,9 @@ lbk_status fetch(lbk_lattice *lat, int slots, unsigned max_mask);
 // NaN/Inf check of the current state; FP16 also re-centres the scale.
 lbk_status check_state(lbk_lattice *lat);
 
-// Read-out sums (MAC_* slots) of the current state into lat->host.
-lbk_status macro_sums(lbk_lattice *lat, bool residual);
+// Read-out sums (MAC_* slots) of the current state into lat->host, with the
+// residual's and the mass when asked for.
+lbk_status macro_sums(lbk_lattice *lat, bool residual, bool mass);
 
 // Whether the run has a drive the global permeability is normalised by: a
 // pressure difference (pressure columns) or a body force along x.

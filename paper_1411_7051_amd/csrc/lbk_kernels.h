@@ -24,6 +24,9 @@ constexpr int kStrip2 = 60;
 // Columns a wave of the three-step pass stores (six halo lanes).
 constexpr int kStrip3 = 58;
 
+// Threads per block of the kernels that sum a slot's partials.
+constexpr int kFinish = 1024;
+
 // Largest batch tile width (workgroup size) of the batched sweep.
 constexpr int kBatchMaxTile = 256;
 
@@ -47,7 +50,7 @@ enum {
     MAC_UX,       // sum u_x
     MAC_DU2,      // sum |u - u_prev|^2
     MAC_U2,       // sum |u|^2
-    MAC_RHO,      // sum rho
+    MAC_MASS,     // sum of the stored populations (when asked for)
     MAC_QOUT,     // sum over column nx-1 of rho u_x (outlet mass flux)
     MAC_SLOTS
 };
@@ -90,15 +93,21 @@ hipError_t launch_sweep3x(int storage, int bcx, int bcy, const char *src, char *
                           const Physics &ph, float s, float inv_s, int band, float *hist1,
                           float *hist2, float *hist3, hipStream_t st);
 
-// Macroscopic read-out ([ny][nx] outputs, any may be null) and FP64 partials
-// [MAC_SLOTS][blocks].  If u_prev ([ny][pitch]) is given it is read for the
-// residual and then overwritten with the current velocity.
+// Macroscopic fields ([ny][nx] outputs, any may be null).
 hipError_t launch_macro(int storage, int bcx, int bcy, const char *src, const Layout &lay,
                         const char *med, const MLayout &mlay, const Geom &g, const Physics &ph,
                         float s, float inv_s, float *rho_out, float *ux_out, float *uy_out,
-                        float *ux_prev, float *uy_prev, double *partials, hipStream_t st);
+                        hipStream_t st);
 
-// The read-out sums of launch_macro (no outputs, no residual) over a fixed
+// Read-out sums: FP64 partials [MAC_SLOTS][blocks].  If u_prev ([ny][pitch])
+// is given it is read for the residual and then overwritten with the current
+// velocity; MAC_MASS is summed when `mass` asks for it.
+hipError_t launch_macro_sums(int storage, int bcx, int bcy, const char *src, const Layout &lay,
+                             const char *med, const MLayout &mlay, const Geom &g,
+                             const Physics &ph, float s, float inv_s, float *ux_prev,
+                             float *uy_prev, bool mass, double *partials, hipStream_t st);
+
+// The read-out sums of launch_macro_sums (no residual, no mass) over a fixed
 // grid of `grid` workgroups that walk the lattice: partials
 // [MAC_SLOTS][grid].
 hipError_t launch_macro_strided(int storage, int bcx, int bcy, const char *src,
@@ -111,9 +120,10 @@ hipError_t launch_state_sums(int storage, const char *src, const Layout &lay, co
                              float inv_s, double *partials, hipStream_t st);
 
 // Reduce partials [slots][blocks] in a fixed order into out[slots]; bit k of
-// max_mask selects max instead of sum for slot k.
+// max_mask selects max instead of sum for slot k.  With `done` (then out and
+// done[slots] are coherent host memory) done[k] = seq marks out[k] written.
 hipError_t launch_finish(const double *partials, int slots, int blocks, unsigned max_mask,
-                         double *out, hipStream_t st);
+                         double *out, uint64_t *done, uint64_t seq, hipStream_t st);
 
 // Field set-up: in place, turn the raw k slot into drag = eps nu / k
 // (0 where k = +inf or eps = 0) and count invalid values into

@@ -819,33 +819,6 @@ __global__ __launch_bounds__(kBlock) void batch_rec_sweep2_kernel(
 
 // ----------------------------------------------------------- reductions
 
-struct SumOp {
-    static __device__ __forceinline__ double f(double a, double b) { return a + b; }
-};
-struct MaxOp {
-    static __device__ __forceinline__ double f(double a, double b) { return a > b ? a : b; }
-};
-
-// Fixed-order block reduction of one value: butterfly inside each wave64,
-// then the four wave results in order.  Every thread must call it.
-template <typename Op>
-__device__ __forceinline__ double block_reduce(double v, double *sh)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
-        v = Op::f(v, __shfl_xor(v, off, 64));
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    __syncthreads();
-    if (lane == 0)
-        sh[wave] = v;
-    __syncthreads();
-    double r = sh[0];
-#pragma unroll
-    for (int w = 1; w < kBlock / 64; ++w)
-        r = Op::f(r, sh[w]);
-    return r;
-}
-
 // Read-out of node (x, y): post-stream density (FP64, with its residual)
 // and velocity (Eqs. 16-17 after the boundary override).
 template <typename T, int BCX, int BCY>
@@ -868,33 +841,61 @@ __device__ __forceinline__ void readout_node(const char *src, const Layout &lay,
     rp = (double)rho + (double)r;
 }
 
+// Macroscopic fields of every node ([ny][nx], any output may be null).  No
+// sums: the field read-out of a 4096 x 4096 FP32 lattice moves 68 B/node and
+// took 237-332 us while it also reduced (and then dropped) six FP64 sums.
 template <typename T, int BCX, int BCY>
 __global__ __launch_bounds__(kBlock) void macro_kernel(const char *src, Layout lay,
                                                         const char *med, MLayout mlay, Geom g,
                                                         Physics ph, float s, float inv_s, int bpr,
                                                         float *rho_out, float *ux_out,
-                                                        float *uy_out, float *ux_prev,
-                                                        float *uy_prev, double *partials)
+                                                        float *uy_out)
 {
-    __shared__ double sh[kBlock / 64];
+    const Node nd = node_of(bpr);
+    if (nd.x >= (uint32_t)g.nx)
+        return;
+    double rp;
+    float ux, uy;
+    readout_node<T, BCX, BCY>(src, lay, med, mlay, g, ph, s, inv_s, nd.y, nd.x, rp, ux, uy);
+    const uint32_t o = (uint32_t)nd.y * (uint32_t)g.nx + nd.x;
+    if (rho_out)
+        rho_out[o] = (float)rp;
+    if (ux_out)
+        ux_out[o] = ux;
+    if (uy_out)
+        uy_out[o] = uy;
+}
+
+// Read-out sums of one node's density and velocity.
+__device__ __forceinline__ void macro_sums_of(double rp, float ux, float uy, bool outlet,
+                                              double (&v)[MAC_SLOTS])
+{
+    v[MAC_FLUX] += rp * (double)ux;
+    v[MAC_UX] += ux;
+    v[MAC_U2] += (double)ux * ux + (double)uy * uy;
+    v[MAC_QOUT] += outlet ? rp * (double)ux : 0.0;
+}
+
+// Read-out sums: per-block FP64 partials [MAC_SLOTS][blocks].  With u_prev
+// the residual's sum too (u_prev is then overwritten); with `mass` the sum of
+// the node's own stored populations, whose lines the pulls of the
+// neighbouring nodes bring in anyway (a pass of its own over the state took
+// 151 us on 4096 x 4096 at FP32).
+template <typename T, int BCX, int BCY>
+__global__ __launch_bounds__(kBlock) void macro_sums_kernel(const char *src, Layout lay,
+                                                             const char *med, MLayout mlay,
+                                                             Geom g, Physics ph, float s,
+                                                             float inv_s, int bpr, float *ux_prev,
+                                                             float *uy_prev, int mass,
+                                                             double *partials)
+{
     const Node nd = node_of(bpr);
     double v[MAC_SLOTS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (nd.x < (uint32_t)g.nx) {
         double rp;
         float ux, uy;
         readout_node<T, BCX, BCY>(src, lay, med, mlay, g, ph, s, inv_s, nd.y, nd.x, rp, ux, uy);
-        const uint32_t o = (uint32_t)nd.y * (uint32_t)g.nx + nd.x;
-        if (rho_out)
-            rho_out[o] = (float)rp;
-        if (ux_out)
-            ux_out[o] = ux;
-        if (uy_out)
-            uy_out[o] = uy;
-        v[MAC_FLUX] = rp * (double)ux;
-        v[MAC_UX] = ux;
-        v[MAC_U2] = (double)ux * ux + (double)uy * uy;
-        v[MAC_RHO] = rp;
-        v[MAC_QOUT] = (nd.x == (uint32_t)g.nx - 1) ? rp * (double)ux : 0.0;
+        macro_sums_of(rp, ux, uy, nd.x == (uint32_t)g.nx - 1, v);
         if (ux_prev) {
             const uint32_t c = (uint32_t)nd.y * (uint32_t)g.pitch + nd.x;
             const double dx = (double)ux - ux_prev[c], dy = (double)uy - uy_prev[c];
@@ -902,17 +903,21 @@ __global__ __launch_bounds__(kBlock) void macro_kernel(const char *src, Layout l
             ux_prev[c] = ux;
             uy_prev[c] = uy;
         }
-    }
+        if (mass) {
+            const Rsrc row = state_row<T>(src, lay, nd.y);
+            double hsum = 0.0;
 #pragma unroll
-    for (int k = 0; k < MAC_SLOTS; ++k) {
-        const double rr = block_reduce<SumOp>(v[k], sh);
-        if (threadIdx.x == 0)
-            partials[(int64_t)k * gridDim.x + nd.L] = rr;
+            for (int i = 0; i < 9; ++i)
+                hsum += (double)(Elem<T>::ld(row, nd.x * sizeof(T), lay.h_off + i * lay.h_slot) *
+                                 inv_s);
+            v[MAC_MASS] = (double)ld_f32(row, nd.x * 4, 0) + hsum;
+        }
     }
+    block_sums<MAC_SLOTS>(v, partials, nd.L, gridDim.x);
 }
 
-// The read-out sums of macro_kernel (no field outputs, no residual) with a
-// fixed grid: workgroup b walks the lattice's 256-node blocks b, b + G, ...
+// The read-out sums of macro_sums_kernel (no residual, no mass) with a fixed
+// grid: workgroup b walks the lattice's 256-node blocks b, b + G, ...
 // and writes one partial per slot, partials[k][b], so the partial count is
 // the grid size whatever the lattice size.
 template <typename T, int BCX, int BCY>
@@ -922,7 +927,6 @@ __global__ __launch_bounds__(kBlock) void macro_strided_kernel(const char *src, 
                                                                 float inv_s, int bpr, int nblocks,
                                                                 double *partials)
 {
-    __shared__ double sh[kBlock / 64];
     double v[MAC_SLOTS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     for (int L = blockIdx.x; L < nblocks; L += gridDim.x) {
         const int y = L / bpr;
@@ -931,19 +935,10 @@ __global__ __launch_bounds__(kBlock) void macro_strided_kernel(const char *src, 
             double rp;
             float ux, uy;
             readout_node<T, BCX, BCY>(src, lay, med, mlay, g, ph, s, inv_s, y, x, rp, ux, uy);
-            v[MAC_FLUX] += rp * (double)ux;
-            v[MAC_UX] += ux;
-            v[MAC_U2] += (double)ux * ux + (double)uy * uy;
-            v[MAC_RHO] += rp;
-            v[MAC_QOUT] += (x == (uint32_t)g.nx - 1) ? rp * (double)ux : 0.0;
+            macro_sums_of(rp, ux, uy, x == (uint32_t)g.nx - 1, v);
         }
     }
-#pragma unroll
-    for (int k = 0; k < MAC_SLOTS; ++k) {
-        const double rr = block_reduce<SumOp>(v[k], sh);
-        if (threadIdx.x == 0)
-            partials[(int64_t)k * gridDim.x + blockIdx.x] = rr;
-    }
+    block_sums<MAC_SLOTS>(v, partials, blockIdx.x, gridDim.x);
 }
 
 template <typename T>
@@ -951,112 +946,129 @@ __global__ __launch_bounds__(kBlock) void state_sums_kernel(const char *src, Lay
                                                              float inv_s, double *partials,
                                                              int bpr)
 {
-    __shared__ double sh[kBlock / 64];
     const Node nd = node_of(bpr);
-    double mass = 0.0, hmax = 0.0, bad = 0.0;
+    double mass = 0.0;
+    float hmax = 0.0f;
+    int bad = 0;
     if (nd.x < (uint32_t)g.nx) {
         const Rsrc row = state_row<T>(src, lay, nd.y);
         const float rho = ld_f32(row, nd.x * 4, 0);
         double hsum = 0.0;
-        bad += isfinite(rho) ? 0.0 : 1.0;
+        bad += isfinite(rho) ? 0 : 1;
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             const float v = Elem<T>::ld(row, nd.x * sizeof(T), lay.h_off + i * lay.h_slot) * inv_s;
             hsum += (double)v;
-            const double a = fabs((double)v);
+            const float a = fabsf(v);
             hmax = a > hmax ? a : hmax;
-            bad += isfinite(v) ? 0.0 : 1.0;
+            bad += isfinite(v) ? 0 : 1;
         }
         mass = (double)rho + hsum;
     }
-    double r = block_reduce<SumOp>(mass, sh);
-    if (threadIdx.x == 0)
-        partials[(int64_t)ST_MASS * gridDim.x + nd.L] = r;
-    r = block_reduce<MaxOp>(hmax, sh);
-    if (threadIdx.x == 0)
-        partials[(int64_t)ST_HMAX * gridDim.x + nd.L] = r;
-    r = block_reduce<SumOp>(bad, sh);
-    if (threadIdx.x == 0)
-        partials[(int64_t)ST_BAD * gridDim.x + nd.L] = r;
+    block_state(mass, hmax, bad, partials, nd.L, gridDim.x);
 }
 
 // Read-out of every sample of a batch: per-tile FP64 partials
 // [MAC_SLOTS][ntiles] (tiles of kBlock nodes), reduced per sample by
 // batch_finish_kernel in a fixed order.
 template <typename T, int BCX, int BCY>
-__global__ __launch_bounds__(kBlock) void batch_macro_kernel(const SampleDesc *samples,
-                                                              const int *tile_sample, int ntiles,
-                                                              int parity, double *partials)
+__global__ __launch_bounds__(kBlock) void batch_macro_kernel(
+    const SampleDesc *__restrict__ samples, const int *__restrict__ tile_sample, int ntiles,
+    int parity, double *__restrict__ partials)
 {
-    __shared__ double sh[kBlock / 64];
-    const int t = blockIdx.x;
-    const int si = tile_sample[t];
-    const SampleDesc &sd = samples[si];
+    const int t = xcd_remap(blockIdx.x, gridDim.x);
+    const SampleDesc sd = samples[tile_sample[t]];
     const int rel = t - sd.tile0;
     const int y = rel / sd.tpr;
     const uint32_t x = (uint32_t)(rel - y * sd.tpr) * kBlock + threadIdx.x;
     double v[MAC_SLOTS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (x < (uint32_t)sd.g.nx) {
-        const Rows R = rows_of<BCY>(sd.state[parity], sd.lay, sd.g, y);
-        const Med md{med_row(sd.med, sd.mlay, y), sd.mlay.slot, 2 * sd.mlay.slot};
-        float d[9], inc, r;
-        const float rho =
-            post_stream<T, BCX>(R, sd.lay, md, sd.g, sd.ph, sd.s, sd.inv_s, x, d, inc, r);
-        float jx, jy, ux, uy, Fx, Fy;
-        momentum(d, jx, jy);
-        if (Elem<T>::kScaled) {
-            jx *= sd.inv_s;
-            jy *= sd.inv_s;
-        }
-        velocity(sd.ph, rho, jx, jy, md.eps(x), md.drag(x), md.kn0(x), ux, uy, Fx, Fy);
-        const double rp = (double)rho + (double)r;
-        v[MAC_FLUX] = rp * (double)ux;
-        v[MAC_UX] = ux;
-        v[MAC_U2] = (double)ux * ux + (double)uy * uy;
-        v[MAC_RHO] = rp;
-        v[MAC_QOUT] = (x == (uint32_t)sd.g.nx - 1) ? rp * (double)ux : 0.0;
+        double rp;
+        float ux, uy;
+        readout_node<T, BCX, BCY>(parity ? sd.state[1] : sd.state[0], sd.lay, sd.med, sd.mlay,
+                                  sd.g, sd.ph, sd.s, sd.inv_s, y, x, rp, ux, uy);
+        macro_sums_of(rp, ux, uy, x == (uint32_t)sd.g.nx - 1, v);
+    }
+    block_sums<MAC_SLOTS>(v, partials, t, ntiles);
+}
+
+// Sum (or, for is_max, the maximum from 0) of p[0 .. n) in a fixed order by
+// one workgroup of kFinish threads, the result on thread 0.  Eight loads are
+// in flight per thread: one workgroup of 256 threads walking the slots one
+// after the other, a load at a time, took 669 us for the six slots of
+// 65,536 partials (4096 x 4096 nodes), a wait for memory per load; a slot
+// per workgroup of 1024 threads is bound by what one compute unit can read.
+__device__ __forceinline__ double finish_range(const double *__restrict__ p, int n, bool is_max)
+{
+    __shared__ double sh[kFinish / 64];
+    constexpr int U = 8;
+    auto op = [&](double a, double b) { return is_max ? (b > a ? b : a) : a + b; };
+    double acc[U] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    int j = threadIdx.x;
+    for (; j + (U - 1) * kFinish < n; j += U * kFinish) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            v[u] = p[j + u * kFinish];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            acc[u] = op(acc[u], v[u]);
     }
 #pragma unroll
-    for (int k = 0; k < MAC_SLOTS; ++k) {
-        const double rr = block_reduce<SumOp>(v[k], sh);
-        if (threadIdx.x == 0)
-            partials[(int64_t)k * ntiles + t] = rr;
-    }
+    for (int u = 0; u < U; ++u)
+        if (j + u * kFinish < n)
+            acc[u] = op(acc[u], p[j + u * kFinish]);
+#pragma unroll
+    for (int h = U / 2; h > 0; h >>= 1)
+#pragma unroll
+        for (int u = 0; u < h; ++u)
+            acc[u] = op(acc[u], acc[u + h]);
+    double r = acc[0];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+        r = op(r, __shfl_xor(r, off, 64));
+    if ((threadIdx.x & 63) == 0)
+        sh[threadIdx.x >> 6] = r;
+    __syncthreads();
+    r = sh[0];
+#pragma unroll
+    for (int w = 1; w < kFinish / 64; ++w)
+        r = op(r, sh[w]);
+    return r;
 }
 
-// out[s][k] = sum of partials[k][tile0(s) .. tile0(s) + tiles(s)) in order.
-__global__ __launch_bounds__(kBlock) void batch_finish_kernel(const SampleDesc *samples,
-                                                               const double *partials, int slots,
-                                                               int ntiles, double *out)
+// out[s][k] = sum of partials[k][tile0(s) .. tile0(s) + tiles(s)): workgroup
+// (s, k), in the order of finish_kernel.
+__global__ __launch_bounds__(kFinish) void batch_finish_kernel(
+    const SampleDesc *__restrict__ samples, const double *__restrict__ partials, int slots,
+    int ntiles, double *__restrict__ out)
 {
-    __shared__ double sh[kBlock / 64];
-    const SampleDesc &sd = samples[blockIdx.x];
-    const int t0 = sd.tile0, n = sd.tpr * sd.g.ny;
-    for (int k = 0; k < slots; ++k) {
-        const double *p = partials + (int64_t)k * ntiles + t0;
-        double v = 0.0;
-        for (int j = threadIdx.x; j < n; j += kBlock)
-            v += p[j];
-        const double r = block_reduce<SumOp>(v, sh);
-        if (threadIdx.x == 0)
-            out[(int64_t)blockIdx.x * slots + k] = r;
-    }
+    const int s = blockIdx.x, k = blockIdx.y;
+    const int t0 = samples[s].tile0, n = samples[s].tpr * samples[s].g.ny;
+    const double r = finish_range(partials + (int64_t)k * ntiles + t0, n, false);
+    if (threadIdx.x == 0)
+        out[(int64_t)s * slots + k] = r;
 }
 
-__global__ __launch_bounds__(kBlock) void finish_kernel(const double *partials, int slots,
-                                                         int blocks, unsigned max_mask,
-                                                         double *out)
+// out[k] = sum (or maximum) of partials[k][0 .. blocks): workgroup k.  With
+// `done` (coherent host memory, as `out` then is) workgroup k also sets
+// done[k] = seq once its result is visible to the host, which polls for it
+// instead of waiting for the stream.
+__global__ __launch_bounds__(kFinish) void finish_kernel(const double *__restrict__ partials,
+                                                          int blocks, unsigned max_mask,
+                                                          double *__restrict__ out,
+                                                          uint64_t *done, uint64_t seq)
 {
-    __shared__ double sh[kBlock / 64];
-    for (int k = 0; k < slots; ++k) {
-        const bool is_max = (max_mask >> k) & 1u;
-        const double *p = partials + (int64_t)k * blocks;
-        double v = 0.0;
-        for (int j = threadIdx.x; j < blocks; j += kBlock)
-            v = is_max ? (p[j] > v ? p[j] : v) : v + p[j];
-        const double r = is_max ? block_reduce<MaxOp>(v, sh) : block_reduce<SumOp>(v, sh);
-        if (threadIdx.x == 0)
+    const int k = blockIdx.x;
+    const double r =
+        finish_range(partials + (int64_t)k * blocks, blocks, ((max_mask >> k) & 1u) != 0);
+    if (threadIdx.x == 0) {
+        if (done) {
+            __hip_atomic_store(&out[k], r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(&done[k], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        } else {
             out[k] = r;
+        }
     }
 }
 
@@ -1065,23 +1077,20 @@ __global__ __launch_bounds__(kBlock) void finish_kernel(const double *partials, 
 __global__ __launch_bounds__(kBlock) void fields_kernel(char *med, MLayout mlay, Geom g,
                                                          double nu, double *partials, int bpr)
 {
-    __shared__ double sh[kBlock / 64];
     const Node nd = node_of(bpr);
-    double bad = 0.0;
+    double bad[1] = {0.0};
     if (nd.x < (uint32_t)g.nx) {
         const Rsrc row = med_row(med, mlay, nd.y);
         const float e = ld_f32(row, nd.x * 4, 0), k = ld_f32(row, nd.x * 4, mlay.slot),
                     kn = ld_f32(row, nd.x * 4, 2 * mlay.slot);
         const bool ok = (e >= 0.0f && e <= 1.0f) && (k > 0.0f) && (kn >= 0.0f) && isfinite(kn);
-        bad = ok ? 0.0 : 1.0;
+        bad[0] = ok ? 0.0 : 1.0;
         double d = 0.0;
         if (ok && e > 0.0f && isfinite(k))
             d = (double)e * nu / (double)k;
         st_f32(row, nd.x * 4, mlay.slot, (float)d, false);
     }
-    const double r = block_reduce<SumOp>(bad, sh);
-    if (threadIdx.x == 0)
-        partials[(int64_t)FLD_BAD * gridDim.x + nd.L] = r;
+    block_sums<FLD_SLOTS>(bad, partials, nd.L, gridDim.x);
 }
 
 template <typename T>
@@ -1210,14 +1219,26 @@ static hipError_t sweep3x_t(const char *src, char *dst, const Layout &lay, const
 template <typename T, int BCX, int BCY>
 static hipError_t macro_t(const char *src, const Layout &lay, const char *med,
                           const MLayout &mlay, const Geom &g, const Physics &ph, float s,
-                          float inv_s,
-                          float *rho_out, float *ux_out, float *uy_out, float *ux_prev,
-                          float *uy_prev, double *partials, hipStream_t st)
+                          float inv_s, float *rho_out, float *ux_out, float *uy_out,
+                          hipStream_t st)
 {
     const Launch l = launch_of(g);
     hipLaunchKernelGGL((macro_kernel<T, BCX, BCY>), dim3(l.blocks), dim3(kBlock), 0, st, src,
                        lay, med, mlay, g, ph, s, inv_s, l.blocks_per_row, rho_out, ux_out,
-                       uy_out, ux_prev, uy_prev, partials);
+                       uy_out);
+    return hipGetLastError();
+}
+
+template <typename T, int BCX, int BCY>
+static hipError_t macro_sums_t(const char *src, const Layout &lay, const char *med,
+                               const MLayout &mlay, const Geom &g, const Physics &ph, float s,
+                               float inv_s, float *ux_prev, float *uy_prev, bool mass,
+                               double *partials, hipStream_t st)
+{
+    const Launch l = launch_of(g);
+    hipLaunchKernelGGL((macro_sums_kernel<T, BCX, BCY>), dim3(l.blocks), dim3(kBlock), 0, st,
+                       src, lay, med, mlay, g, ph, s, inv_s, l.blocks_per_row, ux_prev, uy_prev,
+                       mass ? 1 : 0, partials);
     return hipGetLastError();
 }
 
@@ -1308,12 +1329,22 @@ hipError_t launch_sweep3x(int storage, int bcx, int bcy, const char *src, char *
 hipError_t launch_macro(int storage, int bcx, int bcy, const char *src, const Layout &lay,
                         const char *med, const MLayout &mlay, const Geom &g, const Physics &ph,
                         float s, float inv_s, float *rho_out, float *ux_out, float *uy_out,
-                        float *ux_prev, float *uy_prev, double *partials, hipStream_t st)
+                        hipStream_t st)
 {
     if (bcy < 0 || bcy > 1)
         return hipErrorInvalidValue;
-    LBK_DISPATCH(macro_t, src, lay, med, mlay, g, ph, s, inv_s, rho_out, ux_out, uy_out,
-                 ux_prev, uy_prev, partials, st)
+    LBK_DISPATCH(macro_t, src, lay, med, mlay, g, ph, s, inv_s, rho_out, ux_out, uy_out, st)
+}
+
+hipError_t launch_macro_sums(int storage, int bcx, int bcy, const char *src, const Layout &lay,
+                             const char *med, const MLayout &mlay, const Geom &g,
+                             const Physics &ph, float s, float inv_s, float *ux_prev,
+                             float *uy_prev, bool mass, double *partials, hipStream_t st)
+{
+    if (bcy < 0 || bcy > 1)
+        return hipErrorInvalidValue;
+    LBK_DISPATCH(macro_sums_t, src, lay, med, mlay, g, ph, s, inv_s, ux_prev, uy_prev, mass,
+                 partials, st)
 }
 
 hipError_t launch_macro_strided(int storage, int bcx, int bcy, const char *src,
@@ -1334,10 +1365,10 @@ hipError_t launch_state_sums(int storage, const char *src, const Layout &lay, co
 }
 
 hipError_t launch_finish(const double *partials, int slots, int blocks, unsigned max_mask,
-                         double *out, hipStream_t st)
+                         double *out, uint64_t *done, uint64_t seq, hipStream_t st)
 {
-    hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(kBlock), 0, st, partials, slots, blocks,
-                       max_mask, out);
+    hipLaunchKernelGGL(finish_kernel, dim3(slots), dim3(kFinish), 0, st, partials, blocks,
+                       max_mask, out, done, seq);
     return hipGetLastError();
 }
 
@@ -1466,7 +1497,7 @@ hipError_t launch_batch_macro(int storage, int bcx, int bcy, const SampleDesc *s
 hipError_t launch_batch_finish(const SampleDesc *samples, int nsamples, const double *partials,
                                int slots, int ntiles, double *out, hipStream_t st)
 {
-    hipLaunchKernelGGL(batch_finish_kernel, dim3(nsamples), dim3(kBlock), 0, st, samples,
+    hipLaunchKernelGGL(batch_finish_kernel, dim3(nsamples, slots), dim3(kFinish), 0, st, samples,
                        partials, slots, ntiles, out);
     return hipGetLastError();
 }

@@ -104,7 +104,7 @@ extern "C" lbk_status lbk_apparent_permeability_noalloc(lbk_lattice *lat, double
     HIP_TRY(launch_macro_strided(d.storage, d.bc_x, d.bc_y, lat->state(lat->cur), lat->L.lay,
                                  lat->med(), lat->L.mlay, lat->g, lat->ph, lat->s(),
                                  lat->inv_s(), grid, partials, lat->stream));
-    HIP_TRY(launch_finish(partials, MAC_SLOTS, grid, 0, totals, lat->stream));
+    HIP_TRY(launch_finish(partials, MAC_SLOTS, grid, 0, totals, nullptr, 0, lat->stream));
     double sums[MAC_SLOTS];
     HIP_TRY(hipMemcpyAsync(sums, totals, sizeof sums, hipMemcpyDeviceToHost, lat->stream));
     HIP_TRY(hipStreamSynchronize(lat->stream));
