@@ -259,6 +259,7 @@ lbk_status lbk3_create(const lbk_desc3 *d, const float *eps, const float *k, con
     ph.corr = d->correlation;
     ph.slip_nb = (float)(-d->slip_b);
     ph.slip_c = (float)(4.0 - d->slip_b);
+    ph.derive();
 
     hipStream_t st = lat->stream;
     char *med = lat->med();

@@ -166,9 +166,9 @@ template <typename T>
 __device__ __forceinline__ float density3(float rc, const float (&d)[19], float inv_s,
                                           float &inc, float &r)
 {
-    float sum = 0.0f;
+    float sum = d[0];
 #pragma unroll
-    for (int i = 0; i < 19; ++i)
+    for (int i = 1; i < 19; ++i)
         sum += d[i];
     const float sp = Elem<T>::kScaled ? sum * inv_s : sum;
     const float rho = rc + sp;
@@ -202,29 +202,38 @@ __device__ __forceinline__ void velocity3(const Physics3 &p3, float rho, const f
 #pragma unroll
     for (int a = 0; a < 3; ++a)
         v[a] = j[a] * rinv + 0.5f * eps * G[a];
-    float g, ag, B = 0.0f;
-    if (ph.feps == 0.0f) {
+    const bool solid = !(eps > 0.0f);
+    if (!forchheimer(ph)) {
         const float dn = drag * num;
         const float R2 = 2.0f * __builtin_amdgcn_rcpf(2.0f * den + dn);
-        g = den * R2;
-        ag = dn * R2;
+        const float g = den * R2, ag = dn * R2;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            u[a] = g * v[a];
+            F[a] = eps * G[a] - ag * v[a];
+        }
     } else {
         const float A = drag * num * __builtin_amdgcn_rcpf(den);
-        B = ph.feps * __builtin_sqrtf(eps * A * ph.inv_nu);
+        const float B = ph.feps * __builtin_sqrtf(eps * A * ph.inv_nu);
         const float c0 = 1.0f + 0.5f * A;
         const float wn = __builtin_sqrtf(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-        g = 2.0f / (c0 + __builtin_sqrtf(c0 * c0 + 2.0f * B * wn));
-        ag = A * g;
+        const float g = 2.0f / (c0 + __builtin_sqrtf(c0 * c0 + 2.0f * B * wn));
+        const float ag = A * g;
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            u[a] = solid ? 0.0f : g * v[a];
+        const float bu = B * __builtin_sqrtf(u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            F[a] = eps * G[a] - ag * v[a] - bu * u[a];
     }
-    const bool solid = !(eps > 0.0f);
+    if (any_lane(solid)) { // most waves hold none
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-        u[a] = solid ? 0.0f : g * v[a];
-    const float bu = (ph.feps != 0.0f) ? B * __builtin_sqrtf(u[0] * u[0] + u[1] * u[1] + u[2] * u[2])
-                                       : 0.0f;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-        F[a] = solid ? -2.0f * j[a] * rinv : eps * G[a] - ag * v[a] - bu * u[a];
+        for (int a = 0; a < 3; ++a) {
+            u[a] = solid ? 0.0f : u[a];
+            F[a] = solid ? -2.0f * j[a] * rinv : F[a];
+        }
+    }
 }
 
 // BGK + Guo in deviation form over the opposite pairs (see the D2Q9
@@ -236,12 +245,14 @@ __device__ __forceinline__ void collide3(const Physics &ph, float rho, float inc
                                          float (&hs)[19])
 {
     const bool solid = !(eps > 0.0f);
-    const float ie = solid ? 0.0f : __builtin_amdgcn_rcpf(eps);
-    const float om = ph.omega, cg = ph.guo, keep = 1.0f - om;
+    float ie = __builtin_amdgcn_rcpf(eps);
+    if (any_lane(solid))
+        ie = solid ? 0.0f : ie;
+    const float om = ph.omega, cg = ph.guo, keep = ph.keep;
     float C = om * r - keep * inc +
               rho * ie *
-                  (-1.5f * om * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]) -
-                   3.0f * cg * (u[0] * F[0] + u[1] * F[1] + u[2] * F[2]));
+                  (ph.om15 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]) -
+                   ph.guo3 * (u[0] * F[0] + u[1] * F[1] + u[2] * F[2]));
     float rs = rho;
     if (Elem<T>::kScaled) {
         C *= s;

@@ -335,6 +335,7 @@ lbk_status lbk_create(const lbk_desc *d, const float *eps, const float *k, const
     ph.corr = d->correlation;
     ph.slip_nb = (float)(-d->slip_b);
     ph.slip_c = (float)(4.0 - d->slip_b);
+    ph.derive();
 
     char *ws = lat->ws;
     char *med = lat->med();

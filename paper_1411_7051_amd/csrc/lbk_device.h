@@ -237,9 +237,43 @@ struct Physics {
     int corr;        // slip correlation: CORR_BKC, CORR_KLINKENBERG, CORR_NONE
     float slip_nb;   // -b, b the slip coefficient of Eq. 6
     float slip_c;    // 4 - b
+    // derived scalars of the collide, rounded as the expressions they stand
+    // for (the device has no scalar FP32 unit: each was a vector instruction
+    // per node)
+    float keep;      // 1 - omega
+    float om15;      // -1.5 omega
+    float guo3;      // 3 guo
+    void derive()
+    {
+        keep = 1.0f - omega;
+        om15 = -1.5f * omega;
+        guo3 = 3.0f * guo;
+    }
 };
 
 enum { CORR_BKC = 0, CORR_KLINKENBERG = 1, CORR_NONE = 2 };
+
+// Whether v holds for any active lane of the wave, followed by a branch that
+// stays a branch: the empty statement keeps the compiler from computing what
+// few waves need for every node and selecting afterwards.
+__device__ __forceinline__ bool any_lane(bool v)
+{
+    if (__builtin_amdgcn_ballot_w64(v) == 0)
+        return false;
+    asm volatile("");
+    return true;
+}
+// Whether the Forchheimer term is on: a scalar test (the bits of f_eps, its
+// sign apart) and a branch that stays one.  With a select in its place the
+// square roots of Eq. 2 were evaluated for every node of a Darcy run, about
+// 28 of its 190 vector instructions per update.
+__device__ __forceinline__ bool forchheimer(const Physics &ph)
+{
+    if ((__float_as_uint(ph.feps) << 1) == 0u)
+        return false;
+    asm volatile("");
+    return true;
+}
 
 // Correction factor of the selected correlation as a ratio f_c = den / num
 // (one reciprocal serves f_c and the velocity solve):
@@ -395,9 +429,9 @@ template <typename T>
 __device__ __forceinline__ float density(float rc, const float (&d)[9], float inv_s, float &inc,
                                          float &r)
 {
-    float sum = 0.0f;
+    float sum = d[0];
 #pragma unroll
-    for (int i = 0; i < 9; ++i)
+    for (int i = 1; i < 9; ++i)
         sum += d[i];
     const float sp = Elem<T>::kScaled ? sum * inv_s : sum;
     const float rho = rc + sp;
@@ -410,7 +444,7 @@ __device__ __forceinline__ float density(float rc, const float (&d)[9], float in
 __device__ __forceinline__ void momentum(const float (&d)[9], float &jx, float &jy)
 {
     jx = (d[1] - d[3]) + (d[5] - d[7]) + (d[8] - d[6]);
-    jy = (d[2] - d[4]) + (d[5] - d[7]) + (d[6] - d[8]);
+    jy = (d[2] - d[4]) + (d[5] - d[7]) - (d[8] - d[6]); // one difference serves both
 }
 
 // Velocity and force of one node from rho and j = sum f e: Eq. 16b solved
@@ -435,34 +469,39 @@ __device__ __forceinline__ void velocity(const Physics &ph, float rho, float jx,
     const float egx = eps * ph.gx, egy = eps * ph.gy;
     const float vx = jx * rinv + 0.5f * egx;
     const float vy = jy * rinv + 0.5f * egy;
-    float g, ag, B = 0.0f;
-    if (ph.feps == 0.0f) {
+    const bool solid = !(eps > 0.0f);
+    if (!forchheimer(ph)) {
         const float dn = drag * num;
         const float R2 = 2.0f * __builtin_amdgcn_rcpf(2.0f * den + dn);
-        g = den * R2;
-        ag = dn * R2;
+        const float g = den * R2, ag = dn * R2;
+        ux = g * vx;
+        uy = g * vy;
+        Fx = egx - ag * vx;
+        Fy = egy - ag * vy;
     } else {
         // Forchheimer (Eq. 2): (1 + A/2) u + (B/2) |u| u = v with
         // B = eps F_eps / sqrt(k_a), k_a = eps nu / A; positive root of
         // the quadratic in |u|, rationalized.
         const float A = drag * num * __builtin_amdgcn_rcpf(den);
-        B = ph.feps * __builtin_sqrtf(eps * A * ph.inv_nu);
+        const float B = ph.feps * __builtin_sqrtf(eps * A * ph.inv_nu);
         const float c0 = 1.0f + 0.5f * A;
         const float wn = __builtin_sqrtf(vx * vx + vy * vy);
-        g = 2.0f / (c0 + __builtin_sqrtf(c0 * c0 + 2.0f * B * wn));
-        ag = A * g;
-    }
-    const bool solid = !(eps > 0.0f);
-    ux = solid ? 0.0f : g * vx;
-    uy = solid ? 0.0f : g * vy;
-    float fx = egx - ag * vx, fy = egy - ag * vy;
-    if (ph.feps != 0.0f) {
+        const float g = 2.0f / (c0 + __builtin_sqrtf(c0 * c0 + 2.0f * B * wn));
+        const float ag = A * g;
+        ux = solid ? 0.0f : g * vx;
+        uy = solid ? 0.0f : g * vy;
+        Fx = egx - ag * vx;
+        Fy = egy - ag * vy;
         const float bu = B * __builtin_sqrtf(ux * ux + uy * uy);
-        fx -= bu * ux;
-        fy -= bu * uy;
+        Fx -= bu * ux;
+        Fy -= bu * uy;
     }
-    Fx = solid ? -2.0f * jx * rinv : fx;
-    Fy = solid ? -2.0f * jy * rinv : fy;
+    if (any_lane(solid)) { // most waves hold none
+        ux = solid ? 0.0f : ux;
+        uy = solid ? 0.0f : uy;
+        Fx = solid ? -2.0f * jx * rinv : Fx;
+        Fy = solid ? -2.0f * jy * rinv : Fy;
+    }
 }
 
 // BGK relaxation with Guo forcing (Eqs. 12, 14, 15) in deviation form.
@@ -481,10 +520,12 @@ __device__ __forceinline__ void collide(const Physics &ph, float rho, float inc,
                                         float Fy, float eps, float s, float (&hs)[9])
 {
     const bool solid = !(eps > 0.0f);
-    const float ie = solid ? 0.0f : __builtin_amdgcn_rcpf(eps);
-    const float om = ph.omega, cg = ph.guo, keep = 1.0f - om;
+    float ie = __builtin_amdgcn_rcpf(eps);
+    if (any_lane(solid))
+        ie = solid ? 0.0f : ie;
+    const float om = ph.omega, cg = ph.guo, keep = ph.keep;
     float C = om * r - keep * inc +
-              rho * ie * (-1.5f * om * (ux * ux + uy * uy) - 3.0f * cg * (ux * Fx + uy * Fy));
+              rho * ie * (ph.om15 * (ux * ux + uy * uy) - ph.guo3 * (ux * Fx + uy * Fy));
     float rs = rho;
     if (Elem<T>::kScaled) {
         C *= s;
