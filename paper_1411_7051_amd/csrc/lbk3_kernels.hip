@@ -227,7 +227,7 @@ __device__ __forceinline__ void velocity3(const Physics3 &p3, float rho, const f
         for (int a = 0; a < 3; ++a)
             F[a] = eps * G[a] - ag * v[a] - bu * u[a];
     }
-    if (any_lane(solid)) { // most waves hold none
+    if (uniform_branch(any_lane(solid))) { // most waves hold none
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             u[a] = solid ? 0.0f : u[a];
@@ -246,7 +246,7 @@ __device__ __forceinline__ void collide3(const Physics &ph, float rho, float inc
 {
     const bool solid = !(eps > 0.0f);
     float ie = __builtin_amdgcn_rcpf(eps);
-    if (any_lane(solid))
+    if (uniform_branch(any_lane(solid)))
         ie = solid ? 0.0f : ie;
     const float om = ph.omega, cg = ph.guo, keep = ph.keep;
     float C = om * r - keep * inc +

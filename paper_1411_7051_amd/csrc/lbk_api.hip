@@ -122,43 +122,102 @@ void split(double v, float &hi, float &lo)
 
 } // namespace
 
-// n steps of the lattice on stream st: when the lattice takes three-step
-// passes, triples of steps fused into one pass (launch_sweep3x), the rest
-// in a two-step pass or a single sweep; when it takes two-step passes,
-// pairs of steps fused into one pass (launch_sweep2) and a single sweep if
-// n is odd; otherwise n single sweeps.  Every pass is bitwise the single
-// sweeps it replaces.
-lbk_status lbk::advance(lbk_lattice *lat, int64_t n, hipStream_t st)
+// Shape and steps of a lattice's tile passes: the least predicted time per
+// step.  A launch costs about 4.2 us (dispatch, the latency of the loads, the
+// drain of the stores) and each row update a workgroup makes u_inf per tile
+// of its compute unit's share plus c for what one tile alone leaves
+// exposed (its waves wait for one another at every step); u_inf and c in us,
+// for one and two rows per wave, fit the measured times of lattices from
+// 33 x 21 to 4096 x 4096 within about 15%, which orders the shapes right:
+// 64 x 32 takes 8 x 1 rows and 3 steps (2.0 us a step; 16 x 1 and 6 steps
+// 2.3), 256 x 256 16 x 1 and 5 (2.4; 16 x 2 and 5 4.4), 1024 x 512 16 x 1 and 3
+// (6.9; 8 x 2 and 3 7.1), 4096 x 4096 16 x 2 and 4 (108; 16 x 1 and 3 137).
+TilePlan lbk::tile_plan(int nx, int ny)
+{
+    static const TilePlan cand[] = {{{8, 1}, 3},  {{12, 1}, 4}, {{16, 1}, 3}, {{16, 1}, 4},
+                                    {{16, 1}, 5}, {{16, 2}, 4}, {{16, 2}, 5}};
+    const double launch_us = 4.2, u_inf[2] = {0.100, 0.078}, c[2] = {0.060, 0.070};
+    const int cus = 256;
+    TilePlan best = cand[0];
+    double best_us = INFINITY;
+    for (const TilePlan &p : cand) {
+        const int H = p.tile.waves * p.tile.rows, R = p.tile.rows;
+        const int own_x = 64 - 2 * p.steps, own_y = H - 2 * p.steps;
+        const double tiles = (double)((nx + own_x - 1) / own_x) * ((ny + own_y - 1) / own_y);
+        // tiles of the busiest compute unit: whole ones while they are few
+        const double q = tiles <= 8.0 * cus ? ceil(tiles / cus) : tiles / cus;
+        int rows = 0; // row updates of a tile: waves with rows k + 1 .. H - 2 - k
+        for (int k = 0; k < p.steps; ++k)
+            for (int j = 0; j < H; j += R)
+                rows += (j + R <= k + 1 || j > H - 2 - k) ? 0 : R;
+        const double us = (launch_us + rows * (q * u_inf[R - 1] + c[R - 1])) / p.steps;
+        if (us < best_us) {
+            best_us = us;
+            best = p;
+        }
+    }
+    return best;
+}
+
+// The next launch of `left` >= 1 steps.  Tile passes share the steps evenly
+// (20 steps at up to 6 a launch are four fives); three-step passes leave a
+// remainder to a two-step pass or a single sweep.  Every pass is bitwise the
+// single sweeps it replaces.
+Pass lbk::next_pass(const lbk_lattice *lat, int64_t left)
+{
+    if (left > 1 && tile_pass(lat)) {
+        const TilePlan p = tile_plan(lat->d.nx, lat->d.ny);
+        const int64_t launches = (left + p.steps - 1) / p.steps;
+        const int steps = (int)((left + launches - 1) / launches);
+        if (steps > 1)
+            return Pass{PASS_TILE, steps, p.tile};
+        return Pass{PASS_ONE, 1, {}};
+    }
+    if (left > 2 && three_step_pass(lat))
+        return Pass{PASS_THREE, 3, {}};
+    if (left > 1 && two_step_pass(lat))
+        return Pass{PASS_TWO, 2, {}};
+    return Pass{PASS_ONE, 1, {}};
+}
+
+hipError_t lbk::launch_pass(const lbk_lattice *lat, const Pass &p, const char *src, char *dst,
+                            float *hist, size_t hist_bytes, hipStream_t st)
 {
     const lbk_desc &d = lat->d;
-    int64_t i = 0;
-    for (; three_step_pass(lat) && i + 2 < n; i += 3) {
-        const int nxt = lat->cur ^ 1;
-        HIP_TRY(launch_sweep3x(d.storage, d.bc_x, d.bc_y, lat->state(lat->cur),
-                               lat->state(nxt), lat->L.lay, lat->med(), lat->L.mlay, lat->g,
-                               lat->ph, lat->s(), lat->inv_s(), fwd_band3(d), nullptr,
-                               nullptr, nullptr, st));
-        lat->cur = nxt;
-        lat->t += 3;
-        ++lat->version;
+    auto slot = [&](int k) {
+        return hist ? reinterpret_cast<float *>(reinterpret_cast<char *>(hist) + k * hist_bytes)
+                    : nullptr;
+    };
+    switch (p.kind) {
+    case PASS_TILE:
+        return launch_tile(d.storage, d.bc_x, d.bc_y, src, dst, lat->L.lay, lat->med(),
+                           lat->L.mlay, lat->g, lat->ph, lat->s(), lat->inv_s(), p.tile, p.steps,
+                           hist, hist_bytes, st);
+    case PASS_THREE:
+        return launch_sweep3x(d.storage, d.bc_x, d.bc_y, src, dst, lat->L.lay, lat->med(),
+                              lat->L.mlay, lat->g, lat->ph, lat->s(), lat->inv_s(), fwd_band3(d),
+                              slot(0), slot(1), slot(2), st);
+    case PASS_TWO:
+        return launch_sweep2(d.storage, d.bc_x, d.bc_y, src, dst, lat->L.lay, lat->med(),
+                             lat->L.mlay, lat->g, lat->ph, lat->s(), lat->inv_s(), fwd_band(d),
+                             slot(0), slot(1), st);
+    default:
+        return launch_sweep(d.storage, d.bc_x, d.bc_y, src, dst, lat->L.lay, lat->med(),
+                            lat->L.mlay, lat->g, lat->ph, lat->s(), lat->inv_s(), hist, st);
     }
-    for (; two_step_pass(lat) && i + 1 < n; i += 2) {
+}
+
+// n steps of the lattice on stream st.
+lbk_status lbk::advance(lbk_lattice *lat, int64_t n, hipStream_t st)
+{
+    for (int64_t i = 0; i < n;) {
+        const Pass p = next_pass(lat, n - i);
         const int nxt = lat->cur ^ 1;
-        HIP_TRY(launch_sweep2(d.storage, d.bc_x, d.bc_y, lat->state(lat->cur), lat->state(nxt),
-                              lat->L.lay, lat->med(), lat->L.mlay, lat->g, lat->ph, lat->s(),
-                              lat->inv_s(), fwd_band(d), nullptr, nullptr, st));
+        HIP_TRY(launch_pass(lat, p, lat->state(lat->cur), lat->state(nxt), nullptr, 0, st));
         lat->cur = nxt;
-        lat->t += 2;
+        lat->t += p.steps;
         ++lat->version;
-    }
-    for (; i < n; ++i) {
-        const int nxt = lat->cur ^ 1;
-        HIP_TRY(launch_sweep(d.storage, d.bc_x, d.bc_y, lat->state(lat->cur), lat->state(nxt),
-                             lat->L.lay, lat->med(), lat->L.mlay, lat->g, lat->ph, lat->s(),
-                             lat->inv_s(), nullptr, st));
-        lat->cur = nxt;
-        ++lat->t;
-        ++lat->version;
+        i += p.steps;
     }
     return LBK_OK;
 }
@@ -843,26 +902,9 @@ extern "C" lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws
     double *grad2 = reinterpret_cast<double *>(w + P.grad2);
     float *seg2 = kn ? reinterpret_cast<float *>(w + P.seg2) : nullptr;
     char *rec[2] = {level(P.rec, 0), level(P.rec, 1)};
-    auto sweep = [&](const char *src, char *dst, float *hist) {
-        return launch_sweep(d.storage, d.bc_x, d.bc_y, src, dst, lat->L.lay, lat->med(),
-                            lat->L.mlay, lat->g, lat->ph, lat->s(), lat->inv_s(), hist, st);
-    };
-    // two steps src -> dst in one pass, recording both when hist1 is given;
     // rebuilt inner checkpoints (no history) and recorded segments take
     // lbk_step's passes, the reverse steps pairs
-    const bool two = two_step_pass(lat), three = three_step_pass(lat);
-    auto sweep2 = [&](const char *src, char *dst, float *hist1, float *hist2) {
-        return launch_sweep2(d.storage, d.bc_x, d.bc_y, src, dst, lat->L.lay, lat->med(),
-                             lat->L.mlay, lat->g, lat->ph, lat->s(), lat->inv_s(),
-                             fwd_band(d), hist1, hist2, st);
-    };
-    // three steps src -> dst in one pass, recording all three when hist1
-    // is given
-    auto sweep3 = [&](const char *src, char *dst, float *hist1, float *hist2, float *hist3) {
-        return launch_sweep3x(d.storage, d.bc_x, d.bc_y, src, dst, lat->L.lay, lat->med(),
-                              lat->L.mlay, lat->g, lat->ph, lat->s(), lat->inv_s(),
-                              fwd_band3(d), hist1, hist2, hist3, st);
-    };
+    const bool two = two_step_pass(lat);
     const float a1 = (float)P.a1, a2 = (float)P.a2;
 
     HIP_TRY(hipMemsetAsync(grad, 0, (size_t)d.ny * lat->L.pitch * 8, st));
@@ -872,7 +914,8 @@ extern "C" lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws
         HIP_TRY(hipMemsetAsync(seg2, 0, (size_t)d.ny * lat->L.pitch * 4, st));
     }
     // read-out of J at step n: linearisation point of the pull of S_n
-    HIP_TRY(sweep(lat->state(lat->cur), rec[0], histp(0)));
+    HIP_TRY(launch_pass(lat, Pass{PASS_ONE, 1, {}}, lat->state(lat->cur), rec[0], histp(0),
+                        P.hist_bytes, st));
     HIP_TRY(launch_adjoint(d.bc_x, d.bc_y, nullptr, lam[0], histp(0), lat->med(), lat->L.mlay,
                            seg, seg2, lat->g, lat->ph, 1, a1, a2, P.outlet, st));
     int cur = 0;
@@ -900,16 +943,9 @@ extern "C" lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws
                     break; // the last inner segment needs no further state
                 for (int64_t i = 0; i < steps;) {
                     const char *from = i == 0 ? level(inner, nseg) : rec[r];
-                    if (three && i + 2 < steps) {
-                        HIP_TRY(sweep3(from, rec[r ^ 1], nullptr, nullptr, nullptr));
-                        i += 3;
-                    } else if (two && i + 1 < steps) {
-                        HIP_TRY(sweep2(from, rec[r ^ 1], nullptr, nullptr));
-                        i += 2;
-                    } else {
-                        HIP_TRY(sweep(from, rec[r ^ 1], nullptr));
-                        ++i;
-                    }
+                    const Pass p = next_pass(lat, steps - i);
+                    HIP_TRY(launch_pass(lat, p, from, rec[r ^ 1], nullptr, 0, st));
+                    i += p.steps;
                     r ^= 1;
                 }
                 src = rec[r];
@@ -926,17 +962,10 @@ extern "C" lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws
                 Range range("adjoint recompute");
                 for (int64_t t = a2s; t < b2s;) {
                     const char *from = t == a2s ? src : rec[r];
-                    if (three && t + 2 < b2s) {
-                        HIP_TRY(sweep3(from, rec[r ^ 1], histp(t - a2s + 1), histp(t - a2s + 2),
-                                       histp(t - a2s + 3)));
-                        t += 3;
-                    } else if (two && t + 1 < b2s) {
-                        HIP_TRY(sweep2(from, rec[r ^ 1], histp(t - a2s + 1), histp(t - a2s + 2)));
-                        t += 2;
-                    } else {
-                        HIP_TRY(sweep(from, rec[r ^ 1], histp(t - a2s + 1)));
-                        ++t;
-                    }
+                    const Pass p = next_pass(lat, b2s - t);
+                    HIP_TRY(launch_pass(lat, p, from, rec[r ^ 1], histp(t - a2s + 1),
+                                        P.hist_bytes, st));
+                    t += p.steps;
                     r ^= 1;
                 }
             }

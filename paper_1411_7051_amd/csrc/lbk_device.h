@@ -243,8 +243,11 @@ struct Physics {
     float keep;      // 1 - omega
     float om15;      // -1.5 omega
     float guo3;      // 3 guo
+    int standard;    // the default model under a pressure drive (MODEL_STD)
     void derive()
     {
+        standard = corr == 0 && feps == 0.0f && kn_local && rho_ref == 1.0f && gx == 0.0f &&
+                   gy == 0.0f;
         keep = 1.0f - omega;
         om15 = -1.5f * omega;
         guo3 = 3.0f * guo;
@@ -253,26 +256,25 @@ struct Physics {
 
 enum { CORR_BKC = 0, CORR_KLINKENBERG = 1, CORR_NONE = 2 };
 
-// Whether v holds for any active lane of the wave, followed by a branch that
-// stays a branch: the empty statement keeps the compiler from computing what
-// few waves need for every node and selecting afterwards.
-__device__ __forceinline__ bool any_lane(bool v)
+// A uniform condition that stays a branch: the empty statement keeps the
+// compiler from computing what few waves need for every node and selecting
+// afterwards.
+__device__ __forceinline__ bool uniform_branch(bool v)
 {
-    if (__builtin_amdgcn_ballot_w64(v) == 0)
+    if (!v)
         return false;
     asm volatile("");
     return true;
 }
-// Whether the Forchheimer term is on: a scalar test (the bits of f_eps, its
-// sign apart) and a branch that stays one.  With a select in its place the
-// square roots of Eq. 2 were evaluated for every node of a Darcy run, about
-// 28 of its 190 vector instructions per update.
+// Whether v holds for any active lane of the wave.
+__device__ __forceinline__ bool any_lane(bool v) { return __builtin_amdgcn_ballot_w64(v) != 0; }
+// Whether the Forchheimer term is on (the bits of f_eps, its sign apart).
+// With a select in place of this branch the square roots of Eq. 2 were
+// evaluated for every node of a Darcy run, about 28 of its 190 vector
+// instructions per update.
 __device__ __forceinline__ bool forchheimer(const Physics &ph)
 {
-    if ((__float_as_uint(ph.feps) << 1) == 0u)
-        return false;
-    asm volatile("");
-    return true;
+    return uniform_branch((__float_as_uint(ph.feps) << 1) != 0u);
 }
 
 // Correction factor of the selected correlation as a ratio f_c = den / num
@@ -286,14 +288,20 @@ __device__ __forceinline__ float fc_pow(float kn)
 {
     return __builtin_amdgcn_exp2f(0.4348f * __builtin_amdgcn_logf(kn));
 }
+// CORR_BKC with t = fc_pow(kn).
+__device__ __forceinline__ void fc_bkc(const Physics &ph, float kn, float t, float &num,
+                                       float &den)
+{
+    const float a = t + 0.170f;
+    num = a * (1.0f + ph.slip_nb * kn);
+    den = (a + 1.358f * t * kn) * (1.0f + ph.slip_c * kn);
+}
 // fc_parts with t = fc_pow(kn) given (used only by CORR_BKC).
 __device__ __forceinline__ void fc_parts_t(const Physics &ph, float kn, float t, float &num,
                                            float &den)
 {
     if (ph.corr == CORR_BKC) {
-        const float a = t + 0.170f;
-        num = a * (1.0f + ph.slip_nb * kn);
-        den = (a + 1.358f * t * kn) * (1.0f + ph.slip_c * kn);
+        fc_bkc(ph, kn, t, num, den);
     } else if (ph.corr == CORR_KLINKENBERG) {
         num = 1.0f;
         den = 1.0f + 4.0f * kn;
@@ -458,45 +466,69 @@ __device__ __forceinline__ void momentum(const float (&d)[9], float &jx, float &
 // v = j / rho + eps G / 2, so one reciprocal R = 1 / (2 den + drag num)
 // yields both u = 2 den R v and A u = 2 drag num R v.
 // eps = 0: u = 0 and rho F = -2 j (the infinite-drag limit of Eq. 17).
+//
+// MODEL_STD: the run is the paper's default model under a pressure drive
+// (second-order correlation, Darcy drag, local Kn quoted at density 1, no body
+// force; Physics::standard), compiled without the tests and terms of the
+// others.  Its nodes carry e = 1 / eps (0 where eps = 0) in place of eps, so
+// a reciprocal is taken once per node and not once per step.  The values are
+// those of the general form.  any_solid: whether a lane may hold eps = 0.
+enum { MODEL_GEN = 0, MODEL_STD = 1 };
+template <int MODEL>
 __device__ __forceinline__ void velocity(const Physics &ph, float rho, float jx, float jy,
-                                         float eps, float drag, float kn0, float &ux, float &uy,
-                                         float &Fx, float &Fy)
+                                         float e, float drag, float kn0, bool any_solid,
+                                         float &ux, float &uy, float &Fx, float &Fy)
 {
     const float rinv = __builtin_amdgcn_rcpf(rho);
-    const float kn = ph.kn_local ? kn0 * (ph.rho_ref * rinv) : kn0;
-    float num, den;
-    fc_parts(ph, kn, num, den);
-    const float egx = eps * ph.gx, egy = eps * ph.gy;
-    const float vx = jx * rinv + 0.5f * egx;
-    const float vy = jy * rinv + 0.5f * egy;
-    const bool solid = !(eps > 0.0f);
-    if (!forchheimer(ph)) {
+    const bool solid = !(e > 0.0f);
+    if (MODEL == MODEL_STD) {
+        const float kn = kn0 * rinv;
+        float num, den;
+        fc_bkc(ph, kn, fc_pow(kn), num, den);
+        const float vx = jx * rinv, vy = jy * rinv;
         const float dn = drag * num;
         const float R2 = 2.0f * __builtin_amdgcn_rcpf(2.0f * den + dn);
         const float g = den * R2, ag = dn * R2;
         ux = g * vx;
         uy = g * vy;
-        Fx = egx - ag * vx;
-        Fy = egy - ag * vy;
+        Fx = -(ag * vx);
+        Fy = -(ag * vy);
     } else {
-        // Forchheimer (Eq. 2): (1 + A/2) u + (B/2) |u| u = v with
-        // B = eps F_eps / sqrt(k_a), k_a = eps nu / A; positive root of
-        // the quadratic in |u|, rationalized.
-        const float A = drag * num * __builtin_amdgcn_rcpf(den);
-        const float B = ph.feps * __builtin_sqrtf(eps * A * ph.inv_nu);
-        const float c0 = 1.0f + 0.5f * A;
-        const float wn = __builtin_sqrtf(vx * vx + vy * vy);
-        const float g = 2.0f / (c0 + __builtin_sqrtf(c0 * c0 + 2.0f * B * wn));
-        const float ag = A * g;
-        ux = solid ? 0.0f : g * vx;
-        uy = solid ? 0.0f : g * vy;
-        Fx = egx - ag * vx;
-        Fy = egy - ag * vy;
-        const float bu = B * __builtin_sqrtf(ux * ux + uy * uy);
-        Fx -= bu * ux;
-        Fy -= bu * uy;
+        const float eps = e;
+        const float kn = ph.kn_local ? kn0 * (ph.rho_ref * rinv) : kn0;
+        float num, den;
+        fc_parts(ph, kn, num, den);
+        const float egx = eps * ph.gx, egy = eps * ph.gy;
+        const float vx = jx * rinv + 0.5f * egx;
+        const float vy = jy * rinv + 0.5f * egy;
+        if (!forchheimer(ph)) {
+            const float dn = drag * num;
+            const float R2 = 2.0f * __builtin_amdgcn_rcpf(2.0f * den + dn);
+            const float g = den * R2, ag = dn * R2;
+            ux = g * vx;
+            uy = g * vy;
+            Fx = egx - ag * vx;
+            Fy = egy - ag * vy;
+        } else {
+            // Forchheimer (Eq. 2): (1 + A/2) u + (B/2) |u| u = v with
+            // B = eps F_eps / sqrt(k_a), k_a = eps nu / A; positive root of
+            // the quadratic in |u|, rationalized.
+            const float A = drag * num * __builtin_amdgcn_rcpf(den);
+            const float B = ph.feps * __builtin_sqrtf(eps * A * ph.inv_nu);
+            const float c0 = 1.0f + 0.5f * A;
+            const float wn = __builtin_sqrtf(vx * vx + vy * vy);
+            const float g = 2.0f / (c0 + __builtin_sqrtf(c0 * c0 + 2.0f * B * wn));
+            const float ag = A * g;
+            ux = solid ? 0.0f : g * vx;
+            uy = solid ? 0.0f : g * vy;
+            Fx = egx - ag * vx;
+            Fy = egy - ag * vy;
+            const float bu = B * __builtin_sqrtf(ux * ux + uy * uy);
+            Fx -= bu * ux;
+            Fy -= bu * uy;
+        }
     }
-    if (any_lane(solid)) { // most waves hold none
+    if (uniform_branch(any_solid)) { // most waves hold none
         ux = solid ? 0.0f : ux;
         uy = solid ? 0.0f : uy;
         Fx = solid ? -2.0f * jx * rinv : Fx;
@@ -514,15 +546,18 @@ __device__ __forceinline__ void velocity(const Physics &ph, float rho, float jx,
 //   C = omega r - (1 - omega) inc + rho/eps (-1.5 omega u.u - 3 g u.F).
 // d_i and the outputs are in the storage unit (times s for FP16).
 // For eps = 0 the 1/eps terms vanish with u = 0.
-template <typename T>
+template <typename T, int MODEL>
 __device__ __forceinline__ void collide(const Physics &ph, float rho, float inc, float r,
                                         const float (&d)[9], float ux, float uy, float Fx,
-                                        float Fy, float eps, float s, float (&hs)[9])
+                                        float Fy, float e, bool any_solid, float s,
+                                        float (&hs)[9])
 {
-    const bool solid = !(eps > 0.0f);
-    float ie = __builtin_amdgcn_rcpf(eps);
-    if (any_lane(solid))
-        ie = solid ? 0.0f : ie;
+    float ie = e;
+    if (MODEL != MODEL_STD) {
+        ie = __builtin_amdgcn_rcpf(e);
+        if (uniform_branch(any_solid))
+            ie = e > 0.0f ? ie : 0.0f;
+    }
     const float om = ph.omega, cg = ph.guo, keep = ph.keep;
     float C = om * r - keep * inc +
               rho * ie * (ph.om15 * (ux * ux + uy * uy) - ph.guo3 * (ux * Fx + uy * Fy));

@@ -93,6 +93,24 @@ hipError_t launch_sweep3x(int storage, int bcx, int bcy, const char *src, char *
                           const Physics &ph, float s, float inv_s, int band, float *hist1,
                           float *hist2, float *hist3, hipStream_t st);
 
+// Shape of a tile pass: workgroups of `waves` waves with `rows` (1, 2 or 4)
+// rows each, 64 columns wide.
+constexpr int kTileMaxWaves = 16;
+struct Tile {
+    int waves, rows;
+};
+
+// `steps` steps src -> dst in one launch (bitwise as many launch_sweep calls):
+// every workgroup advances a tile of 64 columns by waves * rows rows in
+// registers and stores the nodes `steps` or more away from its edges.  src
+// and dst must be different levels; 2 steps must leave rows and columns to
+// store.  With hist, step k's linearisation point goes to the slot at
+// hist + k * hist_bytes.
+hipError_t launch_tile(int storage, int bcx, int bcy, const char *src, char *dst,
+                       const Layout &lay, const char *med, const MLayout &mlay, const Geom &g,
+                       const Physics &ph, float s, float inv_s, const Tile &t, int steps,
+                       float *hist, uint64_t hist_bytes, hipStream_t st);
+
 // Macroscopic fields ([ny][nx] outputs, any may be null).
 hipError_t launch_macro(int storage, int bcx, int bcy, const char *src, const Layout &lay,
                         const char *med, const MLayout &mlay, const Geom &g, const Physics &ph,

@@ -163,8 +163,8 @@ __device__ __forceinline__ void sweep2_strip_dir(const char *__restrict__ src,
         const int y = Y(m);
         float hs[9], jx, jy;
         const float rho = step_from<T, BCX>(ph, s, inv_s, DIR > 0 ? m0 : m2, m1,
-                                            DIR > 0 ? m2 : m0, wall_lo(y), wall_hi(y), ln, hs,
-                                            jx, jy);
+                                            DIR > 0 ? m2 : m0, wall_lo(y), wall_hi(y), ln,
+                                            any_lane(!(m1.e > 0.0f)), hs, jx, jy);
         if (HIST && owned)
             record(hist2, g, y, ln.x, rho, jx, jy, false);
         const Rsrc out = make_rsrc(dst + (uint64_t)y * lay.row, (uint32_t)lay.row);
@@ -338,8 +338,8 @@ __device__ __forceinline__ void sweep3x_strip_dir(const char *__restrict__ src,
         const int y = Y(m);
         float hs[9], jx, jy;
         const float rho = step_from<T, BCX>(ph, s, inv_s, DIR > 0 ? q0 : q2, q1,
-                                            DIR > 0 ? q2 : q0, wall_lo(y), wall_hi(y), ln, hs,
-                                            jx, jy);
+                                            DIR > 0 ? q2 : q0, wall_lo(y), wall_hi(y), ln,
+                                            any_lane(!(q1.e > 0.0f)), hs, jx, jy);
         if (HIST && owned)
             record(hist3, g, y, ln.x, rho, jx, jy, false);
         const Rsrc out = make_rsrc(dst + (uint64_t)y * lay.row, (uint32_t)lay.row);
@@ -547,7 +547,9 @@ __device__ __forceinline__ void readout_node(const char *src, const Layout &lay,
         jx *= inv_s;
         jy *= inv_s;
     }
-    velocity(ph, rho, jx, jy, md.eps(x), md.drag(x), md.kn0(x), ux, uy, Fx, Fy);
+    const float eps = md.eps(x);
+    velocity<MODEL_GEN>(ph, rho, jx, jy, eps, md.drag(x), md.kn0(x), any_lane(!(eps > 0.0f)), ux,
+                        uy, Fx, Fy);
     rp = (double)rho + (double)r;
 }
 

@@ -47,7 +47,8 @@ struct Med {
 // on return d holds the boundary node's deviations relative to the imposed
 // density rb (returned), inc = 0 and r its density residual:
 //   f_i = f_eq_i(rho_b, u_n; eps_b) + f_i(n) - f_eq_i(rho_n, u_n; eps_n)
-template <typename T>
+// eb and en are what the model's nodes carry: eps, or 1 / eps under MODEL_STD.
+template <typename T, int MODEL>
 __device__ __forceinline__ float extrapolate(const Physics &ph, float s, float inv_s, bool in,
                                              float eb, float en, float dragn, float kn0n,
                                              float rho, float (&d)[9], float &inc, float &r)
@@ -58,7 +59,7 @@ __device__ __forceinline__ float extrapolate(const Physics &ph, float s, float i
         jx *= inv_s;
         jy *= inv_s;
     }
-    velocity(ph, rho, jx, jy, en, dragn, kn0n, ux, uy, Fx, Fy);
+    velocity<MODEL>(ph, rho, jx, jy, en, dragn, kn0n, true, ux, uy, Fx, Fy);
     const float rb = in ? ph.rin_hi : ph.rout_hi;
     const float rbl = in ? ph.rin_lo : ph.rout_lo;
     // f_eq_i(rho_b, u; eps_b) - f_eq_i(rho_n, u; eps_n) of Eq. 14 as
@@ -66,8 +67,9 @@ __device__ __forceinline__ float extrapolate(const Physics &ph, float s, float i
     // deviation from w_i rho vanishing at eps = 0
     const bool sb = !(eb > 0.0f), sn = !(en > 0.0f);
     const float a = 3.0f * ((sb ? 0.0f : rb) - (sn ? 0.0f : rho));
-    const float b = (sb ? 0.0f : rb * __builtin_amdgcn_rcpf(eb)) -
-                    (sn ? 0.0f : rho * __builtin_amdgcn_rcpf(en));
+    const float ib = MODEL == MODEL_STD ? eb : __builtin_amdgcn_rcpf(eb);
+    const float in_ = MODEL == MODEL_STD ? en : __builtin_amdgcn_rcpf(en);
+    const float b = (sb ? 0.0f : rb * ib) - (sn ? 0.0f : rho * in_);
     const float uu = ux * ux + uy * uy;
     const float c = (rbl - r) - inc; // w_i (rbl - r) - w_i inc, over w_i
     float sum = 0.0f;
@@ -104,8 +106,8 @@ __device__ __forceinline__ float post_stream(const Rows &R, const Layout &L, con
     const float rho = density<T>(rc, d, inv_s, inc, r);
     if (BCX == BC_PRESSURE && bnode) {
         const float en = md.eps(xs), eb = md.eps(x);
-        return extrapolate<T>(ph, s, inv_s, x == 0, eb, en, md.drag(xs), md.kn0(xs), rho, d, inc,
-                              r);
+        return extrapolate<T, MODEL_GEN>(ph, s, inv_s, x == 0, eb, en, md.drag(xs), md.kn0(xs),
+                                         rho, d, inc, r);
     }
     return rho;
 }
@@ -145,9 +147,10 @@ __device__ __forceinline__ void sweep_node(const char *src, char *dst, const Lay
     if (HIST)
         record(hist, g, y, x, rho, jx, jy);
     const float eps = md.eps(x);
-    velocity(ph, rho, jx, jy, eps, md.drag(x), md.kn0(x), ux, uy, Fx, Fy);
+    const bool solids = any_lane(!(eps > 0.0f));
+    velocity<MODEL_GEN>(ph, rho, jx, jy, eps, md.drag(x), md.kn0(x), solids, ux, uy, Fx, Fy);
     float hs[9];
-    collide<T>(ph, rho, inc, r, d, ux, uy, Fx, Fy, eps, s, hs);
+    collide<T, MODEL_GEN>(ph, rho, inc, r, d, ux, uy, Fx, Fy, eps, solids, s, hs);
     const Rsrc out = make_rsrc(dst + (uint64_t)y * lay.row, (uint32_t)lay.row);
     st_f32(out, x * 4, 0, rho, true);
     constexpr uint32_t es = sizeof(T);
@@ -162,13 +165,13 @@ __device__ __forceinline__ void sweep_node(const char *src, char *dst, const Lay
 // unit, as stored), with the node's medium.
 struct Mid {
     float rho, h[9];
-    float eps, drag, kn0;
+    float e, drag, kn0; // e = eps, or 1 / eps under MODEL_STD (0 where eps = 0)
 };
 
 // Node (x, y) of a stored level and its medium.  A row the march loads
 // ahead but will not use (live = false, uniform) gets empty buffer
 // resources: its loads return 0 without touching memory.
-template <typename T>
+template <typename T, int MODEL = MODEL_GEN>
 __device__ __forceinline__ void load_node(const char *src, const Layout &lay, const char *med,
                                           const MLayout &mlay, int y, uint32_t x, Mid &m,
                                           bool live = true)
@@ -183,7 +186,9 @@ __device__ __forceinline__ void load_node(const char *src, const Layout &lay, co
     for (int i = 0; i < 9; ++i)
         m.h[i] = Elem<T>::template ld<0>(row, x * es, lay.h_off + i * lay.h_slot);
     const Rsrc mr = make_rsrc(med + (uint64_t)y * mlay.row, live ? (uint32_t)mlay.row : 0u);
-    m.eps = ld_f32(mr, x * 4, 0);
+    m.e = ld_f32(mr, x * 4, 0);
+    if (MODEL == MODEL_STD)
+        m.e = m.e > 0.0f ? __builtin_amdgcn_rcpf(m.e) : 0.0f;
     m.drag = ld_f32(mr, x * 4, mlay.slot);
     m.kn0 = ld_f32(mr, x * 4, 2 * mlay.slot);
 }
@@ -234,10 +239,11 @@ struct Lanes {
 // lane's pull, moments, velocity and collide -- sweep_node's update.
 // Returns the new density, the unrounded deviations hs and, for the
 // history, (jx, jy).
-template <typename T, int BCX>
+template <typename T, int BCX, int MODEL = MODEL_GEN>
 __device__ __forceinline__ float step_from(const Physics &ph, float s, float inv_s, const Mid &dn,
                                            const Mid &c, const Mid &up, bool wym, bool wyp,
-                                           const Lanes &ln, float (&hs)[9], float &jx, float &jy)
+                                           const Lanes &ln, bool any_solid, float (&hs)[9],
+                                           float &jx, float &jy)
 {
     float d[9], rc, inc, r;
     pull_mid<T, BCX>(dn, c, up, wym, wyp, ln.wxm, ln.wxp, s, rc, d);
@@ -251,7 +257,7 @@ __device__ __forceinline__ float step_from(const Physics &ph, float s, float inv
         }
         const float rl = lane_from<-1>(rc), rr = lane_from<1>(rc);
         rc = ln.bin ? rl : (ln.bout ? rr : rc);
-        const float el = lane_from<-1>(c.eps), er = lane_from<1>(c.eps);
+        const float el = lane_from<-1>(c.e), er = lane_from<1>(c.e);
         const float dl = lane_from<-1>(c.drag), dr = lane_from<1>(c.drag);
         const float kl = lane_from<-1>(c.kn0), kr = lane_from<1>(c.kn0);
         en = ln.bin ? el : er;
@@ -260,15 +266,15 @@ __device__ __forceinline__ float step_from(const Physics &ph, float s, float inv
     }
     float rho = density<T>(rc, d, inv_s, inc, r);
     if (BCX == BC_PRESSURE && (ln.bin || ln.bout))
-        rho = extrapolate<T>(ph, s, inv_s, ln.bin, c.eps, en, dragn, kn0n, rho, d, inc, r);
+        rho = extrapolate<T, MODEL>(ph, s, inv_s, ln.bin, c.e, en, dragn, kn0n, rho, d, inc, r);
     momentum(d, jx, jy);
     if (Elem<T>::kScaled) {
         jx *= inv_s;
         jy *= inv_s;
     }
     float ux, uy, Fx, Fy;
-    velocity(ph, rho, jx, jy, c.eps, c.drag, c.kn0, ux, uy, Fx, Fy);
-    collide<T>(ph, rho, inc, r, d, ux, uy, Fx, Fy, c.eps, s, hs);
+    velocity<MODEL>(ph, rho, jx, jy, c.e, c.drag, c.kn0, any_solid, ux, uy, Fx, Fy);
+    collide<T, MODEL>(ph, rho, inc, r, d, ux, uy, Fx, Fy, c.e, any_solid, s, hs);
     return rho;
 }
 
@@ -280,13 +286,14 @@ __device__ __forceinline__ void first_step(const Physics &ph, float s, float inv
                                            bool rec, Mid &m)
 {
     float hs[9], jx, jy;
-    m.rho = step_from<T, BCX>(ph, s, inv_s, dn, c, up, wym, wyp, ln, hs, jx, jy);
+    m.rho = step_from<T, BCX>(ph, s, inv_s, dn, c, up, wym, wyp, ln, any_lane(!(c.e > 0.0f)), hs,
+                              jx, jy);
     if (HIST && rec)
         record(hist, g, y, ln.x, m.rho, jx, jy, false);
 #pragma unroll
     for (int i = 0; i < 9; ++i)
         m.h[i] = Elem<T>::round(hs[i]);
-    m.eps = c.eps;
+    m.e = c.e;
     m.drag = c.drag;
     m.kn0 = c.kn0;
 }

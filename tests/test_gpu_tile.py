@@ -1,0 +1,77 @@
+"""The tile pass (several steps per launch, the automatic mode's way to step)
+is bitwise the single sweeps it replaces: every storage type and boundary
+combination, sizes at which each tile shape is chosen and around the columns
+and rows a tile stores, remainders of every length, the models with and
+without a compiled fast path, and the history of recorded steps."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_1411_7051_amd import Lattice, inputs  # noqa: E402
+
+STORAGES = ("f32", "f16", "bf16")
+
+
+def drive(bcx):
+    if bcx == inputs.PRESSURE:
+        return dict(bc_x=bcx, rho_in=1.01, rho_out=1.0, init=1)
+    return dict(bc_x=bcx, gx=2e-5, gy=-1e-5)
+
+
+def same(case, steps, storage="f32", **extra):
+    params = dict(case.params, **extra)
+    states = []
+    for mode in ("single", "auto"):
+        lat = Lattice(case.eps, case.k, case.kn0, storage=storage, pass_mode=mode, check_every=0,
+                      **params)
+        for n in steps:
+            lat.step(n)
+        states.append(lat.save_state())
+        lat.close()
+    return torch.equal(*states)
+
+
+def medium(nx, ny, seed=1, **params):
+    return inputs.random_medium(nx, ny, seed=seed, solid_frac=0.04, pore_frac=0.05, **params)
+
+
+@pytest.mark.parametrize("storage", STORAGES)
+@pytest.mark.parametrize("bcx", [inputs.PERIODIC, inputs.WALL, inputs.PRESSURE])
+@pytest.mark.parametrize("bcy", [inputs.PERIODIC, inputs.WALL])
+def test_tile_bitwise(storage, bcx, bcy):
+    small = [(3, 1), (5, 2), (57, 3), (58, 9), (59, 10), (61, 11), (64, 32), (117, 23), (174, 5)]
+    if bcx != inputs.PRESSURE:
+        small += [(1, 1), (2, 3)]
+    for nx, ny in small:
+        assert same(medium(nx, ny, bc_y=bcy, **drive(bcx)), (7, 2, 1, 5), storage), (nx, ny)
+    # the larger shapes: 12 and 16 waves, 3 to 5 steps, one and two rows a wave
+    for nx, ny in ((200, 160), (256, 256), (384, 256), (509, 511), (1111, 1025)):
+        assert same(medium(nx, ny, bc_y=bcy, **drive(bcx)), (11,), storage), (nx, ny)
+
+
+@pytest.mark.parametrize("extra", [dict(f_eps=0.7), dict(correlation=1), dict(correlation=2),
+                                   dict(slip_b=-0.5), dict(kn_local=0), dict(rho_ref=1.5),
+                                   dict(gx=1e-5), dict(gy=-1e-5), dict(tau=1.3)])
+def test_tile_models(extra):
+    for nx, ny in ((130, 37), (1030, 1021)):
+        for storage in ("f32", "f16"):
+            case = medium(nx, ny, seed=2, bc_y=inputs.WALL, **drive(inputs.PRESSURE))
+            assert same(case, (8,), storage, **extra), (nx, ny, storage)
+
+
+@pytest.mark.parametrize("bcx,obj,storage", [(inputs.PRESSURE, "k_app", "f32"),
+                                             (inputs.PRESSURE, "q_out", "f16"),
+                                             (inputs.PERIODIC, "k_app", "bf16")])
+def test_tile_recording(bcx, obj, storage):
+    for nx, ny in ((70, 41), (300, 230)):
+        case = medium(nx, ny, seed=3, **drive(bcx))
+        out = []
+        for mode in ("single", "auto"):
+            lat = Lattice(case.eps, case.k, case.kn0, storage=storage, pass_mode=mode,
+                          **case.params)
+            out.append(lat.gradient(23, obj, ckpt_every=14, hist_len=9, wrt_kn0=True))
+            lat.close()
+        assert out[0][0] == out[1][0]
+        assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[0][2], out[1][2])
