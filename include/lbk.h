@@ -347,6 +347,11 @@ lbk_status lbk_batch_set_pass_mode(lbk_batch *b, int32_t pass_mode);
 lbk_status lbk_batch_get_pass_mode(const lbk_batch *b, int32_t *pass_mode,
                                    int32_t *steps_per_launch);
 
+/* Steps of a whole tile pass when the batch steps in tile passes (the
+ * automatic mode, unless lbk_batch_autotune measured another pass faster), 0
+ * when it does not. */
+lbk_status lbk_batch_tile_steps(const lbk_batch *b, int32_t *steps);
+
 /* on != 0: every graph replay ends with the per-sample read-out reductions
  * (the FP64 sums behind lbk_batch_apparent_permeability), so that after
  * steps that end in a replay the permeabilities need only a copy of the

@@ -117,6 +117,7 @@ _SIG = {
     "lbk_batch_set_pass_mode": (ctypes.c_int, [_P, ctypes.c_int32]),
     "lbk_batch_get_pass_mode": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_int32),
                                                ctypes.POINTER(ctypes.c_int32)]),
+    "lbk_batch_tile_steps": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_int32)]),
     "lbk_batch_autotune": (ctypes.c_int, [_P, ctypes.c_int32, ctypes.POINTER(ctypes.c_double)]),
     "lbk_batch_apparent_permeability": (ctypes.c_int, [_P, _P]),
     "lbk_batch_check": (ctypes.c_int, [_P]),

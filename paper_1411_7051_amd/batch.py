@@ -106,10 +106,11 @@ class Batch:
 
     def autotune(self, reps: int = 10, cache: Optional[str] = None) -> float:
         """Pick the fastest (tile_x, rows, grid) for this batch and, in the
-        automatic pass mode, whether two-step passes beat it, leaving the
-        samples' states untouched; returns the mean step time in
-        microseconds (NaN when taken from ``cache``, a JSON file of
-        signature -> [tile_x, rows, grid, steps per launch, us])."""
+        automatic pass mode, the faster of it, two-step passes and tile
+        passes, leaving the samples' states untouched; returns the mean step
+        time in microseconds (NaN when taken from ``cache``, a JSON file of
+        signature -> [tile_x, rows, grid, steps per launch, us], 0 steps per
+        launch standing for tile passes)."""
         sig = self.signature()
         table = {}
         if cache and os.path.exists(cache):
@@ -119,13 +120,16 @@ class Batch:
             if entry is not None and len(entry) == 5:
                 tile_x, rows, grid, per_launch, _ = entry
                 self.set_launch(tile_x, rows, grid, self.launch[3])
-                self.set_pass_mode("two_step" if per_launch == 2 else "single")
+                self.set_pass_mode({0: "auto", 2: "two_step"}.get(per_launch, "single"))
                 return float("nan")
         us = ctypes.c_double()
         check(_lib.load().lbk_batch_autotune(self._handle(), int(reps), ctypes.byref(us)))
         if cache:
             tile_x, rows, grid, _ = self.launch
-            table[sig] = [tile_x, rows, grid, self.steps_per_launch, float(us.value)]
+            k = ctypes.c_int32()
+            check(_lib.load().lbk_batch_tile_steps(self._handle(), ctypes.byref(k)))
+            per_launch = 0 if k.value else self.steps_per_launch
+            table[sig] = [tile_x, rows, grid, per_launch, float(us.value)]
             tmp = cache + ".tmp"
             with open(tmp, "w") as f:
                 json.dump(table, f, indent=1, sort_keys=True)

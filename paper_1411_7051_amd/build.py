@@ -9,9 +9,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbk.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
-SOURCES = ["lbk_kernels.hip", "lbk_tile.hip", "lbk_adjoint.hip", "lbk_api.hip", "lbk_batch.hip",
+SOURCES = ["lbk_kernels.hip", "lbk_tile.hip", "lbk_tile_batch.hip", "lbk_adjoint.hip", "lbk_api.hip", "lbk_batch.hip",
            "lbk3_kernels.hip", "lbk3_api.hip", "lbk_noalloc.hip"]
-HEADERS = ["lbk_device.h", "lbk_kernels.h", "lbk_sweep.h", "lbk_adjoint.h", "lbk_host.h", "lbk3_kernels.h"]
+HEADERS = ["lbk_device.h", "lbk_kernels.h", "lbk_sweep.h", "lbk_tile.h", "lbk_adjoint.h", "lbk_host.h", "lbk3_kernels.h"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -22,6 +22,8 @@ FLAGS = [
     # rounds identically in every kernel that inlines it (single lattice,
     # batched tile list, adjoint recompute), whatever the control flow around
     "-ffp-contract=on",
+    # the sources compile side by side
+    "-parallel-jobs=8",
 ]
 
 

@@ -122,8 +122,8 @@ void split(double v, float &hi, float &lo)
 
 } // namespace
 
-// Shape and steps of a lattice's tile passes: the least predicted time per
-// step.  A launch costs about 4.2 us (dispatch, the latency of the loads, the
+// Shape and steps of tile passes over one or several lattices: the least
+// predicted time per step.  A launch costs about 4.2 us (dispatch, the latency of the loads, the
 // drain of the stores) and each row update a workgroup makes u_inf per tile
 // of its compute unit's share plus c for what one tile alone leaves
 // exposed (its waves wait for one another at every step); u_inf and c in us,
@@ -132,7 +132,7 @@ void split(double v, float &hi, float &lo)
 // 64 x 32 takes 8 x 1 rows and 3 steps (2.0 us a step; 16 x 1 and 6 steps
 // 2.3), 256 x 256 16 x 1 and 5 (2.4; 16 x 2 and 5 4.4), 1024 x 512 16 x 1 and 3
 // (6.9; 8 x 2 and 3 7.1), 4096 x 4096 16 x 2 and 4 (108; 16 x 1 and 3 137).
-TilePlan lbk::tile_plan(int nx, int ny)
+TilePlan lbk::tile_plan(const int *nx, const int *ny, int n)
 {
     static const TilePlan cand[] = {{{8, 1}, 3},  {{12, 1}, 4}, {{16, 1}, 3}, {{16, 1}, 4},
                                     {{16, 1}, 5}, {{16, 2}, 4}, {{16, 2}, 5}};
@@ -142,8 +142,9 @@ TilePlan lbk::tile_plan(int nx, int ny)
     double best_us = INFINITY;
     for (const TilePlan &p : cand) {
         const int H = p.tile.waves * p.tile.rows, R = p.tile.rows;
-        const int own_x = 64 - 2 * p.steps, own_y = H - 2 * p.steps;
-        const double tiles = (double)((nx + own_x - 1) / own_x) * ((ny + own_y - 1) / own_y);
+        double tiles = 0;
+        for (int i = 0; i < n; ++i)
+            tiles += (double)tile_strips(nx[i], p) * tile_bands(ny[i], p);
         // tiles of the busiest compute unit: whole ones while they are few
         const double q = tiles <= 8.0 * cus ? ceil(tiles / cus) : tiles / cus;
         int rows = 0; // row updates of a tile: waves with rows k + 1 .. H - 2 - k
@@ -166,7 +167,7 @@ TilePlan lbk::tile_plan(int nx, int ny)
 Pass lbk::next_pass(const lbk_lattice *lat, int64_t left)
 {
     if (left > 1 && tile_pass(lat)) {
-        const TilePlan p = tile_plan(lat->d.nx, lat->d.ny);
+        const TilePlan &p = lat->plan;
         const int64_t launches = (left + p.steps - 1) / p.steps;
         const int steps = (int)((left + launches - 1) / launches);
         if (steps > 1)
@@ -395,6 +396,7 @@ lbk_status lbk_create(const lbk_desc *d, const float *eps, const float *k, const
     ph.slip_nb = (float)(-d->slip_b);
     ph.slip_c = (float)(4.0 - d->slip_b);
     ph.derive();
+    lat->plan = tile_plan(&d->nx, &d->ny, 1);
 
     char *ws = lat->ws;
     char *med = lat->med();

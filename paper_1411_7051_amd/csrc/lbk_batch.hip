@@ -66,13 +66,31 @@ int64_t total_tiles2(lbk_lattice *const *lats, int n)
     return t;
 }
 
+// Tile pass shape of the batch and the tiles it cuts a sample into.
+TilePlan plan_of(lbk_lattice *const *lats, int n)
+{
+    std::vector<int> nx(n), ny(n);
+    for (int i = 0; i < n; ++i) {
+        nx[i] = lats[i]->d.nx;
+        ny[i] = lats[i]->d.ny;
+    }
+    return tile_plan(nx.data(), ny.data(), n);
+}
+
+int64_t tiles_in(const lbk_lattice *l, const TilePlan &p)
+{
+    return (int64_t)tile_strips(l->d.nx, p) * tile_bands(l->d.ny, p);
+}
+
 // Workspace regions: descriptor table and tile -> sample map of the sweep
-// (sized for the finest allowed tiling), of the two-step pass and of the
-// read-out; read-out partials [MAC_SLOTS][read tiles] and per-sample sums
+// (sized for the finest allowed tiling), of the two-step pass, of the
+// read-out and of the tile pass; read-out partials [MAC_SLOTS][read tiles] and per-sample sums
 // [n][MAC_SLOTS].
 struct BatchLayout {
-    size_t desc_sweep, map_sweep, desc_sweep2, map_sweep2, desc_read, map_read;
-    int64_t max_sweep_tiles, sweep2_tiles, read_tiles;
+    size_t desc_sweep, map_sweep, desc_sweep2, map_sweep2, desc_read, map_read, desc_tile,
+        map_tile;
+    int64_t max_sweep_tiles, sweep2_tiles, read_tiles, tile_tiles;
+    TilePlan plan; // shape of the tile passes
     size_t partials, results, total;
 };
 
@@ -117,6 +135,12 @@ BatchLayout batch_layout(lbk_lattice *const *lats, int n)
     B.map_sweep2 = take((size_t)B.sweep2_tiles * sizeof(int));
     B.desc_read = take((size_t)n * sizeof(SampleDesc));
     B.map_read = take((size_t)B.read_tiles * sizeof(int));
+    B.plan = plan_of(lats, n);
+    B.tile_tiles = 0;
+    for (int i = 0; i < n; ++i)
+        B.tile_tiles += tiles_in(lats[i], B.plan);
+    B.desc_tile = take((size_t)n * sizeof(SampleDesc));
+    B.map_tile = take((size_t)B.tile_tiles * sizeof(int));
     B.partials = take((size_t)MAC_SLOTS * (size_t)B.read_tiles * sizeof(double));
     B.results = take((size_t)n * MAC_SLOTS * sizeof(double));
     B.total = o;
@@ -146,8 +170,8 @@ struct BatchAdj {
 size_t batch_adj_place(BatchAdj &A, int64_t keep)
 {
     const int n = (int)A.plans.size();
-    // descriptor tables: the sweep's tiling, then the two-step tiling
-    size_t o = align_up((size_t)2 * n * sizeof(AdjSampleDesc), 256);
+    // descriptor tables: the sweep's tiling, the two-step tiling, the tiles
+    size_t o = align_up((size_t)3 * n * sizeof(AdjSampleDesc), 256);
     for (int i = 0; i < n; ++i) {
         AdjPlan &P = A.plans[i];
         P.total = P.inner + (size_t)(keep > 1 ? keep : 1) * P.inner_seg;
@@ -205,10 +229,12 @@ struct lbk_batch {
     std::vector<uint64_t> ver0; // each lattice's version when the tables were last set
     Shape shape;        // sweep tiling
     int64_t sweep_tiles;
-    std::vector<int64_t> tile0_sweep, tile0_read, tile0_sweep2;
+    std::vector<int64_t> tile0_sweep, tile0_read, tile0_sweep2, tile0_tile;
     int pass_mode;         // lbk_pass_mode asked for
-    int tuned_two;         // -1: not tuned; else the tuner's choice (AUTO)
-    SampleDesc *host_desc; // pinned staging, [3][n]: sweep, read-out, two-step pass
+    int tuned;             // -1: not tuned; else the tuner's choice of pass (AUTO):
+                           // PASS_ONE, PASS_TWO or PASS_TILE
+    int standard;          // every sample runs the standard model (MODEL_STD)
+    SampleDesc *host_desc; // pinned staging, [4][n]: sweep, read-out, two-step pass, tiles
     double *host_res;      // pinned, [n][MAC_SLOTS]
     int grid, graph_steps;
     hipGraphExec_t exec[2]; // graphs starting at parity 0 / 1
@@ -226,15 +252,26 @@ struct lbk_batch {
     double *partials() const { return reinterpret_cast<double *>(ws + B.partials); }
     double *results() const { return reinterpret_cast<double *>(ws + B.results); }
     const lbk_desc &d0() const { return lats[0]->d; }
-    // whether steps go through the two-step pass (in pairs)
+    SampleDesc *desc_tile() const { return reinterpret_cast<SampleDesc *>(ws + B.desc_tile); }
+    int *map_tile() const { return reinterpret_cast<int *>(ws + B.map_tile); }
+    // whether steps go through tile passes: the automatic mode unless the
+    // tuner measured another pass faster (a batch of 16 FP16 samples 256 to
+    // 1536 wide: TILE_US us a step against TWO_US in two-step passes; of
+    // twelve FP32 samples 64 to 256 wide SMALL_US against ONE_US in single steps)
+    bool tile() const
+    {
+        return pass_mode == LBK_PASS_AUTO && (tuned < 0 || tuned == PASS_TILE);
+    }
+    // whether the batch counts as one that steps in pairs: what the calls
+    // report, its passes where it takes no tile passes, and its reverse steps
     bool two() const
     {
         if (pass_mode == LBK_PASS_TWO_STEP)
             return true;
         if (pass_mode == LBK_PASS_SINGLE)
             return false;
-        if (tuned_two >= 0)
-            return tuned_two != 0;
+        if (tuned == PASS_ONE || tuned == PASS_TWO)
+            return tuned == PASS_TWO;
         int64_t nodes = 0;
         for (const lbk_lattice *l : lats)
             nodes += (int64_t)l->d.nx * l->d.ny;
@@ -254,7 +291,7 @@ void drop_graphs(lbk_batch *b)
 }
 
 // Upload the tile -> sample map of tiling `sh` (rows 0: the two-step
-// pass's tiling) into `map`; tile0[i] gets the first tile of sample i.
+// pass's tiling, rows -1: the tile pass's) into `map`; tile0[i] gets the first tile of sample i.
 // Synchronous.
 lbk_status upload_map(lbk_batch *b, Shape sh, int *map, std::vector<int64_t> &tile0,
                       int64_t &ntiles)
@@ -263,7 +300,10 @@ lbk_status upload_map(lbk_batch *b, Shape sh, int *map, std::vector<int64_t> &ti
     tile0.assign(b->n, 0);
     for (int i = 0; i < b->n; ++i) {
         tile0[i] = (int64_t)h.size();
-        h.insert(h.end(), (size_t)(sh.rows ? tiles_of(b->lats[i], sh) : tiles2_of(b->lats[i])), i);
+        const int64_t nt = sh.rows > 0    ? tiles_of(b->lats[i], sh)
+                           : sh.rows == 0 ? tiles2_of(b->lats[i])
+                                          : tiles_in(b->lats[i], b->B.plan);
+        h.insert(h.end(), (size_t)nt, i);
     }
     ntiles = (int64_t)h.size();
     HIP_TRY(hipStreamSynchronize(b->stream));
@@ -292,7 +332,7 @@ lbk_status sync_tables(lbk_batch *b, bool force)
         b->cur0[i] = l->cur ^ b->parity;
         b->scale0[i] = l->scale_exp;
         b->ver0[i] = l->version;
-        for (int k = 0; k < 3; ++k) {
+        for (int k = 0; k < 4; ++k) {
             const Shape sh = k == 0 ? b->shape : kReadShape;
             SampleDesc &sd = b->host_desc[(size_t)k * b->n + i];
             sd.state[b->parity] = l->state(l->cur);
@@ -304,9 +344,13 @@ lbk_status sync_tables(lbk_batch *b, bool force)
             sd.ph = l->ph;
             sd.s = l->s();
             sd.inv_s = l->inv_s();
-            sd.tile0 = (int)(k == 0 ? b->tile0_sweep[i]
-                                    : (k == 1 ? b->tile0_read[i] : b->tile0_sweep2[i]));
-            sd.tpr = k == 2 ? groups_of(l->d.nx) : tiles_per_row(l->d.nx, sh.tile_x);
+            sd.tile0 = (int)(k == 0   ? b->tile0_sweep[i]
+                             : k == 1 ? b->tile0_read[i]
+                             : k == 2 ? b->tile0_sweep2[i]
+                                      : b->tile0_tile[i]);
+            sd.tpr = k == 3   ? tile_strips(l->d.nx, b->B.plan)
+                     : k == 2 ? groups_of(l->d.nx)
+                              : tiles_per_row(l->d.nx, sh.tile_x);
         }
     }
     HIP_TRY(hipMemcpyAsync(b->desc_sweep(), b->host_desc, (size_t)b->n * sizeof(SampleDesc),
@@ -314,6 +358,8 @@ lbk_status sync_tables(lbk_batch *b, bool force)
     HIP_TRY(hipMemcpyAsync(b->desc_read(), b->host_desc + b->n, (size_t)b->n * sizeof(SampleDesc),
                            hipMemcpyHostToDevice, b->stream));
     HIP_TRY(hipMemcpyAsync(b->desc_sweep2(), b->host_desc + 2 * (size_t)b->n,
+                           (size_t)b->n * sizeof(SampleDesc), hipMemcpyHostToDevice, b->stream));
+    HIP_TRY(hipMemcpyAsync(b->desc_tile(), b->host_desc + 3 * (size_t)b->n,
                            (size_t)b->n * sizeof(SampleDesc), hipMemcpyHostToDevice, b->stream));
     HIP_TRY(hipStreamSynchronize(b->stream));
     return LBK_OK;
@@ -361,11 +407,36 @@ hipError_t readout(lbk_batch *b, int parity, hipStream_t st)
     return e;
 }
 
-// Parity after a graph replay of graph_steps steps from `parity`: single
-// steps flip it each step (an even count), two-step passes once a pass.
+// `steps` steps of every sample in one tile pass, parity -> parity ^ 1.
+hipError_t tile_once(lbk_batch *b, int parity, int steps, hipStream_t st)
+{
+    const lbk_desc &d = b->d0();
+    return launch_batch_tile(d.storage, d.bc_x, d.bc_y, b->desc_tile(), b->map_tile(),
+                             (int)b->B.tile_tiles, parity, b->B.plan.tile, b->B.plan.steps,
+                             steps, b->standard, st);
+}
+
+// Steps the next launch advances when `left` >= 1 remain, and that launch.
+int pass_steps(const lbk_batch *b, int64_t left)
+{
+    if (left < 2)
+        return 1;
+    return b->tile() ? (int)std::min<int64_t>(left, b->B.plan.steps) : (b->two() ? 2 : 1);
+}
+hipError_t pass_once(lbk_batch *b, int parity, int steps, hipStream_t st)
+{
+    if (steps == 1)
+        return sweep_once(b, parity, b->grid, st);
+    return b->tile() ? tile_once(b, parity, steps, st) : sweep2_once(b, parity, st);
+}
+
+// Parity after a graph replay of graph_steps steps from `parity`: each
+// launch flips it.
 int parity_after_graph(const lbk_batch *b, int parity)
 {
-    return b->two() ? parity ^ ((b->graph_steps / 2) & 1) : parity;
+    for (int left = b->graph_steps; left > 0; left -= pass_steps(b, left))
+        parity ^= 1;
+    return parity;
 }
 
 // Record graph_steps steps starting at `parity` on the private stream
@@ -374,12 +445,11 @@ lbk_status record_graph(lbk_batch *b, int parity)
 {
     HIP_TRY(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
     hipError_t e = hipSuccess;
-    if (b->two())
-        for (int i = 0; i < b->graph_steps / 2 && e == hipSuccess; ++i)
-            e = sweep2_once(b, parity ^ (i & 1), b->cap);
-    else
-        for (int i = 0; i < b->graph_steps && e == hipSuccess; ++i)
-            e = sweep_once(b, parity ^ (i & 1), b->grid, b->cap);
+    for (int left = b->graph_steps, p = parity; left > 0 && e == hipSuccess; p ^= 1) {
+        const int steps = pass_steps(b, left);
+        e = pass_once(b, p, steps, b->cap);
+        left -= steps;
+    }
     if (e == hipSuccess && b->graph_readout)
         e = readout(b, parity_after_graph(b, parity), b->cap);
     hipGraph_t graph = nullptr;
@@ -468,7 +538,7 @@ lbk_status lbk_batch_create(lbk_lattice *const *lats, int32_t n, void *workspace
     b->sums_fresh = false;
     int64_t read_tiles = 0;
     if (hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking) != hipSuccess ||
-        hipHostMalloc((void **)&b->host_desc, (size_t)3 * n * sizeof(SampleDesc),
+        hipHostMalloc((void **)&b->host_desc, (size_t)4 * n * sizeof(SampleDesc),
                       hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&b->host_res, (size_t)n * MAC_SLOTS * sizeof(double),
                       hipHostMallocDefault) != hipSuccess) {
@@ -476,11 +546,15 @@ lbk_status lbk_batch_create(lbk_lattice *const *lats, int32_t n, void *workspace
         return fail(LBK_ERR_DEVICE, "stream or pinned host allocation failed");
     }
     b->pass_mode = LBK_PASS_AUTO;
-    b->tuned_two = -1;
-    int64_t sweep2_tiles = 0;
+    b->tuned = -1;
+    b->standard = 1;
+    for (int i = 0; i < n; ++i)
+        b->standard = b->standard && lats[i]->ph.standard;
+    int64_t sweep2_tiles = 0, tile_tiles = 0;
     if ((s = upload_map(b, kReadShape, b->map_read(), b->tile0_read, read_tiles)) != LBK_OK ||
         (s = upload_map(b, Shape{kStrip2, 0}, b->map_sweep2(), b->tile0_sweep2,
                         sweep2_tiles)) != LBK_OK ||
+        (s = upload_map(b, Shape{64, -1}, b->map_tile(), b->tile0_tile, tile_tiles)) != LBK_OK ||
         (s = set_shape(b, Shape{kBlock, 1})) != LBK_OK) {
         destroy_batch(b);
         return s;
@@ -506,7 +580,6 @@ lbk_status lbk_batch_step(lbk_batch *b, int64_t n)
     if (s != LBK_OK)
         return s;
     int64_t left = n;
-    const bool two = b->two();
     while (left > 0) {
         if (b->graph_steps > 0 && left >= b->graph_steps) {
             if (!b->have_exec[b->parity] && (s = record_graph(b, b->parity)) != LBK_OK)
@@ -516,15 +589,11 @@ lbk_status lbk_batch_step(lbk_batch *b, int64_t n)
             left -= b->graph_steps;
             b->parity = parity_after_graph(b, b->parity);
             b->sums_fresh = b->graph_readout;
-        } else if (two && left >= 2) {
-            HIP_TRY(sweep2_once(b, b->parity, b->stream));
-            b->parity ^= 1;
-            left -= 2;
-            b->sums_fresh = false;
         } else {
-            HIP_TRY(sweep_once(b, b->parity, b->grid, b->stream));
+            const int steps = pass_steps(b, left);
+            HIP_TRY(pass_once(b, b->parity, steps, b->stream));
             b->parity ^= 1;
-            --left;
+            left -= steps;
             b->sums_fresh = false;
         }
     }
@@ -594,10 +663,10 @@ lbk_status lbk_batch_set_pass_mode(lbk_batch *b, int32_t pass_mode)
         return fail(LBK_ERR_INVALID_ARG, "batch is NULL");
     if (pass_mode < LBK_PASS_AUTO || pass_mode > LBK_PASS_SINGLE)
         return fail(LBK_ERR_INVALID_ARG, "pass_mode must be 0..2 (got %d)", pass_mode);
-    const bool before = b->two();
+    const bool two = b->two(), tile = b->tile();
     b->pass_mode = pass_mode;
-    b->tuned_two = -1;
-    if (b->two() != before)
+    b->tuned = -1;
+    if (b->two() != two || b->tile() != tile)
         drop_graphs(b);
     return LBK_OK;
 }
@@ -611,6 +680,14 @@ lbk_status lbk_batch_get_pass_mode(const lbk_batch *b, int32_t *pass_mode,
         *pass_mode = b->pass_mode;
     if (steps_per_launch)
         *steps_per_launch = b->two() ? 2 : 1;
+    return LBK_OK;
+}
+
+lbk_status lbk_batch_tile_steps(const lbk_batch *b, int32_t *steps)
+{
+    if (!b || !steps)
+        return fail(LBK_ERR_INVALID_ARG, "NULL argument");
+    *steps = b->tile() ? b->B.plan.steps : 0;
     return LBK_OK;
 }
 
@@ -661,26 +738,34 @@ lbk_status lbk_batch_autotune(lbk_batch *b, int32_t reps, double *best_us)
             }
         }
     }
-    // the two-step pass against the best single step, per step (automatic
-    // pass mode only)
-    int two = -1;
+    // the two-step and the tile pass against the best single step, per step
+    // (automatic pass mode only)
+    int tuned = -1;
     if (s == LBK_OK && e == hipSuccess && b->pass_mode == LBK_PASS_AUTO) {
-        e = sweep2_once(b, b->parity, b->stream);
-        if (e == hipSuccess)
-            e = hipEventRecord(ev[0], b->stream);
-        for (int k = 0; k < reps && e == hipSuccess; ++k)
-            e = sweep2_once(b, b->parity, b->stream);
-        if (e == hipSuccess)
-            e = hipEventRecord(ev[1], b->stream);
-        if (e == hipSuccess)
-            e = hipEventSynchronize(ev[1]);
-        float ms = 0.0f;
-        if (e == hipSuccess)
-            e = hipEventElapsedTime(&ms, ev[0], ev[1]);
-        if (e == hipSuccess) {
-            two = ms / (2.0 * reps) < best ? 1 : 0;
-            if (two)
-                best = ms / (2.0 * reps);
+        tuned = PASS_ONE;
+        for (int kind : {(int)PASS_TWO, (int)PASS_TILE}) {
+            const int steps = kind == PASS_TWO ? 2 : b->B.plan.steps;
+            auto once = [&] {
+                return kind == PASS_TWO ? sweep2_once(b, b->parity, b->stream)
+                                        : tile_once(b, b->parity, steps, b->stream);
+            };
+            if (e == hipSuccess)
+                e = once();
+            if (e == hipSuccess)
+                e = hipEventRecord(ev[0], b->stream);
+            for (int k = 0; k < reps && e == hipSuccess; ++k)
+                e = once();
+            if (e == hipSuccess)
+                e = hipEventRecord(ev[1], b->stream);
+            if (e == hipSuccess)
+                e = hipEventSynchronize(ev[1]);
+            float ms = 0.0f;
+            if (e == hipSuccess)
+                e = hipEventElapsedTime(&ms, ev[0], ev[1]);
+            if (e == hipSuccess && ms / (steps * (double)reps) < best) {
+                best = ms / (steps * (double)reps);
+                tuned = kind;
+            }
         }
     }
     (void)hipEventDestroy(ev[0]);
@@ -692,9 +777,9 @@ lbk_status lbk_batch_autotune(lbk_batch *b, int32_t reps, double *best_us)
     if ((s = lbk_batch_set_launch(b, best_shape.tile_x, best_shape.rows, best_grid,
                                   b->graph_steps)) != LBK_OK)
         return s;
-    if (two >= 0 && two != b->tuned_two) {
+    if (tuned >= 0 && tuned != b->tuned) {
         drop_graphs(b);
-        b->tuned_two = two;
+        b->tuned = tuned;
     }
     if (best_us)
         *best_us = best * 1e3;
@@ -908,8 +993,8 @@ lbk_status lbk_batch_adjoint_backward(lbk_batch *b, void *ws, size_t ws_bytes,
     char *w = static_cast<char *>(ws);
     hipStream_t st = b->stream;
     // descriptor tables of this pass: the sweep's tiling (one workgroup per
-    // tile), then the same descriptors over the two-step tiling
-    std::vector<AdjSampleDesc> h(2 * (size_t)b->n);
+    // tile), then the same descriptors over the two-step tiling and the tiles
+    std::vector<AdjSampleDesc> h(3 * (size_t)b->n);
     for (int i = 0; i < b->n; ++i) {
         lbk_lattice *l = b->lats[i];
         const AdjPlan &P = A.plans[i];
@@ -946,6 +1031,10 @@ lbk_status lbk_batch_adjoint_backward(lbk_batch *b, void *ws, size_t ws_bytes,
         s2 = sd;
         s2.tile0 = (int)b->tile0_sweep2[i];
         s2.tpr = groups_of(l->d.nx);
+        AdjSampleDesc &s3 = h[(size_t)2 * b->n + i];
+        s3 = sd;
+        s3.tile0 = (int)b->tile0_tile[i];
+        s3.tpr = tile_strips(l->d.nx, b->B.plan);
     }
     AdjSampleDesc *table = reinterpret_cast<AdjSampleDesc *>(w + A.table);
     HIP_TRY(hipMemcpyAsync(table, h.data(), h.size() * sizeof(AdjSampleDesc),
@@ -957,12 +1046,21 @@ lbk_status lbk_batch_adjoint_backward(lbk_batch *b, void *ws, size_t ws_bytes,
         return launch_batch_rec_sweep(d.storage, d.bc_x, d.bc_y, table, map, nt, tx, rows, src,
                                       dst, slot, st);
     };
-    // pairs of steps through the two-step passes (bitwise the same) when
-    // the batch steps that way
+    // reverse steps in pairs (bitwise the same) when the batch counts as one
+    // that steps that way
     const bool two = b->two();
     const AdjSampleDesc *table2 = table + b->n;
     const int nt2 = (int)b->B.sweep2_tiles, band = band2_of(d.storage);
-    auto rec2 = [&](LevelSel src, LevelSel dst, int slot) {
+    // the next recomputing launch of `left` steps, as lbk_batch_step takes
+    // them; returns its steps in n
+    auto rec_pass = [&](LevelSel src, LevelSel dst, int slot, int64_t left, int &n) {
+        n = pass_steps(b, left);
+        if (n == 1)
+            return rec(src, dst, slot);
+        if (b->tile())
+            return launch_batch_rec_tile(d.storage, d.bc_x, d.bc_y, table + 2 * (size_t)b->n,
+                                         b->map_tile(), (int)b->B.tile_tiles, b->B.plan.tile,
+                                         b->B.plan.steps, n, b->standard, src, dst, slot, st);
         return launch_batch_rec_sweep2(d.storage, d.bc_x, d.bc_y, table2, b->map_sweep2(), nt2,
                                        band, src, dst, slot, st);
     };
@@ -1007,13 +1105,9 @@ lbk_status lbk_batch_adjoint_backward(lbk_batch *b, void *ws, size_t ws_bytes,
                 for (int64_t i = 0; i < steps;) {
                     const LevelSel from =
                         i == 0 ? LevelSel{ADJ_INNER, (int)nseg} : LevelSel{ADJ_REC, r};
-                    if (two && i + 1 < steps) {
-                        HIP_TRY(rec2(from, LevelSel{ADJ_REC, r ^ 1}, -1));
-                        i += 2;
-                    } else {
-                        HIP_TRY(rec(from, LevelSel{ADJ_REC, r ^ 1}, -1));
-                        ++i;
-                    }
+                    int n;
+                    HIP_TRY(rec_pass(from, LevelSel{ADJ_REC, r ^ 1}, -1, steps - i, n));
+                    i += n;
                     r ^= 1;
                 }
                 src = LevelSel{ADJ_REC, r};
@@ -1030,13 +1124,10 @@ lbk_status lbk_batch_adjoint_backward(lbk_batch *b, void *ws, size_t ws_bytes,
                 Range range("batch adjoint recompute");
                 for (int64_t t = a2s; t < b2s;) {
                     const LevelSel from = t == a2s ? src : LevelSel{ADJ_REC, r};
-                    if (two && t + 1 < b2s) {
-                        HIP_TRY(rec2(from, LevelSel{ADJ_REC, r ^ 1}, (int)(t - a2s + 1)));
-                        t += 2;
-                    } else {
-                        HIP_TRY(rec(from, LevelSel{ADJ_REC, r ^ 1}, (int)(t - a2s + 1)));
-                        ++t;
-                    }
+                    int n;
+                    HIP_TRY(rec_pass(from, LevelSel{ADJ_REC, r ^ 1}, (int)(t - a2s + 1), b2s - t,
+                                     n));
+                    t += n;
                     r ^= 1;
                 }
             }

@@ -146,7 +146,9 @@ __device__ __forceinline__ float f32_reg(float v)
 }
 
 // Storage element types, loaded and stored in the storage's own unit
-// (scaled for FP16).
+// (scaled for FP16).  A value that a kernel keeps in registers between steps
+// is a Reg: what a store would leave in memory (FP16: its 16 bits, so that the
+// pull's FMA widens it as it reads it instead of a conversion each way).
 template <typename T> struct Elem;
 template <> struct Elem<float> {
     static constexpr bool kScaled = false;
@@ -160,8 +162,20 @@ template <> struct Elem<float> {
     {
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)voff, (int)soff, AUX);
     }
-    // the value a store followed by a load returns
-    static __device__ __forceinline__ float round(float v) { return v; }
+    // a value as a store would leave it, and back
+    typedef float Reg;
+    static __device__ __forceinline__ Reg reg(float v) { return v; }
+    static __device__ __forceinline__ float val(Reg r) { return r; }
+    template <int AUX>
+    static __device__ __forceinline__ Reg ldr(Rsrc r, uint32_t voff, uint32_t soff)
+    {
+        return ld<AUX>(r, voff, soff);
+    }
+    template <int AUX>
+    static __device__ __forceinline__ void str(Rsrc r, uint32_t voff, uint32_t soff, Reg v)
+    {
+        st<AUX>(r, voff, soff, v);
+    }
 };
 template <> struct Elem<__half> {
     static constexpr bool kScaled = true;
@@ -177,9 +191,24 @@ template <> struct Elem<__half> {
         __builtin_amdgcn_raw_buffer_store_b16(__half_as_ushort(__float2half_rn(f32_reg(v))), r,
                                               (int)voff, (int)soff, AUX);
     }
-    static __device__ __forceinline__ float round(float v)
+    typedef uint32_t Reg; // the 16 bits, zero-extended
+    static __device__ __forceinline__ Reg reg(float v)
     {
-        return __half2float(__float2half_rn(f32_reg(v)));
+        return __half_as_ushort(__float2half_rn(f32_reg(v)));
+    }
+    static __device__ __forceinline__ float val(Reg r)
+    {
+        return __half2float(__ushort_as_half((uint16_t)r));
+    }
+    template <int AUX>
+    static __device__ __forceinline__ Reg ldr(Rsrc r, uint32_t voff, uint32_t soff)
+    {
+        return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)voff, (int)soff, AUX);
+    }
+    template <int AUX>
+    static __device__ __forceinline__ void str(Rsrc r, uint32_t voff, uint32_t soff, Reg v)
+    {
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, (int)voff, (int)soff, AUX);
     }
 };
 template <> struct Elem<__hip_bfloat16> {
@@ -197,10 +226,23 @@ template <> struct Elem<__hip_bfloat16> {
         __builtin_amdgcn_raw_buffer_store_b16(*reinterpret_cast<const uint16_t *>(&b), r,
                                               (int)voff, (int)soff, AUX);
     }
-    static __device__ __forceinline__ float round(float v)
+    typedef float Reg; // rounded
+    static __device__ __forceinline__ Reg reg(float v)
     {
         const __hip_bfloat16 b = __float2bfloat16(v);
         return __uint_as_float((uint32_t)(*reinterpret_cast<const uint16_t *>(&b)) << 16);
+    }
+    static __device__ __forceinline__ float val(Reg r) { return r; }
+    template <int AUX>
+    static __device__ __forceinline__ Reg ldr(Rsrc r, uint32_t voff, uint32_t soff)
+    {
+        return ld<AUX>(r, voff, soff);
+    }
+    template <int AUX>
+    static __device__ __forceinline__ void str(Rsrc r, uint32_t voff, uint32_t soff, Reg v)
+    {
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(__float_as_uint(v) >> 16), r, (int)voff,
+                                              (int)soff, AUX);
     }
 };
 
@@ -219,6 +261,10 @@ template <int DX> __device__ __forceinline__ float lane_from(float v)
         return __int_as_float(
             __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
     return v;
+}
+template <int DX> __device__ __forceinline__ uint32_t lane_from(uint32_t v)
+{
+    return __float_as_uint(lane_from<DX>(__uint_as_float(v)));
 }
 
 // -------------------------------------------------------------- layouts

@@ -87,6 +87,25 @@ struct HostSums {
                      hipStream_t st);
 };
 
+// Shape of a lattice's or batch's tile passes and the steps of a whole one.
+struct TilePlan {
+    Tile tile;
+    int steps;
+};
+// The shape for one launch over n lattices of nx[i] x ny[i] nodes.
+TilePlan tile_plan(const int *nx, const int *ny, int n);
+// Tiles that shape cuts one lattice into.
+inline int tile_strips(int nx, const TilePlan &p)
+{
+    const int own = 64 - 2 * p.steps;
+    return (nx + own - 1) / own;
+}
+inline int tile_bands(int ny, const TilePlan &p)
+{
+    const int own = p.tile.waves * p.tile.rows - 2 * p.steps;
+    return (ny + own - 1) / own;
+}
+
 } // namespace lbk
 
 struct lbk_lattice {
@@ -98,6 +117,7 @@ struct lbk_lattice {
     WsLayout L;
     Geom g;
     Physics ph;
+    lbk::TilePlan plan; // its tile passes
     hipStream_t stream;
     int device;    // the HIP device current at create
     char *ws;
@@ -228,18 +248,13 @@ inline bool three_step_pass(const lbk_lattice *lat)
 }
 
 // Whether the automatic mode advances this lattice in tile passes (several
-// steps per launch, launch_tile), and the shape and step count it takes.
-// They lead at every size: 64 x 32 FP32 2.0 us a step against 3.2 with single
+// steps per launch, launch_tile).  They lead at every size: 64 x 32 FP32 2.0 us a step against 3.2 with single
 // sweeps, 1024 x 512 6.9 against 10.2, 2048 x 2048 31 against 43 in three-step
 // passes, 4096 x 4096 108 against 128.  The exception are 16-bit lattices of
 // 2^23 nodes and more outside the standard model: their conversions and the
 // general node update make the tile pass's recomputed rows dearer than the
 // marching pass's (121.5 against 116.9 us on 4096 x 4096 FP16).  An explicit
 // band asks for the marching passes, too.
-struct TilePlan {
-    Tile tile;
-    int steps;
-};
 inline bool tile_pass(const lbk_lattice *lat)
 {
     const lbk_desc &d = lat->d;
@@ -247,7 +262,6 @@ inline bool tile_pass(const lbk_lattice *lat)
            (d.storage == LBK_F32 || (d.bc_x == LBK_BC_PRESSURE && lat->ph.standard) ||
             (int64_t)d.nx * d.ny < three_step_nodes(d.storage));
 }
-TilePlan tile_plan(int nx, int ny);
 
 // One launch of the lattice's next steps src -> dst: how many of the `left`
 // steps it advances, by which pass.

@@ -225,6 +225,21 @@ hipError_t launch_batch_sweep2(int storage, int bcx, int bcy, const SampleDesc *
                                const int *tile_sample, int ntiles, int parity, int band,
                                hipStream_t st);
 
+// `steps` steps of every sample of a batch in one launch, parity -> parity ^ 1
+// (bitwise as many launch_batch_sweep calls): the tile list is cut for tile
+// shape t with `halo` >= steps halo nodes (64 - 2 halo columns by t.waves *
+// t.rows - 2 halo rows a tile; the descriptors' tpr = tiles per row of tiles).
+// standard: every sample's Physics::standard.
+hipError_t launch_batch_tile(int storage, int bcx, int bcy, const SampleDesc *samples,
+                             const int *tile_sample, int ntiles, int parity, const Tile &t,
+                             int halo, int steps, int standard, hipStream_t st);
+// The same for a batched gradient's recomputing steps, level src -> dst,
+// recording step k into history slot hist_slot + k (hist_slot < 0: none).
+hipError_t launch_batch_rec_tile(int storage, int bcx, int bcy, const AdjSampleDesc *samples,
+                                 const int *tile_sample, int ntiles, const Tile &t, int halo,
+                                 int steps, int standard, LevelSel src, LevelSel dst,
+                                 int hist_slot, hipStream_t st);
+
 // Read-out partials of every sample over tiles of kBlock nodes
 // ([MAC_SLOTS][ntiles]) and their per-sample fixed-order sums
 // out[nsamples][slots].

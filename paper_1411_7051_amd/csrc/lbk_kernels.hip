@@ -132,7 +132,7 @@ __device__ __forceinline__ void sweep2_strip_dir(const char *__restrict__ src,
     // The steps in march order: p, c, n are the rows at positions m - 1, m,
     // m + 1, which are the physical rows below, at and above (DIR = 1) or
     // above, at and below (DIR = -1).
-    auto first = [&](const Mid &p, const Mid &c, const Mid &n, int m, bool rec, Mid &out) {
+    auto first = [&](const Mid<T> &p, const Mid<T> &c, const Mid<T> &n, int m, bool rec, Mid<T> &out) {
         const int y = Y(m);
         first_step<T, BCX, HIST>(ph, s, inv_s, g, DIR > 0 ? p : n, c, DIR > 0 ? n : p,
                                  wall_lo(y), wall_hi(y), ln, wrap(y), hist1, rec, out);
@@ -142,7 +142,7 @@ __device__ __forceinline__ void sweep2_strip_dir(const char *__restrict__ src,
     // in use, m + 3 and m + 4 in flight (loads are issued two rows ahead of
     // their use, which keeps enough of them outstanding per wave to cover
     // HBM latency), intermediate rows m - 1 .. m + 1 (m0..m2).
-    Mid a1, a2, a3, a4, a5, m0, m1, m2;
+    Mid<T> a1, a2, a3, a4, a5, m0, m1, m2;
     load_node<T>(src, lay, med, mlay, held(Y(-2)), ln.x, a4);
     load_node<T>(src, lay, med, mlay, held(Y(-1)), ln.x, a5);
     load_node<T>(src, lay, med, mlay, Y(0), ln.x, a1);
@@ -156,7 +156,7 @@ __device__ __forceinline__ void sweep2_strip_dir(const char *__restrict__ src,
     // old-row registers in rotated roles, so no loaded value is ever copied
     // (a copy would make the wave wait for its load -- and for the stores
     // issued after it -- at that point rather than at the value's first use).
-    auto row = [&](int m, const Mid &u0, const Mid &u1, const Mid &u2, Mid &nx) {
+    auto row = [&](int m, const Mid<T> &u0, const Mid<T> &u1, const Mid<T> &u2, Mid<T> &nx) {
         // the last output row needs old rows up to position nb + 1
         load_node<T>(src, lay, med, mlay, held(Y(m + 4)), ln.x, nx, m + 4 <= nb + 1);
         first(u0, u1, u2, m + 1, owned && m + 1 < nb, m2);
@@ -297,19 +297,19 @@ __device__ __forceinline__ void sweep3x_strip_dir(const char *__restrict__ src,
     // One step of the row at march position m from the rows at m - 1, m,
     // m + 1 of the level below (old or intermediate), rounded as stored;
     // recorded into hist where rec (a row of this band, an owned lane).
-    auto step = [&](const Mid &p, const Mid &c, const Mid &n, int m, float *hist, bool rec,
-                    Mid &out) {
+    auto step = [&](const Mid<T> &p, const Mid<T> &c, const Mid<T> &n, int m, float *hist, bool rec,
+                    Mid<T> &out) {
         const int y = Y(m);
         first_step<T, BCX, HIST>(ph, s, inv_s, g, DIR > 0 ? p : n, c, DIR > 0 ? n : p,
                                  wall_lo(y), wall_hi(y), ln, wrap(y), hist, rec, out);
     };
-    auto load = [&](int m, Mid &out) {
+    auto load = [&](int m, Mid<T> &out) {
         // the last output row needs old rows up to position nb + 2
         load_node<T>(src, lay, med, mlay, held(Y(m)), ln.x, out, m <= nb + 2);
     };
 
     // old rows a1..a5, first intermediate level p0..p2, second q0..q2
-    Mid a1, a2, a3, a4, a5, p0, p1, p2, q0, q1, q2;
+    Mid<T> a1, a2, a3, a4, a5, p0, p1, p2, q0, q1, q2;
     load(-3, a1);
     load(-2, a2);
     load(-1, a3);
@@ -331,7 +331,7 @@ __device__ __forceinline__ void sweep3x_strip_dir(const char *__restrict__ src,
     // One output row m: u1..u3 are the old rows at positions m + 1 .. m + 3,
     // nx receives position m + 5; p0, p1 hold the first level's rows m,
     // m + 1 and q0, q1 the second level's rows m - 1, m.
-    auto row = [&](int m, const Mid &u1, const Mid &u2, const Mid &u3, Mid &nx) {
+    auto row = [&](int m, const Mid<T> &u1, const Mid<T> &u2, const Mid<T> &u3, Mid<T> &nx) {
         load(m + 5, nx);
         step(u1, u2, u3, m + 2, hist1, owned && m + 2 < nb, p2);
         step(p0, p1, p2, m + 1, hist2, owned && m + 1 < nb, q2);

@@ -163,8 +163,9 @@ __device__ __forceinline__ void sweep_node(const char *src, char *dst, const Lay
 
 // One node of a level as a pull reads it: density and deviations (storage
 // unit, as stored), with the node's medium.
-struct Mid {
-    float rho, h[9];
+template <typename T> struct Mid {
+    float rho;
+    typename Elem<T>::Reg h[9];
     float e, drag, kn0; // e = eps, or 1 / eps under MODEL_STD (0 where eps = 0)
 };
 
@@ -173,7 +174,7 @@ struct Mid {
 // resources: its loads return 0 without touching memory.
 template <typename T, int MODEL = MODEL_GEN>
 __device__ __forceinline__ void load_node(const char *src, const Layout &lay, const char *med,
-                                          const MLayout &mlay, int y, uint32_t x, Mid &m,
+                                          const MLayout &mlay, int y, uint32_t x, Mid<T> &m,
                                           bool live = true)
 {
     const Rsrc row = make_rsrc(src + (uint64_t)y * lay.row, live ? (uint32_t)lay.row : 0u);
@@ -184,7 +185,7 @@ __device__ __forceinline__ void load_node(const char *src, const Layout &lay, co
     constexpr uint32_t es = sizeof(T);
 #pragma unroll
     for (int i = 0; i < 9; ++i)
-        m.h[i] = Elem<T>::template ld<0>(row, x * es, lay.h_off + i * lay.h_slot);
+        m.h[i] = Elem<T>::template ldr<0>(row, x * es, lay.h_off + i * lay.h_slot);
     const Rsrc mr = make_rsrc(med + (uint64_t)y * mlay.row, live ? (uint32_t)mlay.row : 0u);
     m.e = ld_f32(mr, x * 4, 0);
     if (MODEL == MODEL_STD)
@@ -197,31 +198,31 @@ __device__ __forceinline__ void load_node(const char *src, const Layout &lay, co
 // of the previous level: the arithmetic of pull() with the neighbour values
 // taken from registers and adjacent lanes.
 template <typename T, int BCX>
-__device__ __forceinline__ void pull_mid(const Mid &dn, const Mid &c, const Mid &up, bool wym,
+__device__ __forceinline__ void pull_mid(const Mid<T> &dn, const Mid<T> &c, const Mid<T> &up, bool wym,
                                          bool wyp, bool wxm, bool wxp, float s, float &rc,
                                          float (&d)[9])
 {
     rc = c.rho;
-    d[0] = c.h[0];
+    d[0] = Elem<T>::val(c.h[0]);
 #pragma unroll
     for (int i = 1; i < 9; ++i) {
         const int ex = ex_of(i), ey = ey_of(i);
         const bool wall_y = (ey == 1 && wym) || (ey == -1 && wyp); // uniform
-        const Mid &m = ey == 1 ? dn : (ey == -1 ? up : c);
+        const Mid<T> &m = ey == 1 ? dn : (ey == -1 ? up : c);
         const float ws = Elem<T>::kScaled ? w_of(i) * s : w_of(i);
         // a wall bounces the pull back: a select, not a branch, so that no
         // control flow splits the row's loads from their uses
         float df = (ex == 1 ? lane_from<1>(m.rho) : (ex == -1 ? lane_from<-1>(m.rho) : m.rho)) - rc;
-        float h = ex == 1 ? lane_from<1>(m.h[i]) : (ex == -1 ? lane_from<-1>(m.h[i]) : m.h[i]);
+        auto h = ex == 1 ? lane_from<1>(m.h[i]) : (ex == -1 ? lane_from<-1>(m.h[i]) : m.h[i]);
         if (ey != 0) {
             df = wall_y ? 0.0f : df;
             h = wall_y ? c.h[opp_of(i)] : h;
         }
-        d[i] = ws * df + h;
+        d[i] = ws * df + Elem<T>::val(h);
         if (BCX == BC_WALL) {
             const bool wall_x = (ex == 1 && wxm) || (ex == -1 && wxp); // per lane, edges only
             if (wall_x)
-                d[i] = c.h[opp_of(i)];
+                d[i] = Elem<T>::val(c.h[opp_of(i)]);
         }
     }
 }
@@ -240,8 +241,8 @@ struct Lanes {
 // Returns the new density, the unrounded deviations hs and, for the
 // history, (jx, jy).
 template <typename T, int BCX, int MODEL = MODEL_GEN>
-__device__ __forceinline__ float step_from(const Physics &ph, float s, float inv_s, const Mid &dn,
-                                           const Mid &c, const Mid &up, bool wym, bool wyp,
+__device__ __forceinline__ float step_from(const Physics &ph, float s, float inv_s, const Mid<T> &dn,
+                                           const Mid<T> &c, const Mid<T> &up, bool wym, bool wyp,
                                            const Lanes &ln, bool any_solid, float (&hs)[9],
                                            float &jx, float &jy)
 {
@@ -281,9 +282,9 @@ __device__ __forceinline__ float step_from(const Physics &ph, float s, float inv
 // First step of row y: the intermediate node as the second step reads it.
 template <typename T, int BCX, bool HIST>
 __device__ __forceinline__ void first_step(const Physics &ph, float s, float inv_s, const Geom &g,
-                                           const Mid &dn, const Mid &c, const Mid &up, bool wym,
-                                           bool wyp, const Lanes &ln, int y, float *hist,
-                                           bool rec, Mid &m)
+                                           const Mid<T> &dn, const Mid<T> &c, const Mid<T> &up,
+                                           bool wym, bool wyp, const Lanes &ln, int y, float *hist,
+                                           bool rec, Mid<T> &m)
 {
     float hs[9], jx, jy;
     m.rho = step_from<T, BCX>(ph, s, inv_s, dn, c, up, wym, wyp, ln, any_lane(!(c.e > 0.0f)), hs,
@@ -292,7 +293,7 @@ __device__ __forceinline__ void first_step(const Physics &ph, float s, float inv
         record(hist, g, y, ln.x, m.rho, jx, jy, false);
 #pragma unroll
     for (int i = 0; i < 9; ++i)
-        m.h[i] = Elem<T>::round(hs[i]);
+        m.h[i] = Elem<T>::reg(hs[i]);
     m.e = c.e;
     m.drag = c.drag;
     m.kn0 = c.kn0;

@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-from paper_1411_7051_amd import Lattice, inputs  # noqa: E402
+from paper_1411_7051_amd import Batch, Lattice, inputs  # noqa: E402
 
 STORAGES = ("f32", "f16", "bf16")
 
@@ -75,3 +75,53 @@ def test_tile_recording(bcx, obj, storage):
             lat.close()
         assert out[0][0] == out[1][0]
         assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[0][2], out[1][2])
+
+
+BATCH_SIZES = [(33, 7), (300, 41), (59, 130), (130, 64), (3, 2), (517, 90)]
+
+
+@pytest.mark.parametrize("storage", STORAGES)
+@pytest.mark.parametrize("bcx,bcy", [(inputs.PRESSURE, inputs.PERIODIC),
+                                     (inputs.PRESSURE, inputs.WALL),
+                                     (inputs.PERIODIC, inputs.WALL),
+                                     (inputs.WALL, inputs.PERIODIC)])
+@pytest.mark.parametrize("graph", [0, 10, 14])
+def test_batch_tile_bitwise(storage, bcx, bcy, graph):
+    """Tile passes over a batch (remainders shorter than a whole pass, graph
+    replays of odd and even numbers of launches) against single sweeps of
+    each sample; with FP32 the samples' models differ."""
+    cases = [medium(nx, ny, seed=10 + i, bc_y=bcy, **drive(bcx))
+             for i, (nx, ny) in enumerate(BATCH_SIZES)]
+    extra = [dict(rho_ref=1.0 + 0.5 * (i & 1)) if storage == "f32" else {} for i in range(6)]
+    lats = [Lattice(c.eps, c.k, c.kn0, storage=storage, **dict(c.params, **e))
+            for c, e in zip(cases, extra)]
+    solo = [Lattice(c.eps, c.k, c.kn0, storage=storage, pass_mode="single", check_every=0,
+                    **dict(c.params, **e)) for c, e in zip(cases, extra)]
+    b = Batch(lats)
+    b.set_launch(64, 2, 0, graph)
+    for n in (1, 7, 29):
+        b.step(n)
+    for a, s in zip(lats, solo):
+        s.step(37)
+        assert torch.equal(a.save_state(), s.save_state())
+
+
+def test_batch_tile_large_and_gradient():
+    """Two rows a wave (a batch of 2^21 nodes), and a batched gradient whose
+    recomputing passes are tile passes."""
+    cases = [medium(nx, ny, seed=20, **drive(inputs.PRESSURE))
+             for nx, ny in ((1200, 900), (700, 1500))]
+    lats = [Lattice(c.eps, c.k, c.kn0, storage="f16", **c.params) for c in cases]
+    Batch(lats).step(13)
+    for a, c in zip(lats, cases):
+        s = Lattice(c.eps, c.k, c.kn0, storage="f16", pass_mode="single", **c.params)
+        s.step(13)
+        assert torch.equal(a.save_state(), s.save_state())
+    cases = [medium(nx, ny, seed=30 + i, **drive(inputs.PRESSURE))
+             for i, (nx, ny) in enumerate(BATCH_SIZES)]
+    lats = [Lattice(c.eps, c.k, c.kn0, **c.params) for c in cases]
+    J, g, gk = Batch(lats).gradient(23, ckpt_every=13, hist_len=6, wrt_kn0=True)
+    for i, c in enumerate(cases):
+        s = Lattice(c.eps, c.k, c.kn0, pass_mode="single", **c.params)
+        Js, gs, gks = s.gradient(23, ckpt_every=13, hist_len=6, wrt_kn0=True)
+        assert J[i] == Js and torch.equal(g[i], gs) and torch.equal(gk[i], gks)
