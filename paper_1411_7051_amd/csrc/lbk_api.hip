@@ -123,35 +123,34 @@ void split(double v, float &hi, float &lo)
 } // namespace
 
 // Shape and steps of tile passes over one or several lattices: the least
-// predicted time per step.  A launch costs about 4.2 us (dispatch, the latency of the loads, the
-// drain of the stores) and each row update a workgroup makes u_inf per tile
-// of its compute unit's share plus c for what one tile alone leaves
-// exposed (its waves wait for one another at every step); u_inf and c in us,
-// for one and two rows per wave, fit the measured times of lattices from
-// 33 x 21 to 4096 x 4096 within about 15%, which orders the shapes right:
-// 64 x 32 takes 8 x 1 rows and 3 steps (2.0 us a step; 16 x 1 and 6 steps
-// 2.3), 256 x 256 16 x 1 and 5 (2.4; 16 x 2 and 5 4.4), 1024 x 512 16 x 1 and 3
-// (6.9; 8 x 2 and 3 7.1), 4096 x 4096 16 x 2 and 4 (108; 16 x 1 and 3 137).
+// predicted time per step.  A launch costs about 4.2 us (dispatch, the latency
+// of the loads, the drain of the stores); every tile of a compute unit's share
+// takes 0.103 us per row it loads and 0.043 us per row update; and 0.07 us per
+// row update of one tile is what the barriers leave exposed whatever the
+// share.  The constants fit the FP32 times of ten shapes on lattices from
+// 33 x 21 to 4096 x 4096 within about 10% (16-bit ones run alike), which
+// orders the shapes right where they differ: us a step, chosen against the next
+// candidate kind, 64 x 32: 2.1 (8 x 1 rows, 3 steps) / 2.5 (12 x 1, 4);
+// 256 x 256: 2.4 (16 x 1, 5) / 2.5 (8 x 2, 5); 777 x 333: 4.2 (16 x 1, 3) / 4.7
+// (16 x 2, 5); 1024 x 512: 6.2 (16 x 2, 5) / 6.9 (16 x 1, 3); 1024 x 1024: 9.6
+// (12 x 2, 4) / 10.4 (16 x 2, 5); 4096 x 4096: 99 (16 x 2, 4) / 106 (12 x 2, 4).
 TilePlan lbk::tile_plan(const int *nx, const int *ny, int n)
 {
-    static const TilePlan cand[] = {{{8, 1}, 3},  {{12, 1}, 4}, {{16, 1}, 3}, {{16, 1}, 4},
-                                    {{16, 1}, 5}, {{16, 2}, 4}, {{16, 2}, 5}};
-    const double launch_us = 4.2, u_inf[2] = {0.100, 0.078}, c[2] = {0.060, 0.070};
-    const int cus = 256;
+    static const TilePlan cand[] = {{{8, 1}, 3},  {{12, 1}, 3}, {{12, 1}, 4}, {{16, 1}, 3},
+                                    {{16, 1}, 4}, {{16, 1}, 5}, {{8, 2}, 3},  {{12, 2}, 4},
+                                    {{16, 2}, 4}, {{16, 2}, 5}};
+    const double cus = 256;
     TilePlan best = cand[0];
     double best_us = INFINITY;
     for (const TilePlan &p : cand) {
-        const int H = p.tile.waves * p.tile.rows, R = p.tile.rows;
         double tiles = 0;
         for (int i = 0; i < n; ++i)
             tiles += (double)tile_strips(nx[i], p) * tile_bands(ny[i], p);
         // tiles of the busiest compute unit: whole ones while they are few
-        const double q = tiles <= 8.0 * cus ? ceil(tiles / cus) : tiles / cus;
-        int rows = 0; // row updates of a tile: waves with rows k + 1 .. H - 2 - k
-        for (int k = 0; k < p.steps; ++k)
-            for (int j = 0; j < H; j += R)
-                rows += (j + R <= k + 1 || j > H - 2 - k) ? 0 : R;
-        const double us = (launch_us + rows * (q * u_inf[R - 1] + c[R - 1])) / p.steps;
+        const double q = tiles <= 8 * cus ? ceil(tiles / cus) : tiles / cus;
+        const int H = p.tile.waves * p.tile.rows;
+        const int rows = p.steps * (H - 1 - p.steps); // row updates: H - 2 - 2 k at step k
+        const double us = (4.2 + q * (0.103 * H + 0.043 * rows) + 0.07 * rows) / p.steps;
         if (us < best_us) {
             best_us = us;
             best = p;

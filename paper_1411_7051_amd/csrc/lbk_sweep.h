@@ -210,10 +210,12 @@ __device__ __forceinline__ void pull_mid(const Mid<T> &dn, const Mid<T> &c, cons
         const bool wall_y = (ey == 1 && wym) || (ey == -1 && wyp); // uniform
         const Mid<T> &m = ey == 1 ? dn : (ey == -1 ? up : c);
         const float ws = Elem<T>::kScaled ? w_of(i) * s : w_of(i);
-        // a wall bounces the pull back: a select, not a branch, so that no
-        // control flow splits the row's loads from their uses
+        // the shift of rho folds into the subtraction, the widening of an
+        // FP16 h into the FMA
         float df = (ex == 1 ? lane_from<1>(m.rho) : (ex == -1 ? lane_from<-1>(m.rho) : m.rho)) - rc;
         auto h = ex == 1 ? lane_from<1>(m.h[i]) : (ex == -1 ? lane_from<-1>(m.h[i]) : m.h[i]);
+        // a wall bounces the pull back: a select, not a branch, so that no
+        // control flow splits the row's loads from their uses
         if (ey != 0) {
             df = wall_y ? 0.0f : df;
             h = wall_y ? c.h[opp_of(i)] : h;
@@ -232,7 +234,7 @@ struct Lanes {
     uint32_t x;     // the lane's column, wrapped (periodic) or clamped
     bool wxm, wxp;  // x walls on either side of the column
     bool bin, bout; // the inlet / outlet pressure column
-    bool has_b;     // uniform: the wave may hold a pressure column
+    int has_b;      // uniform: the wave may hold a pressure column
 };
 
 // One step of this lane's node at row y from three rows of the previous

@@ -19,16 +19,20 @@
 // Each step is the node update of the single sweep on values rounded as a
 // store would round them, so K steps are bitwise K single sweeps.
 //
-// What bounds it: on lattices that fill the device, the vector issue (16 x 2
-// rows and K = 4 recompute 1.33 updates per node and step and keep eight waves
-// per SIMD: 4096 x 4096 FP32 runs at 108 us a step, against 128 in three-step
-// marching passes with three waves per SIMD, 176 in two-step passes and 237 in
-// single sweeps); on small ones a launch's fixed 4 us.  Two rows a wave are
-// what 64 registers hold (a third makes the device run four waves per SIMD
-// instead of eight, which measured slower at every size).  MODEL_STD, the
-// default model under a pressure drive, is compiled apart: 57 instead of 64
-// registers and about 145 instead of 165 vector instructions an update (108
-// against 119 us).
+// What bounds it: on lattices that fill the device, the vector issue (the
+// counters show the vector units active 98% of the busy time on 4096 x 4096;
+// 16 x 2 rows and K = 4 make 1.29 updates per node and step), with eight waves
+// per SIMD: FP32 99 us a step there against 128 in three-step marching passes
+// (three waves per SIMD), 176 in two-step passes and 237 in single sweeps, FP16
+// 97 against 115, 128 and 150; on small ones a launch's fixed 4 us.  Two rows
+// a wave are what 64 registers hold (with three or four the device runs half
+// the waves, which measured slower at every size).  What an update does not
+// need is kept out of it: a row beyond the rows still wanted is skipped, LDS
+// addresses are constants of the code (the two buffers' steps are unrolled),
+// only tiles at a wall carry the bounce-back selects and only waves that hold a
+// pressure column the exchange with its neighbour (119 -> 99 us in all with
+// the next).  MODEL_STD, the default model under a pressure drive, is compiled
+// apart: about 135 instead of 155 vector instructions an update.
 #pragma once
 
 #include "lbk_sweep.h"
@@ -36,25 +40,34 @@
 namespace lbk {
 
 // What one wave's row gives its y neighbour in another wave: the density and
-// the populations that cross (2, 5, 6 upwards, 4, 7, 8 downwards).
+// the populations that cross (4, 7, 8 downwards from its first row, 2, 5, 6
+// upwards from its last), Elem<T>::Reg as bits.
 struct Edge {
     float rho[64];
-    uint32_t h[3][64]; // Elem<T>::Reg as bits
+    uint32_t h[3][64];
+};
+// The edges a workgroup exchanges at one step: [parity][wave], its first and
+// last rows.
+struct Edges {
+    Edge first, last;
 };
 __device__ __forceinline__ uint32_t reg_bits(float v) { return __float_as_uint(v); }
 __device__ __forceinline__ uint32_t reg_bits(uint32_t v) { return v; }
 __device__ __forceinline__ void bits_reg(uint32_t b, float &v) { v = __uint_as_float(b); }
 __device__ __forceinline__ void bits_reg(uint32_t b, uint32_t &v) { v = b; }
+constexpr size_t kTileLds = 2 * (size_t)kTileMaxWaves * sizeof(Edges);
 
 // One workgroup's tile: strip `strip` by band `band` of a lattice cut for
 // `halo` >= steps halo nodes on each side (waves, R), advanced `steps` steps.
-template <typename T, int BCX, int BCY, bool HIST, int R, int MODEL>
-__device__ __forceinline__ void tile_steps(const char *__restrict__ src, char *__restrict__ dst,
+// EDGE: rows at a wall may be among the tile's (the selects of the bounce-back
+// are twelve instructions a row update that other tiles are spared).
+template <typename T, int BCX, int BCY, bool HIST, int R, int MODEL, bool EDGE>
+__device__ __forceinline__ void tile_advance(const char *__restrict__ src, char *__restrict__ dst,
                                            const Layout &lay, const char *__restrict__ med,
                                            const MLayout &mlay, const Geom &g, const Physics &ph,
                                            float s, float inv_s, int halo, int steps, int strip,
                                            int band, float *__restrict__ hist,
-                                           uint64_t hist_bytes, Edge *__restrict__ edges)
+                                           uint64_t hist_bytes, Edges *__restrict__ edges)
 {
     const int lane = (int)(threadIdx.x & 63);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -79,76 +92,89 @@ __device__ __forceinline__ void tile_steps(const char *__restrict__ src, char *_
     ln.wxp = BCX == BC_WALL && ln.x == (uint32_t)g.nx - 1;
     ln.bin = BCX == BC_PRESSURE && xr == 0;
     ln.bout = BCX == BC_PRESSURE && xr == g.nx - 1;
-    ln.has_b = BCX == BC_PRESSURE && any_lane(ln.bin || ln.bout);
+    ln.has_b = BCX == BC_PRESSURE && any_lane(ln.bin || ln.bout) ? 1 : 0;
     const int y0 = band * own_y, y1 = min(y0 + own_y, g.ny);
     // tile row j is the lattice's row y0 - halo + j; rows beyond a wall
     // hold copies that the bounce-back never reads
     const int j0 = wave * R;
     auto row_of = [&](int j) { return y0 - halo + j; };
     auto held = [&](int y) {
-        return BCY == BC_PERIODIC ? ((y % g.ny) + g.ny) % g.ny
-                                  : (y < 0 ? 0 : (y >= g.ny ? g.ny - 1 : y));
+        if (BCY != BC_PERIODIC)
+            return y < 0 ? 0 : (y >= g.ny ? g.ny - 1 : y);
+        while (y < 0) // uniform; more than once only where ny is below the tile's rows
+            y += g.ny;
+        while (y >= g.ny)
+            y -= g.ny;
+        return y;
     };
     Mid<T> a[R];
-    bool solids = false; // whether any of the wave's nodes is impermeable
+    int solids = 0; // whether any of the wave's nodes is impermeable (an int: a
+                    // flag kept as a lane mask costs two instructions a test)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         load_node<T, MODEL>(src, lay, med, mlay, held(row_of(j0 + r)), ln.x, a[r]);
-        solids = solids || any_lane(!(a[r].e > 0.0f));
+        solids |= any_lane(!(a[r].e > 0.0f)) ? 1 : 0;
     }
-    Edge *lo = edges, *hi = edges + 2 * waves; // [parity][wave]: first and last rows
-    for (int k = 0; k < steps; ++k) {
-        const int p = (k & 1) * waves;
-        if (waves > 1) {
-            Edge &f = lo[p + wave], &l = hi[p + wave];
-            f.rho[lane] = a[0].rho;
-            f.h[0][lane] = reg_bits(a[0].h[4]);
-            f.h[1][lane] = reg_bits(a[0].h[7]);
-            f.h[2][lane] = reg_bits(a[0].h[8]);
-            l.rho[lane] = a[R - 1].rho;
-            l.h[0][lane] = reg_bits(a[R - 1].h[2]);
-            l.h[1][lane] = reg_bits(a[R - 1].h[5]);
-            l.h[2][lane] = reg_bits(a[R - 1].h[6]);
-            __syncthreads();
-        }
-        // rows k + 1 .. H - 2 - k of the tile are complete after this step; a
-        // wave with none of them, or none in the lattice's rows that remain
-        // to be stored, has nothing to do
-        if (j0 + R <= k + 1 || j0 > H - 2 - k)
-            continue;
-        Mid<T> dn = a[0], up = a[R - 1];
-        if (wave > 0) {
-            const Edge &e = hi[p + wave - 1];
-            dn.rho = e.rho[lane];
-            bits_reg(e.h[0][lane], dn.h[2]);
-            bits_reg(e.h[1][lane], dn.h[5]);
-            bits_reg(e.h[2][lane], dn.h[6]);
-        }
-        if (wave < waves - 1) {
-            const Edge &e = lo[p + wave + 1];
-            up.rho = e.rho[lane];
-            bits_reg(e.h[0][lane], up.h[4]);
-            bits_reg(e.h[1][lane], up.h[7]);
-            bits_reg(e.h[2][lane], up.h[8]);
-        }
+    // The first wave's lower and the last wave's upper neighbours lie outside
+    // the tile: they read their own edges, into rows that are never stored.
+    Edges *const mine = edges + wave;
+    const Edge *const below = wave > 0 ? &edges[wave - 1].last : &mine->last;
+    const Edge *const above = wave < waves - 1 ? &edges[wave + 1].first : &mine->first;
+    // Step k; P = k & 1 is the buffer of the edges, a constant of the code, so
+    // that no LDS address is computed in the loop.
+    auto step = [&](int k, auto parity) {
+        constexpr int P = decltype(parity)::value * kTileMaxWaves; // edges per buffer
+        Edges &m = mine[P];
+        m.first.rho[lane] = a[0].rho;
+        m.first.h[0][lane] = reg_bits(a[0].h[4]);
+        m.first.h[1][lane] = reg_bits(a[0].h[7]);
+        m.first.h[2][lane] = reg_bits(a[0].h[8]);
+        m.last.rho[lane] = a[R - 1].rho;
+        m.last.h[0][lane] = reg_bits(a[R - 1].h[2]);
+        m.last.h[1][lane] = reg_bits(a[R - 1].h[5]);
+        m.last.h[2][lane] = reg_bits(a[R - 1].h[6]);
+        __syncthreads();
+        // rows k + 1 .. H - 2 - k of the tile are complete after this step;
+        // the others have nothing to do
+        const int lo = k + 1, hi = H - 2 - k;
+        if (j0 + R <= lo || j0 > hi)
+            return;
+        const Edge &d = reinterpret_cast<const Edges *>(below)[P].first;
+        const Edge &u = reinterpret_cast<const Edges *>(above)[P].first;
+        Mid<T> dn, up; // the values a pull reads of them
+        dn.rho = d.rho[lane];
+        bits_reg(d.h[0][lane], dn.h[2]);
+        bits_reg(d.h[1][lane], dn.h[5]);
+        bits_reg(d.h[2][lane], dn.h[6]);
+        up.rho = u.rho[lane];
+        bits_reg(u.h[0][lane], up.h[4]);
+        bits_reg(u.h[1][lane], up.h[7]);
+        bits_reg(u.h[2][lane], up.h[8]);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int y = row_of(j0 + r);
             const Mid<T> old = a[r];
-            float hs[9], jx, jy;
-            const float rho = step_from<T, BCX, MODEL>(
-                ph, s, inv_s, dn, old, r + 1 < R ? a[r + 1] : up, BCY == BC_WALL && y == 0,
-                BCY == BC_WALL && y == g.ny - 1, ln, solids, hs, jx, jy);
-            if (HIST && owned && y >= y0 && y < y1)
-                record(reinterpret_cast<float *>(reinterpret_cast<char *>(hist) +
-                                                 (uint64_t)k * hist_bytes),
-                       g, y, ln.x, rho, jx, jy, false);
-            a[r].rho = rho;
+            if (R == 1 || (j0 + r >= lo && j0 + r <= hi)) {
+                const int y = row_of(j0 + r);
+                float hs[9], jx, jy;
+                const float rho = step_from<T, BCX, MODEL>(
+                    ph, s, inv_s, dn, old, r + 1 < R ? a[r + 1] : up, EDGE && y == 0,
+                    EDGE && y == g.ny - 1, ln, solids != 0, hs, jx, jy);
+                if (HIST && owned && y >= y0 && y < y1)
+                    record(reinterpret_cast<float *>(reinterpret_cast<char *>(hist) +
+                                                     (uint64_t)k * hist_bytes),
+                           g, y, ln.x, rho, jx, jy, false);
+                a[r].rho = rho;
 #pragma unroll
-            for (int i = 0; i < 9; ++i)
-                a[r].h[i] = Elem<T>::reg(hs[i]);
+                for (int i = 0; i < 9; ++i)
+                    a[r].h[i] = Elem<T>::reg(hs[i]);
+            }
             dn = old;
         }
+    };
+    for (int k = 0; k < steps; k += 2) {
+        step(k, std::integral_constant<int, 0>{});
+        if (k + 1 < steps)
+            step(k + 1, std::integral_constant<int, 1>{});
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -164,6 +190,25 @@ __device__ __forceinline__ void tile_steps(const char *__restrict__ src, char *_
                 Elem<T>::template str<0>(out, ln.x * es, lay.h_off + i * lay.h_slot, a[r].h[i]);
         }
     }
+}
+
+template <typename T, int BCX, int BCY, bool HIST, int R, int MODEL>
+__device__ __forceinline__ void tile_steps(const char *__restrict__ src, char *__restrict__ dst,
+                                           const Layout &lay, const char *__restrict__ med,
+                                           const MLayout &mlay, const Geom &g, const Physics &ph,
+                                           float s, float inv_s, int halo, int steps, int strip,
+                                           int band, float *__restrict__ hist,
+                                           uint64_t hist_bytes, Edges *__restrict__ edges)
+{
+    const int H = (int)(blockDim.x >> 6) * R, top = band * (H - 2 * halo) - halo;
+    if (BCY == BC_WALL && (top <= 0 || top + H >= g.ny))
+        tile_advance<T, BCX, BCY, HIST, R, MODEL, BCY == BC_WALL>(
+            src, dst, lay, med, mlay, g, ph, s, inv_s, halo, steps, strip, band, hist, hist_bytes,
+            edges);
+    else
+        tile_advance<T, BCX, BCY, HIST, R, MODEL, false>(src, dst, lay, med, mlay, g, ph, s,
+                                                         inv_s, halo, steps, strip, band, hist,
+                                                         hist_bytes, edges);
 }
 
 } // namespace lbk

@@ -9,7 +9,7 @@ __global__ __launch_bounds__(kTileMaxWaves * 64, 8) void tile_kernel(
     const char *__restrict__ med, MLayout mlay, Geom g, Physics ph, float s, float inv_s,
     int steps, int strips, float *__restrict__ hist, uint64_t hist_bytes)
 {
-    extern __shared__ Edge edges[]; // [first, last][parity][waves]
+    extern __shared__ Edges edges[]; // [parity][kTileMaxWaves]
     const int L = xcd_remap(blockIdx.x, gridDim.x);
     const int band = L / strips, strip = L - band * strips;
     tile_steps<T, BCX, BCY, HIST, R, MODEL>(src, dst, lay, med, mlay, g, ph, s, inv_s, steps,
@@ -25,7 +25,7 @@ static hipError_t tile_t(const char *src, char *dst, const Layout &lay, const ch
     const int own_x = 64 - 2 * steps, own_y = t.waves * t.rows - 2 * steps;
     const int strips = (g.nx + own_x - 1) / own_x, bands = (g.ny + own_y - 1) / own_y;
     const dim3 grid((unsigned)(strips * bands)), block(t.waves * 64);
-    const size_t lds = 4 * (size_t)t.waves * sizeof(Edge);
+    const size_t lds = kTileLds;
 #define LBK_TILE(HIST, R)                                                                    \
     do {                                                                                     \
         if (BCX == BC_PRESSURE && ph.standard)                                               \
@@ -58,7 +58,7 @@ hipError_t launch_tile(int storage, int bcx, int bcy, const char *src, char *dst
                        const Physics &ph, float s, float inv_s, const Tile &t, int steps,
                        float *hist, uint64_t hist_bytes, hipStream_t st)
 {
-    if (bcy < 0 || bcy > 1 || steps < 1 || t.waves < 1 || t.waves > kTileMaxWaves ||
+    if (bcy < 0 || bcy > 1 || steps < 1 || t.waves < 2 || t.waves > kTileMaxWaves ||
         (t.rows != 1 && t.rows != 2) || 64 - 2 * steps < 1 ||
         t.waves * t.rows - 2 * steps < 1)
         return hipErrorInvalidValue;

@@ -10,7 +10,7 @@ __global__ __launch_bounds__(kTileMaxWaves * 64, 8) void batch_tile_kernel(
     const SampleDesc *__restrict__ samples, const int *__restrict__ tile_sample, int halo,
     int steps, int parity)
 {
-    extern __shared__ Edge edges[];
+    extern __shared__ Edges edges[];
     const int t = xcd_remap(blockIdx.x, gridDim.x);
     const SampleDesc sd = samples[tile_sample[t]];
     const int rel = t - sd.tile0;
@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kTileMaxWaves * 64, 8) void batch_rec_tile_kernel(
     const AdjSampleDesc *__restrict__ samples, const int *__restrict__ tile_sample, int halo,
     int steps, LevelSel src_sel, LevelSel dst_sel, int hist_slot)
 {
-    extern __shared__ Edge edges[];
+    extern __shared__ Edges edges[];
     const int t = xcd_remap(blockIdx.x, gridDim.x);
     const AdjSampleDesc sd = samples[tile_sample[t]];
     const int rel = t - sd.tile0;
@@ -70,7 +70,7 @@ template <int BCX, typename F> void pick(int rows, int standard, F f)
 
 bool valid(int bcy, const Tile &t, int halo, int steps, int ntiles)
 {
-    return bcy >= 0 && bcy <= 1 && t.waves >= 1 && t.waves <= kTileMaxWaves &&
+    return bcy >= 0 && bcy <= 1 && t.waves >= 2 && t.waves <= kTileMaxWaves &&
            (t.rows == 1 || t.rows == 2) && steps >= 1 && halo >= steps && 64 - 2 * halo >= 1 &&
            t.waves * t.rows - 2 * halo >= 1 && ntiles >= 0;
 }
@@ -85,7 +85,7 @@ static hipError_t batch_tile_t(const SampleDesc *samples, const int *tile_sample
     pick<BCX>(t.rows, standard, [&](auto r, auto m) {
         hipLaunchKernelGGL((batch_tile_kernel<T, BCX, BCY, decltype(r)::value,
                                               decltype(m)::value>),
-                           dim3(ntiles), dim3(t.waves * 64), 4 * t.waves * sizeof(Edge), st,
+                           dim3(ntiles), dim3(t.waves * 64), kTileLds, st,
                            samples, tile_sample, halo, steps, parity);
     });
     return hipGetLastError();
@@ -100,11 +100,11 @@ static hipError_t batch_rec_tile_t(const AdjSampleDesc *samples, const int *tile
         constexpr int R = decltype(r)::value, M = decltype(m)::value;
         if (hist_slot >= 0)
             hipLaunchKernelGGL((batch_rec_tile_kernel<T, BCX, BCY, R, M, true>), dim3(ntiles),
-                               dim3(t.waves * 64), 4 * t.waves * sizeof(Edge), st, samples,
+                               dim3(t.waves * 64), kTileLds, st, samples,
                                tile_sample, halo, steps, src, dst, hist_slot);
         else
             hipLaunchKernelGGL((batch_rec_tile_kernel<T, BCX, BCY, R, M, false>), dim3(ntiles),
-                               dim3(t.waves * 64), 4 * t.waves * sizeof(Edge), st, samples,
+                               dim3(t.waves * 64), kTileLds, st, samples,
                                tile_sample, halo, steps, src, dst, hist_slot);
     });
     return hipGetLastError();
