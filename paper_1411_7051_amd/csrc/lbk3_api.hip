@@ -285,26 +285,7 @@ lbk_status lbk3_create(const lbk_desc3 *d, const float *eps, const float *k, con
         return cleanup(fail(LBK_ERR_INVALID_ARG,
                             "%.0f field values out of range (need 0<=eps<=1, k>0 or +inf, "
                             "kn0>=0 finite)", lat->host[FLD_BAD]));
-    lat->eps_b = 0.0;
-    if (d->bc_x == LBK_BC_PRESSURE) {
-        float *col = nullptr;
-        if (hipHostMalloc((void **)&col, 2 * rows * sizeof(float), hipHostMallocDefault) !=
-            hipSuccess)
-            return cleanup(fail(LBK_ERR_DEVICE, "pinned host allocation failed"));
-        bool good = ok(hipMemcpy2DAsync(col, sizeof(float), med, mrow, sizeof(float), rows,
-                                        hipMemcpyDeviceToHost, st), "eps plane") &&
-                    ok(hipMemcpy2DAsync(col + rows, sizeof(float),
-                                        med + (d->nx - 1) * sizeof(float), mrow, sizeof(float),
-                                        rows, hipMemcpyDeviceToHost, st), "eps plane") &&
-                    ok(hipStreamSynchronize(st), "sync");
-        double sum = 0.0;
-        for (size_t i = 0; good && i < 2 * rows; ++i)
-            sum += col[i];
-        (void)hipHostFree(col);
-        if (!good)
-            return cleanup(LBK_ERR_DEVICE);
-        lat->eps_b = sum / (2.0 * rows);
-    }
+    lat->eps_b = d->bc_x == LBK_BC_PRESSURE ? lat->host[FLD_EPS] / (2.0 * rows) : 0.0;
     if (!ok(launch_init3(d->storage, lat->state(0), L.lay, lat->g, d->init, d->rho0, d->rho_in,
                          d->rho_out, lat->s(), st), "init kernel") ||
         !ok(hipStreamSynchronize(st), "sync"))

@@ -558,17 +558,18 @@ __global__ __launch_bounds__(kBlock3) void fields3_kernel(char *med, MLayout mla
                                                            double nu, double *partials, int bpr)
 {
     const Node3 nd = node3_of(g, bpr);
-    double bad[1] = {0.0};
+    double v[FLD_SLOTS] = {0.0, 0.0};
     if (nd.x < (uint32_t)g.nx) {
         const Rsrc row = make_rsrc(med + row3(g, nd.y, nd.z) * mlay.row, (uint32_t)mlay.row);
         const float e = ld_f32(row, nd.x * 4, 0), k = ld_f32(row, nd.x * 4, mlay.slot),
                     kn = ld_f32(row, nd.x * 4, 2 * mlay.slot);
         const bool ok = (e >= 0.0f && e <= 1.0f) && (k > 0.0f) && (kn >= 0.0f && isfinite(kn));
-        bad[0] = ok ? 0.0 : 1.0;
+        v[FLD_BAD] = ok ? 0.0 : 1.0;
+        v[FLD_EPS] = nd.x == 0 || nd.x == (uint32_t)g.nx - 1 ? (double)e : 0.0;
         const float drag = (!ok || isinf(k) || e == 0.0f) ? 0.0f : (float)((double)e * nu / k);
         st_f32(row, nd.x * 4, mlay.slot, drag, false);
     }
-    block_sums<FLD_SLOTS>(bad, partials, xcd_remap3(blockIdx.x, gridDim.x), gridDim.x);
+    block_sums<FLD_SLOTS>(v, partials, xcd_remap3(blockIdx.x, gridDim.x), gridDim.x);
 }
 
 } // namespace

@@ -11,8 +11,10 @@
 
 #include <algorithm>
 #include <chrono>
+#include <mutex>
 #include <new>
 #include <string>
+#include <vector>
 
 using namespace lbk;
 
@@ -222,21 +224,72 @@ lbk_status lbk::advance(lbk_lattice *lat, int64_t n, hipStream_t st)
     return LBK_OK;
 }
 
-bool lbk::HostSums::alloc()
+namespace {
+
+// Pool of result slots: slabs of pinned memory that every device can write,
+// kSlots slots each.  A slab without a taken slot is freed unless it is the
+// only one, so the pool holds at most one page beyond what its users hold.
+constexpr size_t kSlotBytes = 16 * sizeof(double);
+constexpr int kSlots = 32;
+struct Slab {
+    char *base = nullptr;
+    uint32_t taken = 0; // bit per slot
+};
+std::mutex g_slab_mu;
+std::vector<Slab> &slabs()
 {
-    if (hipHostMalloc((void **)&sums, 16 * sizeof(double), hipHostMallocCoherent) != hipSuccess) {
-        sums = nullptr;
-        return false;
+    static std::vector<Slab> *v = new std::vector<Slab>(); // outlives every handle
+    return *v;
+}
+
+} // namespace
+
+bool lbk::HostSums::alloc()
+try {
+    std::lock_guard<std::mutex> lock(g_slab_mu);
+    std::vector<Slab> &v = slabs();
+    Slab *s = nullptr;
+    for (Slab &c : v)
+        if (c.taken != 0xFFFFFFFFu)
+            s = &c;
+    if (!s) {
+        v.reserve(v.size() + 1);
+        Slab n;
+        if (hipHostMalloc((void **)&n.base, kSlots * kSlotBytes,
+                          hipHostMallocCoherent | hipHostMallocPortable) != hipSuccess)
+            return false;
+        v.push_back(n);
+        s = &v.back();
     }
-    memset(sums, 0, 16 * sizeof(double));
+    const int k = __builtin_ctz(~s->taken);
+    s->taken |= 1u << k;
+    sums = reinterpret_cast<double *>(s->base + k * kSlotBytes);
+    memset(sums, 0, kSlotBytes);
     done = reinterpret_cast<uint64_t *>(sums + 8);
+    seq = 0;
     return true;
+} catch (...) { // no memory for the pool's list
+    return false;
 }
 
 void lbk::HostSums::release()
 {
-    (void)hipHostFree(sums);
+    if (!sums)
+        return;
+    std::lock_guard<std::mutex> lock(g_slab_mu);
+    std::vector<Slab> &v = slabs();
+    const char *p = reinterpret_cast<const char *>(sums);
     sums = nullptr;
+    for (size_t i = 0; i < v.size(); ++i) {
+        if (p < v[i].base || p >= v[i].base + kSlots * kSlotBytes)
+            continue;
+        v[i].taken &= ~(1u << ((p - v[i].base) / kSlotBytes));
+        if (v[i].taken == 0 && v.size() > 1) {
+            (void)hipHostFree(v[i].base);
+            v.erase(v.begin() + i);
+        }
+        return;
+    }
 }
 
 lbk_status lbk::HostSums::fetch(const double *partials, int slots, int blocks,
@@ -424,27 +477,7 @@ lbk_status lbk_create(const lbk_desc *d, const float *eps, const float *k, const
                             "kn0>=0 finite)",
                             lat->host[FLD_BAD]));
     // mean porosity of the pressure columns (for the global permeability)
-    lat->eps_b = 0.0;
-    if (d->bc_x == LBK_BC_PRESSURE) {
-        float *col = nullptr;
-        if (hipHostMalloc((void **)&col, 2 * (size_t)d->ny * sizeof(float),
-                          hipHostMallocDefault) != hipSuccess)
-            return cleanup(fail(LBK_ERR_DEVICE, "pinned host allocation failed"));
-        bool ok =
-            hip_ok(hipMemcpy2DAsync(col, sizeof(float), med, mrow, sizeof(float), d->ny,
-                                    hipMemcpyDeviceToHost, st), "eps column") &&
-            hip_ok(hipMemcpy2DAsync(col + d->ny, sizeof(float), med + (d->nx - 1) * sizeof(float),
-                                    mrow, sizeof(float), d->ny, hipMemcpyDeviceToHost, st),
-                   "eps column") &&
-            hip_ok(hipStreamSynchronize(st), "sync");
-        double sum = 0.0;
-        for (int i = 0; ok && i < 2 * d->ny; ++i)
-            sum += col[i];
-        (void)hipHostFree(col);
-        if (!ok)
-            return cleanup(LBK_ERR_DEVICE);
-        lat->eps_b = sum / (2.0 * d->ny);
-    }
+    lat->eps_b = d->bc_x == LBK_BC_PRESSURE ? lat->host[FLD_EPS] / (2.0 * d->ny) : 0.0;
     if (!hip_ok(launch_init_state(d->storage, lat->state(0), L.lay, lat->g, d->init, d->rho0,
                                   d->rho_in, d->rho_out, lat->s(), st), "init kernel") ||
         !hip_ok(hipStreamSynchronize(st), "sync"))

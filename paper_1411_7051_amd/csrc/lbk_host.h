@@ -72,7 +72,8 @@ struct AdjPlan {
 };
 
 // A handle's read-out results on the host: eight sums and a mark per sum in
-// coherent pinned memory.  The finish kernel writes a sum, then its mark; the
+// coherent pinned memory (a slot of a small pool: allocating and freeing
+// pinned memory took longer than the rest of a small lattice's creation).  The finish kernel writes a sum, then its mark; the
 // host polls the marks, which spares a small lattice the copy of the sums
 // and the wait for the stream (together longer than the read-out itself).
 struct HostSums {
@@ -248,19 +249,14 @@ inline bool three_step_pass(const lbk_lattice *lat)
 }
 
 // Whether the automatic mode advances this lattice in tile passes (several
-// steps per launch, launch_tile).  They lead at every size: 64 x 32 FP32 2.0 us a step against 3.2 with single
-// sweeps, 1024 x 512 6.9 against 10.2, 2048 x 2048 31 against 43 in three-step
-// passes, 4096 x 4096 108 against 128.  The exception are 16-bit lattices of
-// 2^23 nodes and more outside the standard model: their conversions and the
-// general node update make the tile pass's recomputed rows dearer than the
-// marching pass's (121.5 against 116.9 us on 4096 x 4096 FP16).  An explicit
-// band asks for the marching passes, too.
+// steps per launch, launch_tile).  They lead at every size and model, us a step
+// against the passes they replace: 64 x 32 FP32 2.1 / 3.2 (single sweeps),
+// 1024 x 512 6.2 / 10.2, 2048 x 2048 27 / 43 (three-step passes), 4096 x 4096
+// 99 / 128; 4096 x 4096 FP16 96 / 107, with a body force 96 / 99, with the
+// Forchheimer term 141 / 143.  An explicit band asks for the marching passes.
 inline bool tile_pass(const lbk_lattice *lat)
 {
-    const lbk_desc &d = lat->d;
-    return d.pass_mode == LBK_PASS_AUTO && d.band == 0 &&
-           (d.storage == LBK_F32 || (d.bc_x == LBK_BC_PRESSURE && lat->ph.standard) ||
-            (int64_t)d.nx * d.ny < three_step_nodes(d.storage));
+    return lat->d.pass_mode == LBK_PASS_AUTO && lat->d.band == 0;
 }
 
 // One launch of the lattice's next steps src -> dst: how many of the `left`

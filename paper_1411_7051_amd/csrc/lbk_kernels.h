@@ -62,6 +62,7 @@ enum {
 };
 enum {
     FLD_BAD = 0,  // number of invalid field values
+    FLD_EPS,      // sum of eps over the columns (planes) x = 0 and x = nx - 1
     FLD_SLOTS
 };
 
@@ -144,8 +145,8 @@ hipError_t launch_finish(const double *partials, int slots, int blocks, unsigned
                          double *out, uint64_t *done, uint64_t seq, hipStream_t st);
 
 // Field set-up: in place, turn the raw k slot into drag = eps nu / k
-// (0 where k = +inf or eps = 0) and count invalid values into
-// partials [FLD_SLOTS][blocks].
+// (0 where k = +inf or eps = 0), count invalid values and sum the end
+// columns' eps into partials [FLD_SLOTS][blocks].
 hipError_t launch_fields(char *med, const MLayout &mlay, const Geom &g, double nu,
                          double *partials, hipStream_t st);
 

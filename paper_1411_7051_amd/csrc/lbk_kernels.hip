@@ -790,19 +790,20 @@ __global__ __launch_bounds__(kBlock) void fields_kernel(char *med, MLayout mlay,
                                                          double nu, double *partials, int bpr)
 {
     const Node nd = node_of(bpr);
-    double bad[1] = {0.0};
+    double v[FLD_SLOTS] = {0.0, 0.0};
     if (nd.x < (uint32_t)g.nx) {
         const Rsrc row = med_row(med, mlay, nd.y);
         const float e = ld_f32(row, nd.x * 4, 0), k = ld_f32(row, nd.x * 4, mlay.slot),
                     kn = ld_f32(row, nd.x * 4, 2 * mlay.slot);
         const bool ok = (e >= 0.0f && e <= 1.0f) && (k > 0.0f) && (kn >= 0.0f) && isfinite(kn);
-        bad[0] = ok ? 0.0 : 1.0;
+        v[FLD_BAD] = ok ? 0.0 : 1.0;
+        v[FLD_EPS] = nd.x == 0 || nd.x == (uint32_t)g.nx - 1 ? (double)e : 0.0;
         double d = 0.0;
         if (ok && e > 0.0f && isfinite(k))
             d = (double)e * nu / (double)k;
         st_f32(row, nd.x * 4, mlay.slot, (float)d, false);
     }
-    block_sums<FLD_SLOTS>(bad, partials, nd.L, gridDim.x);
+    block_sums<FLD_SLOTS>(v, partials, nd.L, gridDim.x);
 }
 
 template <typename T>
