@@ -635,24 +635,26 @@ __device__ __forceinline__ void collide(const Physics &ph, float rho, float inc,
 // FP64 sums of N <= 8 values over a workgroup of 256 threads (4 waves), in a
 // fixed order: out[k * stride + at] receives value k.  Every thread must call
 // it.  Inside a wave the values are halved with the lanes: at offset 32 each
-// half-wave keeps four of the values and hands over the other four, at 16
-// two, at 8 one, so eight sums take 10 shuffles instead of 48 (the additions,
-// and so the result, are those of a butterfly per value); lane 8 k then holds
-// value k, and one exchange through LDS adds the four waves in order.
+// half-wave keeps half of the values and hands over the others, and so on, so
+// eight sums take 10 shuffles instead of 48 (the additions, and so the result,
+// are those of a butterfly per value); lane k * 64 / P (P = N rounded up to a
+// power of two) then holds value k, and one exchange through LDS adds the four
+// waves in order.
 template <int N>
 __device__ __forceinline__ void block_sums(const double (&v)[N], double *__restrict__ out,
                                            int64_t at, int64_t stride)
 {
     static_assert(N >= 1 && N <= 8, "slots of one packed reduction");
-    __shared__ double sh[4][8];
+    constexpr int P = N <= 1 ? 1 : (N <= 2 ? 2 : (N <= 4 ? 4 : 8)), W = 64 / P;
+    __shared__ double sh[4][P];
     const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
-    double a[8];
+    double a[P];
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
+    for (int k = 0; k < P; ++k)
         a[k] = k < N ? v[k] : 0.0;
     // keep the upper or the lower half of the values by the lane's bit
 #pragma unroll
-    for (int off = 32, n = 4; off >= 8; off >>= 1, n >>= 1) {
+    for (int off = 32, n = P / 2; n >= 1; off >>= 1, n >>= 1) {
         const bool up = (lane & off) != 0;
 #pragma unroll
         for (int k = 0; k < n; ++k) {
@@ -661,10 +663,10 @@ __device__ __forceinline__ void block_sums(const double (&v)[N], double *__restr
         }
     }
 #pragma unroll
-    for (int off = 4; off > 0; off >>= 1)
+    for (int off = W / 2; off > 0; off >>= 1)
         a[0] += __shfl_xor(a[0], off, 64);
-    if ((lane & 7) == 0)
-        sh[wave][lane >> 3] = a[0];
+    if ((lane & (W - 1)) == 0)
+        sh[wave][lane / W] = a[0];
     __syncthreads();
     if (threadIdx.x < N) {
         const int k = (int)threadIdx.x;
