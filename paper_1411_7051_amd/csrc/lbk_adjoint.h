@@ -26,6 +26,15 @@ hipError_t launch_adjoint2(int bcx, int bcy, const float *mu_in, float *mu_out,
                            const MLayout &mlay, float *grad, float *grad2, const Geom &g,
                            const Physics &ph, int band, hipStream_t st);
 
+// What of the model a reverse tile pass is compiled for.  REV_DARCY and
+// REV_FORCH: every model without and with the Forchheimer term; REV_STD:
+// Physics::standard.
+enum { REV_DARCY = 0, REV_FORCH = 1, REV_STD = 2 };
+inline int rev_model(const Physics &ph)
+{
+    return ph.feps != 0.0f ? REV_FORCH : (ph.standard ? REV_STD : REV_DARCY);
+}
+
 // total[y][x] += seg[y][x]; seg[y][x] = 0 ([y][pitch]).
 hipError_t launch_grad_fold(float *seg, double *total, const Geom &g, hipStream_t st);
 

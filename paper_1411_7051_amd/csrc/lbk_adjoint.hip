@@ -38,272 +38,9 @@
 // nontemporally.  With the Forchheimer term on, the quadratic velocity solve
 // of Eq. 2 is differentiated as well (template flag FC; without it the
 // Darcy path alone is compiled).
-#include "lbk_adjoint.h"
-#include "lbk_kernels.h"
+#include "lbk_adjoint_dev.h"
 
 namespace lbk {
-
-namespace {
-
-__device__ __forceinline__ int xcd_remap_a(int b, int nb)
-{
-    const int q = nb >> 3, r = nb & 7;
-    const int j = b & 7, idx = b >> 3;
-    return j * q + (j < r ? j : r) + idx;
-}
-
-// Forward quantities of one node's velocity solve, as in velocity() of the
-// sweep, plus what the adjoint needs: dA/drho through the local Kn and
-// dA/d ln kn0.
-struct NodeFwd {
-    float rho, rinv, jx, jy, eps, ie, A, B, c0, g, ux, uy, un, Fx, Fy, dA_drho, dA_dlnkn;
-    bool solid;
-};
-
-// FC: the Forchheimer term may be on (else it is known to be off, and the
-// Darcy path alone is compiled: fewer registers for the common case).
-template <bool FC>
-__device__ __forceinline__ NodeFwd node_fwd(const Physics &ph, float rho, float jx, float jy,
-                                            float eps, float drag, float kn0)
-{
-    NodeFwd n;
-    n.rho = rho;
-    n.jx = jx;
-    n.jy = jy;
-    n.eps = eps;
-    n.solid = !(eps > 0.0f);
-    // hardware reciprocals, as in the sweep's velocity solve
-    n.ie = n.solid ? 0.0f : __builtin_amdgcn_rcpf(eps);
-    n.rinv = __builtin_amdgcn_rcpf(rho);
-    const float kn = ph.kn_local ? kn0 * (ph.rho_ref * n.rinv) : kn0;
-    float t = 0.0f; // Kn^0.4348 of the second-order correlation, once
-    if (ph.corr == CORR_BKC)
-        t = fc_pow(kn);
-    float num, den; // f_c = den / num, as in the sweep
-    fc_parts_t(ph, kn, t, num, den);
-    const float dn = drag * num;
-    n.A = dn * __builtin_amdgcn_rcpf(den);   // drag / f_c
-    n.c0 = 1.0f + 0.5f * n.A;
-    const float vx = jx * n.rinv + 0.5f * eps * ph.gx;
-    const float vy = jy * n.rinv + 0.5f * eps * ph.gy;
-    n.B = 0.0f;
-    if (!FC || ph.feps == 0.0f) {
-        const float R2 = 2.0f * __builtin_amdgcn_rcpf(2.0f * den + dn);
-        n.g = den * R2; // 1 / (1 + A/2)
-    } else {
-        // Forchheimer (Eq. 2): c0 u + (B/2) |u| u = v, B = eps F_eps / sqrt(k_a),
-        // the positive root as in the forward velocity solve
-        n.B = ph.feps * __builtin_sqrtf(eps * n.A * ph.inv_nu);
-        const float wn = __builtin_sqrtf(vx * vx + vy * vy);
-        n.g = 2.0f / (n.c0 + __builtin_sqrtf(n.c0 * n.c0 + 2.0f * n.B * wn));
-    }
-    n.ux = n.solid ? 0.0f : n.g * vx;
-    n.uy = n.solid ? 0.0f : n.g * vy;
-    n.un = (!FC || ph.feps == 0.0f) ? 0.0f : __builtin_sqrtf(n.ux * n.ux + n.uy * n.uy);
-    n.Fx = n.solid ? -2.0f * jx * n.rinv : eps * ph.gx - n.A * n.ux - n.B * n.un * n.ux;
-    n.Fy = n.solid ? -2.0f * jy * n.rinv : eps * ph.gy - n.A * n.uy - n.B * n.un * n.uy;
-    // Kn ~ kn0: dA/d ln kn0 = -A Kn f_c'(Kn) / f_c; with the local Kn ~ 1/rho
-    // also dA/drho = -(dA/d ln kn0) / rho.  For Eqs. 6-7, f_c = P1 P2 with
-    // P1 = 1 + alpha Kn = p1/a, p1 = a + 1.358 t Kn, and P2 = p2/q,
-    // p2 = 1 + (4 - b) Kn, q = 1 - b Kn: P1' = 1.358 t (t + 1.4348 * 0.170)/a^2
-    // and P2' = 4/q^2, so f_c'/f_c = P1'/P1 + P2'/P2
-    // = 1.358 t (t + 0.243916)/(a p1) + 4/(q p2).  For Eqs. 4-5,
-    // Kn f_c'/f_c = 4 Kn / (1 + 4 Kn).
-    float dAk = 0.0f;
-    if (kn > 0.0f && ph.corr == CORR_BKC) {
-        const float a = t + 0.170f;
-        const float q = 1.0f + ph.slip_nb * kn;
-        const float p1 = a + 1.358f * t * kn, p2 = 1.0f + ph.slip_c * kn;
-        const float l1 = 1.358f * t * (t + 0.243916f) * __builtin_amdgcn_rcpf(a * p1);
-        const float l2 = 4.0f * __builtin_amdgcn_rcpf(q * p2);
-        dAk = -n.A * kn * (l1 + l2);
-    } else if (kn > 0.0f && ph.corr == CORR_KLINKENBERG) {
-        dAk = -n.A * 4.0f * kn * __builtin_amdgcn_rcpf(1.0f + 4.0f * kn);
-    }
-    n.dA_dlnkn = dAk;
-    n.dA_drho = ph.kn_local ? -dAk * n.rinv : 0.0f;
-    return n;
-}
-
-// w-weighted moments of a 9-vector: L0 = sum w l, L1 = sum w l e,
-// L2 = sum w l e e (symmetric; xx, yy, xy), from the sums and differences
-// of opposite directions, each weight class applied once.
-struct Mom {
-    float m0, m1x, m1y, mxx, myy, mxy;
-};
-__device__ __forceinline__ Mom moments(const float (&l)[9])
-{
-    // e_5 = (1, 1), e_6 = (-1, 1), e_7 = (-1, -1), e_8 = (1, -1)
-    const float a13 = l[1] + l[3], d13 = l[1] - l[3];
-    const float a24 = l[2] + l[4], d24 = l[2] - l[4];
-    const float a57 = l[5] + l[7], d57 = l[5] - l[7];
-    const float a68 = l[6] + l[8], d68 = l[6] - l[8];
-    const float sd = a57 + a68;
-    const float w0 = w_of(0), w1 = w_of(1), w2 = w_of(5);
-    Mom m;
-    m.m0 = w0 * l[0] + w1 * (a13 + a24) + w2 * sd;
-    m.m1x = w1 * d13 + w2 * (d57 - d68);
-    m.m1y = w1 * d24 + w2 * (d57 + d68);
-    m.mxx = w1 * a13 + w2 * sd;
-    m.myy = w1 * a24 + w2 * sd;
-    m.mxy = w2 * (a57 - a68);
-    return m;
-}
-
-// out_i = k v_i + c + e_i . (gx, gy) for the nine directions (v = NULL: k
-// v_i left out), the direction-class sums formed once.
-template <bool V>
-__device__ __forceinline__ void spread(float k, const float *v, float c, float gx, float gy,
-                                       float (&out)[9])
-{
-    const float px = c + gx, mx = c - gx;
-    const float t[9] = {c, px, c + gy, mx, c - gy, px + gy, mx + gy, mx - gy, px - gy};
-#pragma unroll
-    for (int i = 0; i < 9; ++i)
-        out[i] = V ? k * v[i] + t[i] : t[i];
-}
-
-// Chain rule from the partials of a node function Psi(rho, u, F) (explicit
-// Psi_rho, vectors Psi_u, Psi_F) to its total derivatives with respect to
-// rho, j and ln k through the node's velocity solve.
-struct Grads {
-    float rho, jx, jy, lnk, lnkn;
-};
-__device__ __forceinline__ Grads chain(const NodeFwd &n, float Pr, float Pux, float Puy,
-                                       float PFx, float PFy)
-{
-    Grads G;
-    if (n.solid) {
-        // u = 0, F = -2 j / rho
-        G.jx = -2.0f * n.rinv * PFx;
-        G.jy = -2.0f * n.rinv * PFy;
-        G.rho = Pr + 2.0f * n.rinv * n.rinv * (PFx * n.jx + PFy * n.jy);
-        G.lnk = 0.0f;
-        G.lnkn = 0.0f;
-        return G;
-    }
-    // The velocity solves M(u) = c0 u + (B/2) |u| u = v, v = j / rho + eps G / 2,
-    // c0 = 1 + A/2, and F = eps G - A u - B |u| u.  With T = dPsi/du through
-    // u and F(u) at fixed A, B, and K = dM/du = a I + (B/2) u u^T / |u|,
-    // a = c0 + B |u| / 2: dPsi/dv = S = K^-1 T, dPsi/dj = S / rho, and
-    // dPsi/dA = -(S.u / 2 + Psi_F.u) = GA, dPsi/dB = |u| GA.  B ~ sqrt(A), so
-    // the B path adds GA |u| B / (2 A) per unit of dA.  Darcy (B = 0): S = T / c0.
-    const float PFu = PFx * n.ux + PFy * n.uy;
-    float Tx = Pux - n.A * PFx, Ty = Puy - n.A * PFy;
-    float Sx, Sy, fac = 1.0f;
-    if (n.B == 0.0f) {
-        Sx = n.g * Tx;
-        Sy = n.g * Ty;
-    } else {
-        const float un = n.un, hb = 0.5f * n.B * un;
-        const float q = un > 0.0f ? PFu * __builtin_amdgcn_rcpf(un) : 0.0f; // u.Psi_F / |u|
-        Tx -= n.B * (un * PFx + q * n.ux);
-        Ty -= n.B * (un * PFy + q * n.uy);
-        const float a = n.c0 + hb;
-        // K^-1 = (I - b/(a + b) u u^T / |u|^2) / a with b = B |u| / 2
-        const float kap =
-            un > 0.0f ? 0.5f * n.B * __builtin_amdgcn_rcpf((a + hb) * un) : 0.0f;
-        const float uT = n.ux * Tx + n.uy * Ty, ia = __builtin_amdgcn_rcpf(a);
-        Sx = ia * (Tx - kap * uT * n.ux);
-        Sy = ia * (Ty - kap * uT * n.uy);
-        fac = n.A > 0.0f ? 1.0f + un * n.B * __builtin_amdgcn_rcpf(2.0f * n.A) : 1.0f;
-    }
-    const float GA = (-0.5f * (Sx * n.ux + Sy * n.uy) - PFu) * fac;
-    G.jx = n.rinv * Sx;
-    G.jy = n.rinv * Sy;
-    G.rho = Pr - (G.jx * n.jx + G.jy * n.jy) * n.rinv + GA * n.dA_drho;
-    G.lnk = -n.A * GA; // dA / d ln k = -A
-    G.lnkn = n.dA_dlnkn * GA;
-    return G;
-}
-
-// Adjoint of the collide at one node: lam_f from mu (the adjoint of the
-// post-collision populations) and the sensitivity to ln k.
-__device__ __forceinline__ Grads collide_adj(const Physics &ph, const NodeFwd &n,
-                                             const float (&mu)[9], float (&lf)[9])
-{
-    const Mom L = moments(mu);
-    const float om = ph.omega, cg = ph.guo, ie = n.ie;
-    const float ux = n.ux, uy = n.uy, Fx = n.Fx, Fy = n.Fy;
-    const float L2ux = L.mxx * ux + L.mxy * uy, L2uy = L.mxy * ux + L.myy * uy;
-    const float L2Fx = L.mxx * Fx + L.mxy * Fy, L2Fy = L.mxy * Fx + L.myy * Fy;
-    const float uu = ux * ux + uy * uy, uF = ux * Fx + uy * Fy;
-    const float L1u = L.m1x * ux + L.m1y * uy, L1F = L.m1x * Fx + L.m1y * Fy;
-    // Psi = rho { omega [L0 + 3 L1.u + 4.5/eps u.L2.u - 1.5/eps |u|^2 L0]
-    //           + g [3 L1.F + 9/eps u.L2.F - 3/eps (u.F) L0] }
-    const float Peq = L.m0 + 3.0f * L1u + 4.5f * ie * (ux * L2ux + uy * L2uy) - 1.5f * ie * uu * L.m0;
-    const float Pf = 3.0f * L1F + 9.0f * ie * (ux * L2Fx + uy * L2Fy) - 3.0f * ie * uF * L.m0;
-    const float Pr = om * Peq + cg * Pf; // Psi / rho
-    const float rho = n.rho;
-    const float Pux = rho * (om * (3.0f * L.m1x + 9.0f * ie * L2ux - 3.0f * ie * L.m0 * ux) +
-                             cg * (9.0f * ie * L2Fx - 3.0f * ie * L.m0 * Fx));
-    const float Puy = rho * (om * (3.0f * L.m1y + 9.0f * ie * L2uy - 3.0f * ie * L.m0 * uy) +
-                             cg * (9.0f * ie * L2Fy - 3.0f * ie * L.m0 * Fy));
-    const float PFx = rho * cg * (3.0f * L.m1x + 9.0f * ie * L2ux - 3.0f * ie * L.m0 * ux);
-    const float PFy = rho * cg * (3.0f * L.m1y + 9.0f * ie * L2uy - 3.0f * ie * L.m0 * uy);
-    const Grads G = chain(n, Pr, Pux, Puy, PFx, PFy);
-    spread<true>(1.0f - om, mu, G.rho, G.jx, G.jy, lf);
-    return G;
-}
-
-// Adjoint of the read-out share of J at one node, J_x = a1 rho u_x + a2 u_x.
-__device__ __forceinline__ Grads readout_adj(const NodeFwd &n, float a1, float a2,
-                                             float (&lf)[9])
-{
-    Grads G{0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    if (!n.solid && (a1 != 0.0f || a2 != 0.0f))
-        G = chain(n, a1 * n.ux, a1 * n.rho + a2, 0.0f, 0.0f, 0.0f);
-    spread<false>(0.0f, nullptr, G.rho, G.jx, G.jy, lf);
-    return G;
-}
-
-// Adjoint of the pressure-column override
-//   f_i(b) = f_eq_i(rho_b, u_n; eps_b) + f_i(n) - f_eq_i(rho_n, u_n; eps_n)
-// with respect to the neighbour's post-stream populations f(n) (through
-// f(n) itself, rho_n, j_n and u_n(rho_n, j_n, ln k_n)).  Adds to lfn and
-// returns the neighbour's ln k and ln kn0 sensitivities.
-__device__ __forceinline__ float2 nee_adj(const NodeFwd &n, float rho_b, float eps_b,
-                                         const float (&lb)[9], float (&lfn)[9])
-{
-    const Mom M = moments(lb);
-    const float ux = n.ux, uy = n.uy;
-    const float M2ux = M.mxx * ux + M.mxy * uy, M2uy = M.mxy * ux + M.myy * uy;
-    const float uu = ux * ux + uy * uy;
-    // Phi(rho, eps) = sum_i lb_i f_eq_i = rho [M0 + 3 M1.u + 4.5/eps u.M2.u
-    //                 - 1.5/eps |u|^2 M0]; for eps = 0 it is rho M0.
-    const bool sb = !(eps_b > 0.0f);
-    const float ieb = sb ? 0.0f : __builtin_amdgcn_rcpf(eps_b), ien = n.ie;
-    const float dbx = sb ? 0.0f : rho_b * (3.0f * M.m1x + 9.0f * ieb * M2ux - 3.0f * ieb * M.m0 * ux);
-    const float dby = sb ? 0.0f : rho_b * (3.0f * M.m1y + 9.0f * ieb * M2uy - 3.0f * ieb * M.m0 * uy);
-    const float dnx = n.solid ? 0.0f : n.rho * (3.0f * M.m1x + 9.0f * ien * M2ux - 3.0f * ien * M.m0 * ux);
-    const float dny = n.solid ? 0.0f : n.rho * (3.0f * M.m1y + 9.0f * ien * M2uy - 3.0f * ien * M.m0 * uy);
-    const float phin_over_rho =
-        n.solid ? M.m0
-                : M.m0 + 3.0f * (M.m1x * ux + M.m1y * uy) + 4.5f * ien * (ux * M2ux + uy * M2uy) -
-                      1.5f * ien * uu * M.m0;
-    // Psi = Phi_b(u) - Phi_n(rho_n, u): explicit d/drho_n = -Phi_n / rho_n,
-    // d/du = Hu; no direct force dependence.
-    const Grads G = chain(n, -phin_over_rho, dbx - dnx, dby - dny, 0.0f, 0.0f);
-    float gx = G.jx, gy = G.jy, gr = G.rho, gl = G.lnk, gk = G.lnkn;
-    if (n.solid) { // u_n = 0 does not move with f(n)
-        gx = gy = gl = gk = 0.0f;
-        gr = -phin_over_rho;
-    }
-    float add[9];
-    spread<true>(1.0f, lb, gr, gx, gy, add);
-#pragma unroll
-    for (int i = 0; i < 9; ++i)
-        lfn[i] += add[i];
-    return make_float2(gl, gk);
-}
-
-__device__ __forceinline__ Rsrc rsrc_row(const void *base, uint64_t row_bytes, int y)
-{
-    return make_rsrc(static_cast<const char *>(base) + (uint64_t)y * row_bytes,
-                     (uint32_t)row_bytes);
-}
-
-} // namespace
 
 // One reverse step (or, with terminal != 0, the read-out of J).
 //   mu_in  [y][9][pitch]  adjoint of S_n (ignored when terminal)
@@ -338,13 +75,13 @@ __device__ __forceinline__ void adjoint_node(const float *mu_in, float *mu_out, 
     auto node_adj = [&](const NodeFwd &n, uint32_t xx, float (&lf)[9]) {
         if (terminal) {
             const float a = (!outlet || xx == nx - 1) ? a1 : 0.0f;
-            return readout_adj(n, a, a2, lf);
+            return readout_adj<FC>(ph, n, a, a2, lf);
         }
         float mu[9];
 #pragma unroll
         for (int i = 0; i < 9; ++i)
             mu[i] = ld_f32_nt(lin, xx * 4, i * slot);
-        return collide_adj(ph, n, mu, lf);
+        return collide_adj<FC>(ph, n, mu, lf);
     };
     // each gradient entry has exactly one writer per launch
     auto add_grad = [&](uint32_t xx, float v, float vk) {
@@ -391,7 +128,7 @@ __device__ __forceinline__ void adjoint_node(const float *mu_in, float *mu_out, 
                 float lb[9];
                 const Grads Gb = node_adj(b, xb, lb);
                 add_grad(xb, Gb.lnk, Gb.lnkn);
-                const float2 gn = nee_adj(n, b.rho, b.eps, lb, lf);
+                const float2 gn = nee_adj<FC>(ph, n, b.rho, b.ie, lb, lf);
                 gl += gn.x;
                 gk += gn.y;
             }
@@ -401,7 +138,7 @@ __device__ __forceinline__ void adjoint_node(const float *mu_in, float *mu_out, 
                 float lb[9];
                 const Grads Gb = node_adj(b, 2, lb);
                 add_grad(2, Gb.lnk, Gb.lnkn);
-                const float2 gn = nee_adj(n, b.rho, b.eps, lb, lf);
+                const float2 gn = nee_adj<FC>(ph, n, b.rho, b.ie, lb, lf);
                 gl += gn.x;
                 gk += gn.y;
             }
@@ -491,16 +228,6 @@ __global__ __launch_bounds__(256) void adjoint_kernel(const float *mu_in, float 
 // gradient entry collects both steps' terms before it is written once.
 namespace {
 
-// Lane-dependent facts of a strip of the reverse pass.
-struct ALanes {
-    uint32_t x;         // the lane's column, wrapped (periodic) or clamped
-    bool wxm, wxp;      // wall x: the column is the first / last
-    bool first, last;   // pressure x: the inlet / outlet column
-    bool cl, cr;        // pressure x: the column next to the inlet / outlet
-    bool has_b;         // uniform: the wave may hold any of these
-    bool bgrad;         // pressure columns receive gradient terms (nx >= 3)
-};
-
 // A row's inputs at this lane's column, in two parts loaded at different
 // times: what the reverse of step n needs (mu_n, the history of step n and
 // the medium) and what the reverse of step n - 1 adds (the history of step
@@ -518,90 +245,6 @@ struct RowB {
 struct AMid {
     float lf[9], gl, gk;
 };
-
-// lam_f and the ln k / ln kn0 terms of one reverse step at this lane's node
-// (adjoint_node's arithmetic, with a pressure column's contribution taken
-// from the neighbouring lane rather than recomputed).
-template <int BCX, bool FC>
-__device__ __forceinline__ void local_adj(const Physics &ph, const float (&mu)[9], const float (&h)[3],
-                                          const float (&md)[3], const ALanes &ln,
-                                          float (&lf)[9], float &gl, float &gk)
-{
-    const NodeFwd n = node_fwd<FC>(ph, h[0], h[1], h[2], md[0], md[1], md[2]);
-    const Grads G = collide_adj(ph, n, mu, lf);
-    gl = G.lnk;
-    gk = G.lnkn;
-    if (BCX != BC_PRESSURE)
-        return;
-    if (ln.has_b) {
-        // the pressure columns' lam_f as computed so far (never changed by
-        // the carries below, which only touch the columns next to them)
-        float lb[9];
-#pragma unroll
-        for (int i = 0; i < 9; ++i)
-            lb[i] = lane_from<1>(lf[i]);
-        float rb = lane_from<1>(n.rho), eb = lane_from<1>(n.eps);
-        if (ln.cl) {
-            const float2 q = nee_adj(n, rb, eb, lb, lf);
-            gl += q.x;
-            gk += q.y;
-        }
-#pragma unroll
-        for (int i = 0; i < 9; ++i)
-            lb[i] = lane_from<-1>(lf[i]);
-        rb = lane_from<-1>(n.rho);
-        eb = lane_from<-1>(n.eps);
-        if (ln.cr) {
-            const float2 q = nee_adj(n, rb, eb, lb, lf);
-            gl += q.x;
-            gk += q.y;
-        }
-    }
-    if (ln.first || ln.last) {
-        // forward values pulled into a pressure column are discarded
-#pragma unroll
-        for (int i = 0; i < 9; ++i)
-            lf[i] = 0.0f;
-        if (!ln.bgrad)
-            gl = gk = 0.0f;
-    }
-}
-
-// mu of this lane's node from lam_f of rows y - 1 (dn), y (c), y + 1 (up).
-// wym / wyp: the row below / above lies beyond a wall.
-template <int BCX>
-__device__ __forceinline__ void gather(const float (&dn)[9], const float (&c)[9],
-                                       const float (&up)[9], bool wym, bool wyp,
-                                       const ALanes &ln, float (&mu)[9])
-{
-    mu[0] = c[0];
-#pragma unroll
-    for (int j = 1; j < 9; ++j) {
-        const int ex = ex_of(j), ey = ey_of(j);
-        const bool wall_y = (ey == 1 && wyp) || (ey == -1 && wym); // uniform
-        const float(&r)[9] = ey == 1 ? up : (ey == -1 ? dn : c);
-        float v;
-        if (wall_y)
-            v = c[opp_of(j)];
-        else if (ex == 1)
-            v = lane_from<-1>(r[j]);
-        else if (ex == -1)
-            v = lane_from<1>(r[j]);
-        else
-            v = r[j];
-        if (BCX == BC_WALL) {
-            const bool out_x = (ex == 1 && ln.wxp) || (ex == -1 && ln.wxm);
-            if (out_x)
-                v = c[opp_of(j)];
-        }
-        if (BCX == BC_PRESSURE) {
-            const bool out_x = (ex == 1 && ln.last) || (ex == -1 && ln.first);
-            if (out_x)
-                v = 0.0f;
-        }
-        mu[j] = v;
-    }
-}
 
 } // namespace
 
