@@ -35,6 +35,15 @@ inline int rev_model(const Physics &ph)
     return ph.feps != 0.0f ? REV_FORCH : (ph.standard ? REV_STD : REV_DARCY);
 }
 
+// `steps` reverse steps in one launch, bitwise as many launch_adjoint calls
+// (terminal = 0): mu_in = mu_n -> mu_out = mu_{n-steps} (different arrays);
+// hist is the history of step n, the steps before it hist_bytes lower each.
+// Tiles as in launch_tile (t.rows 1 or 2; 1 with REV_FORCH).
+hipError_t launch_adjoint_tile(int bcx, int bcy, const float *mu_in, float *mu_out,
+                               const float *hist, uint64_t hist_bytes, const char *med,
+                               const MLayout &mlay, float *grad, float *grad2, const Geom &g,
+                               const Physics &ph, const Tile &t, int steps, hipStream_t st);
+
 // total[y][x] += seg[y][x]; seg[y][x] = 0 ([y][pitch]).
 hipError_t launch_grad_fold(float *seg, double *total, const Geom &g, hipStream_t st);
 

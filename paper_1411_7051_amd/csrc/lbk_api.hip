@@ -911,6 +911,29 @@ extern "C" lbk_status lbk_adjoint_forward(lbk_lattice *lat, int objective, int64
     return LBK_OK;
 }
 
+// The tile of a reverse pass (launch_adjoint_tile) of `steps` steps at most:
+// while every tile has a CU of its own a pass costs its launch and its chain
+// of steps, so the most steps whose tiles number at most the device's 256 CUs
+// (16 waves of one row, then of two); on larger lattices the bytes of the tiles
+// count, and two workgroups a CU, one loading while the other computes.  us a step:
+//   384 x 256    2.9 (16, 1, 4)  3.3 (8, 2, 4)   3.3 (16, 1, 3)
+//   333 x 100    2.4 (16, 1, 6)  2.6 (16, 1, 5)  2.9 (16, 1, 4)
+//   1024 x 512   8.5 (16, 2, 5)  8.9 (8, 2, 3)   10.1 (16, 1, 3)
+//   2048 x 512   14.5 (8, 2, 3)  15.3 (16, 2, 5) 17 (12, 1, 3)
+//   2048 x 2048  49.3 (8, 2, 3)  51.2 (16, 2, 5) 57.5 (12, 1, 3)
+static TilePlan rev_tile_plan(const lbk_lattice *lat)
+{
+    const bool one_row = rev_model(lat->ph) == REV_FORCH;
+    const TilePlan plans[] = {{{16, 1}, 6}, {{16, 1}, 4}, {{16, 2}, 5}};
+    for (const TilePlan &p : plans) {
+        const int64_t own_x = 64 - 2 * p.steps, own_y = p.tile.waves * p.tile.rows - 2 * p.steps;
+        const int64_t tiles = ((lat->d.nx + own_x - 1) / own_x) * ((lat->d.ny + own_y - 1) / own_y);
+        if (tiles <= 256 && !(one_row && p.tile.rows > 1))
+            return p;
+    }
+    return one_row ? TilePlan{{12, 1}, 3} : TilePlan{{8, 2}, 3};
+}
+
 extern "C" lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws_bytes,
                                            float *dJ_dlnk, float *dJ_dlnkn0)
 {
@@ -937,8 +960,9 @@ extern "C" lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws
     float *seg2 = kn ? reinterpret_cast<float *>(w + P.seg2) : nullptr;
     char *rec[2] = {level(P.rec, 0), level(P.rec, 1)};
     // rebuilt inner checkpoints (no history) and recorded segments take
-    // lbk_step's passes, the reverse steps pairs
-    const bool two = two_step_pass(lat);
+    // lbk_step's passes, the reverse steps tile passes or pairs likewise
+    const bool tile = tile_pass(lat), two = two_step_pass(lat);
+    const TilePlan rev = rev_tile_plan(lat);
     const float a1 = (float)P.a1, a2 = (float)P.a2;
 
     HIP_TRY(hipMemsetAsync(grad, 0, (size_t)d.ny * lat->L.pitch * 8, st));
@@ -1005,7 +1029,14 @@ extern "C" lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws
             }
             Range range("adjoint reverse");
             for (int64_t t = b2s; t > a2s;) {
-                if (two && t - 1 > a2s) {
+                if (tile && t - 1 > a2s) {
+                    const int n = (int)std::min<int64_t>(rev.steps, t - a2s);
+                    HIP_TRY(launch_adjoint_tile(d.bc_x, d.bc_y, lam[cur], lam[cur ^ 1],
+                                                histp(t - a2s), P.hist_bytes, lat->med(),
+                                                lat->L.mlay, seg, seg2, lat->g, lat->ph, rev.tile,
+                                                n, st));
+                    t -= n;
+                } else if (two && t - 1 > a2s) {
                     HIP_TRY(launch_adjoint2(d.bc_x, d.bc_y, lam[cur], lam[cur ^ 1],
                                             histp(t - a2s), histp(t - 1 - a2s), lat->med(),
                                             lat->L.mlay, seg, seg2, lat->g, lat->ph,
