@@ -858,6 +858,23 @@ extern "C" lbk_status lbk_adjoint_plan(const lbk_lattice *lat, int64_t n_steps,
     return LBK_OK;
 }
 
+// n >= 1 steps from src to dst (nullptr: to one of the levels lv) by way of the
+// levels lv, one of which src may be; src becomes where the state is then.
+static hipError_t lead(const lbk_lattice *lat, char *&src, int64_t n, char *const (&lv)[2],
+                       char *dst, hipStream_t st)
+{
+    while (n > 0) {
+        const Pass p = next_pass(lat, n);
+        char *to = dst && p.steps == n ? dst : lv[src == lv[0] ? 1 : 0];
+        const hipError_t e = launch_pass(lat, p, src, to, nullptr, 0, st);
+        if (e != hipSuccess)
+            return e;
+        src = to;
+        n -= p.steps;
+    }
+    return hipSuccess;
+}
+
 extern "C" lbk_status lbk_adjoint_forward(lbk_lattice *lat, int objective, int64_t n_steps,
                                           int64_t ckpt_every, int64_t hist_len, void *ws,
                                           size_t ws_bytes, double *J)
@@ -882,25 +899,30 @@ extern "C" lbk_status lbk_adjoint_forward(lbk_lattice *lat, int objective, int64
     char *w = static_cast<char *>(ws);
     hipStream_t st = lat->stream;
     P.t0 = lat->t;
-    for (int64_t k = 0; k < P.k1; ++k) {
-        HIP_TRY(hipMemcpyAsync(w + P.outer + (size_t)k * P.level_bytes, lat->state(lat->cur),
-                               P.level_bytes, hipMemcpyDeviceToDevice, st));
-        const int64_t steps = std::min(P.c1, P.n - k * P.c1);
-        // the last `keep` segments are reversed first: keep their inner
-        // checkpoints now rather than recomputing them in the backward pass
-        const int64_t kept = k - (P.k1 - P.keep);
-        const bool keep_inner = P.two_level && kept >= 0;
-        const int64_t run = keep_inner ? P.c2 : steps; // steps between kept states
-        for (int64_t i = 0; i < steps; i += run) {
-            if (keep_inner)
-                HIP_TRY(hipMemcpyAsync(w + P.inner + (size_t)kept * P.inner_seg +
-                                           (size_t)(i / P.c2) * P.level_bytes,
-                                       lat->state(lat->cur), P.level_bytes,
-                                       hipMemcpyDeviceToDevice, st));
-            if ((s = advance(lat, std::min(run, steps - i), st)) != LBK_OK)
-                return s;
-        }
+    // Segment by segment from checkpoint to checkpoint: the last pass before a
+    // checkpoint writes it, the first one after it reads it, so only the first
+    // is a copy (67 us a checkpoint of 2048 x 2048).  The last `keep` segments
+    // are reversed first: their inner checkpoints are kept now rather than
+    // recomputed in the backward pass.
+    char *lv[2] = {lat->state(0), lat->state(1)};
+    char *src = w + P.outer;
+    HIP_TRY(hipMemcpyAsync(src, lat->state(lat->cur), P.level_bytes, hipMemcpyDeviceToDevice, st));
+    for (int64_t t = 0; t < P.n;) {
+        const int64_t k = t / P.c1, kept = k - (P.k1 - P.keep);
+        const int64_t run = P.two_level && kept >= 0 ? P.c2 : P.c1;
+        const int64_t end = std::min(std::min(P.n, (k + 1) * P.c1), t + run);
+        char *dst = nullptr;
+        if (end < P.n && end == (k + 1) * P.c1)
+            dst = w + P.outer + (size_t)(k + 1) * P.level_bytes;
+        else if (end < P.n)
+            dst = w + P.inner + (size_t)kept * P.inner_seg +
+                  (size_t)((end - k * P.c1) / P.c2) * P.level_bytes;
+        HIP_TRY(lead(lat, src, end - t, lv, dst, st));
+        t = end;
     }
+    lat->cur = src == lv[1];
+    lat->t += P.n;
+    ++lat->version;
     if ((s = macro_sums(lat, false, false)) != LBK_OK)
         return s;
     P.objective = objective;
@@ -988,32 +1010,18 @@ extern "C" lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws
         if (P.two_level && kept >= 0) {
             nseg = (b - a + P.c2 - 1) / P.c2;
         } else if (P.two_level) {
-            // rebuild the inner checkpoints of this outer segment
+            // rebuild the inner checkpoints of this outer segment (the first
+            // is the outer one; the last inner segment needs no further state)
             Range range("adjoint rebuild");
-            const char *src = level(P.outer, k);
-            int r = 0;
-            nseg = 0;
-            for (int64_t t = a; t < b; t += P.c2, ++nseg) {
-                HIP_TRY(hipMemcpyAsync(level(inner, nseg), src, P.level_bytes,
-                                       hipMemcpyDeviceToDevice, st));
-                const int64_t steps = std::min(P.c2, b - t);
-                if (t + steps >= b)
-                    break; // the last inner segment needs no further state
-                for (int64_t i = 0; i < steps;) {
-                    const char *from = i == 0 ? level(inner, nseg) : rec[r];
-                    const Pass p = next_pass(lat, steps - i);
-                    HIP_TRY(launch_pass(lat, p, from, rec[r ^ 1], nullptr, 0, st));
-                    i += p.steps;
-                    r ^= 1;
-                }
-                src = rec[r];
-            }
-            ++nseg;
+            char *src = level(P.outer, k);
+            nseg = (b - a + P.c2 - 1) / P.c2;
+            for (int64_t j = 1; j < nseg; ++j)
+                HIP_TRY(lead(lat, src, P.c2, rec, level(inner, j), st));
         }
         for (int64_t j = nseg - 1; j >= 0; --j) {
             const int64_t a2s = P.two_level ? a + j * P.c2 : a;
             const int64_t b2s = P.two_level ? std::min(b, a2s + P.c2) : b;
-            const char *src = P.two_level ? level(inner, j) : level(P.outer, k);
+            const char *src = j > 0 ? level(inner, j) : level(P.outer, k);
             // recompute the segment, recording each step's linearisation point
             int r = 0;
             {
