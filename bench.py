@@ -1,7 +1,7 @@
 """Benchmark of the Klinkenberg lattice Boltzmann hot path on one MI355X.
 
 One "step" is one fused D2Q9 stream + Klinkenberg + velocity + BGK/Guo
-collide sweep over the whole lattice (one kernel launch).  The workload is
+collide sweep over the whole lattice (a kernel launch takes several).  The workload is
 the two-component heterogeneous medium of Sec. IV.B scaled up: 4096 x 4096
 nodes, 64 seeded overlapping discs (radius 40-200 nodes, eps 0.2,
 k 1e-4) in a matrix (eps 0.5, k 1e-2), local Kn with base 0.05 in the
@@ -110,7 +110,7 @@ def time_storage(case, storage, steps, warmup, device, single=0):
 
     lat = Lattice(case.eps, case.k, case.kn0, device=device, storage=storage,
                   **case.params)
-    per_launch = lat.steps_per_launch
+    per_launch = lat.tile_steps or lat.steps_per_launch
     lat.step(warmup)
     torch.cuda.synchronize(device)
     # clock spin-up: untimed steps for SPINUP_S seconds, so that the timed
@@ -341,8 +341,7 @@ def time_adjoint(n, steps, ckpt, hist, device):
     case = inputs.shale(n=n, seed=3)
     log(f"shale inputs: {case.nodes} nodes in {time.perf_counter() - t:.1f} s")
     torch.cuda.reset_peak_memory_stats(device)
-    # the forward in two-step passes (the passes the gradient's reverse steps
-    # take), timed on 2000 steps and scaled
+    # the forward in two-step passes, timed on 2000 steps and scaled
     lat2 = Lattice(case.eps, case.k, case.kn0, device=device, pass_mode="two_step",
                    **case.params)
     lat2.step(20)
@@ -392,13 +391,12 @@ def time_adjoint(n, steps, ckpt, hist, device):
         "workspace_GB": ws.numel() / 1e9,
         "peak_device_mem_GB": torch.cuda.max_memory_allocated(device) / 1e9,
         "t_fwd_ms": t_fwd,
-        "fwd_steps_per_launch": lat.steps_per_launch,
+        "fwd_steps_per_launch": lat.tile_steps or lat.steps_per_launch,
         "t_fwd_ckpt_ms": t_af,
         "t_grad_ms": t_bwd,
         "grad_over_fwd": t_bwd / t_fwd,
         "total_over_fwd": (t_af + t_bwd) / t_fwd,
-        # against a forward in two-step passes (the passes the gradient's
-        # reverse steps take), from 2000 steps scaled
+        # against a forward in two-step passes, from 2000 steps scaled
         "t_fwd_two_step_ms": t_fwd2,
         "grad_over_fwd_two_step": t_bwd / t_fwd2,
         "total_over_fwd_two_step": (t_af + t_bwd) / t_fwd2,
@@ -441,6 +439,7 @@ def time_ensemble(n_samples, steps, storages, graph_steps, device, launch=None, 
             tile_x, rows, grid = launch
         b.set_launch(tile_x, rows, grid, graph_steps)
         b.step(2 * graph_steps)  # records the graphs
+        per_launch = b.tile_steps or b.steps_per_launch
         torch.cuda.synchronize(device)
         ev = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
         times = []
@@ -464,17 +463,17 @@ def time_ensemble(n_samples, steps, storages, graph_steps, device, launch=None, 
         mlups = nodes * steps / (ms * 1e-3) / 1e6
         runs[storage] = {
             "launch": {"tile_x": tile_x, "rows": rows, "grid": grid, "graph_steps": graph_steps,
-                       "steps_per_launch": b.steps_per_launch},
+                       "steps_per_launch": per_launch},
             "autotune_best_us": tune_us, "ms_per_step": ms / steps,
             "ms_per_step_min": sp["min"] / steps, "ms_per_step_max": sp["max"] / steps,
             "reps": REPS, "check_every": check_every, "mlups": mlups,
             # one-read-one-write bytes per node-step at this rate (what a
             # one-step-per-launch sweep would move), and per launch of the
-            # pass in use (a two-step pass moves ALG_BYTES for two steps)
+            # pass in use (a multi-step pass moves ALG_BYTES for all its steps)
             "alg_GBps": mlups * ALG_BYTES[storage] / 1e3,
             "alg_frac": mlups * ALG_BYTES[storage] / 1e3 / HBM_PEAK_GBS,
-            "pass_alg_GBps": mlups * ALG_BYTES[storage] / 1e3 / b.steps_per_launch,
-            "pass_alg_frac": mlups * ALG_BYTES[storage] / 1e3 / b.steps_per_launch / HBM_PEAK_GBS}
+            "pass_alg_GBps": mlups * ALG_BYTES[storage] / 1e3 / per_launch,
+            "pass_alg_frac": mlups * ALG_BYTES[storage] / 1e3 / per_launch / HBM_PEAK_GBS}
         if si == 0:
             loop_steps = max(2, steps // 10)
             ev[2].record(st)
@@ -708,9 +707,8 @@ def main():
     acc_small = storage_accuracy(small, args.storages.split(","), 2000, dev)
     head = runs.get("f32") or next(iter(runs.values()))
     st = head["storage"]
-    # dominant kernel: the multi-step pass (one launch per three or two
-    # steps) where the library's automatic pass mode takes it, else one
-    # sweep a step; its launch time from whole passes alone
+    # dominant kernel: the automatic pass mode's tile pass (one launch per
+    # several steps); its launch time from whole passes alone
     per_launch = head["steps_per_launch"]
     launch_ms = head.get("launch_ms", per_launch * head["ms_per_step"])
     achieved = case.nodes * ALG_BYTES[st] / (launch_ms * 1e-3) / 1e9
@@ -723,10 +721,7 @@ def main():
         "frac": achieved / HBM_PEAK_GBS,
         "traffic": traffic,
         "traffic_bytes_per_launch": traffic_bytes,
-        "kernel": {3: f"sweep3x_kernel<{st}> (three steps per launch",
-                   2: f"sweep2_kernel<{st}> (two steps per launch"}.get(
-                       per_launch, f"sweep_kernel<{st}> (one step per launch") +
-                  "; pressure x, periodic y)",
+        "kernel": f"tile_kernel<{st}> ({per_launch} steps per launch; pressure x, periodic y)",
         "bytes_per_node_per_launch": ALG_BYTES[st],
         "steps_per_launch": per_launch,
         "launch_ms": launch_ms,

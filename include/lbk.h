@@ -72,9 +72,12 @@ typedef enum lbk_correlation {
  * or one step per sweep.  A multi-step pass reads and writes the state
  * once per pass; it pays off on lattices large enough to fill the device. */
 typedef enum lbk_pass_mode {
-    LBK_PASS_AUTO = 0,     /* three-step passes from 2^22 nodes (FP32), 2^23
-                              (FP16/BF16); two-step passes from 2^20 (FP32),
-                              2^22 (FP16/BF16); single sweeps below */
+    LBK_PASS_AUTO = 0,     /* tile passes, several steps per launch at every
+                              size (lbk_tile_steps), forward and reverse;
+                              with a band set, marching passes: three-step
+                              from 2^22 nodes (FP32), 2^23 (FP16/BF16),
+                              two-step from 2^20 (FP32), 2^22 (FP16/BF16),
+                              single sweeps below */
     LBK_PASS_TWO_STEP = 1, /* two-step passes whatever the size */
     LBK_PASS_SINGLE = 2,   /* single sweeps */
     LBK_PASS_THREE_STEP = 3 /* lbk_step: three-step passes whatever the size (a
@@ -115,7 +118,8 @@ typedef struct lbk_desc {
                             storage: two-step passes 8 rows at FP32, 10 at
                             FP16/BF16, three-step passes 12 and 24, 16 in
                             reverse, halved down to 2 while a pass
-                            would have fewer than 8192 waves.  Any band
+                            would have fewer than 8192 waves; a band asks
+                            the automatic mode for marching passes.  Any band
                             gives the same result bitwise.  A batch ignores
                             it (its passes take the default bands) */
 } lbk_desc;
@@ -146,19 +150,25 @@ lbk_status lbk_create(const lbk_desc *d, const float *eps, const float *k,
 /* Release the handle (not the workspace).  NULL is accepted. */
 lbk_status lbk_destroy(lbk_lattice *lat);
 
-/* Advance n >= 0 time steps of Eq. 12: one fused sweep launch per step,
- * or per two steps in two-step passes (lbk_steps_per_launch), an odd count
- * ending in one single sweep. */
+/* Advance n >= 0 time steps of Eq. 12: in the automatic mode as few tile
+ * passes as lbk_tile_steps allows, of as equal a length as n permits; else one
+ * fused sweep launch per step, or per two or three steps in multi-step passes
+ * (lbk_steps_per_launch), what remains of n in a shorter pass. */
 lbk_status lbk_step(lbk_lattice *lat, int64_t n);
 
 /* Number of steps taken since create (or since the loaded state). */
 lbk_status lbk_time(const lbk_lattice *lat, int64_t *t);
 
-/* Steps each launch of lbk_step advances, 1, 2 or 3, as the descriptor's
- * pass_mode and the lattice's size and storage decide (a gradient's
- * recording passes follow the same choice, its reverse steps take two where
- * lbk_step takes three). */
+/* Steps per launch of the marching passes or single sweeps, 1, 2 or 3, that
+ * the descriptor's pass_mode and the lattice's size and storage decide (a
+ * gradient's recording passes follow the same choice, its reverse steps take
+ * two where lbk_step takes three).  Where lbk_tile_steps is not 0 the launches
+ * are tile passes and advance that many instead. */
 lbk_status lbk_steps_per_launch(const lbk_lattice *lat, int32_t *steps);
+
+/* Steps of a whole tile pass where lbk_step takes tile passes (pass_mode
+ * LBK_PASS_AUTO without a band), 0 where it does not. */
+lbk_status lbk_tile_steps(const lbk_lattice *lat, int32_t *steps);
 
 /* Macroscopic read-out at the current time (Eqs. 16-17 on the post-stream
  * populations, after the boundary override): density and velocity as
@@ -285,8 +295,8 @@ lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws_bytes, flo
  *
  * A batch groups n lattices of uneven size (independent heterogeneous
  * samples, each with its own fields, tau, drive and Kn scale) so that one
- * kernel launch advances every sample by one step (or two, see
- * lbk_batch_set_pass_mode).  The launch walks a list
+ * kernel launch advances every sample by one step (or several, see
+ * lbk_batch_set_pass_mode).  The launch of a single step walks a list
  * of tiles -- tile_x consecutive x by `rows` consecutive y of one sample --
  * that covers all samples; either one workgroup per tile or a persistent
  * grid of `grid` workgroups each taking a contiguous run of tiles.  Steps
@@ -336,14 +346,15 @@ lbk_status lbk_batch_get_launch(const lbk_batch *b, int32_t *tile_x, int32_t *ro
  * four 60-column strips by a band of rows of each sample (tile_x, rows and
  * grid apply to single steps only, such as the last of an odd count);
  * LBK_PASS_SINGLE: one step per launch; LBK_PASS_AUTO (the default):
- * two-step passes for batches of 2^22 nodes and more, until
- * lbk_batch_autotune has timed both and keeps the faster.  Either way each
+ * tile passes (lbk_batch_tile_steps) until lbk_batch_autotune has timed
+ * them against the others and keeps the fastest.  Either way each
  * sample ends bitwise where single steps take it.  Drops recorded graphs
  * when the choice changes.  Batches have no three-step pass:
  * LBK_PASS_THREE_STEP is rejected (LBK_ERR_INVALID_ARG). */
 lbk_status lbk_batch_set_pass_mode(lbk_batch *b, int32_t pass_mode);
-/* The pass mode set, and the steps per launch in use (1 or 2); either
- * pointer may be NULL. */
+/* The pass mode set, and the steps per launch (1 or 2) where no tile passes
+ * are in use, as the mode, the tuner or the batch's size decide (two-step
+ * passes for 2^22 nodes and more); either pointer may be NULL. */
 lbk_status lbk_batch_get_pass_mode(const lbk_batch *b, int32_t *pass_mode,
                                    int32_t *steps_per_launch);
 
@@ -362,7 +373,7 @@ lbk_status lbk_batch_set_graph_readout(lbk_batch *b, int32_t on);
  * x one workgroup per tile or persistent grids of 2, 4 and 8 workgroups
  * per compute unit -- over `reps` >= 1 steps each, and keep the fastest
  * (graph_steps unchanged); with pass_mode LBK_PASS_AUTO also the two-step
- * pass (reps passes), kept when its time per step is lower.
+ * and the tile pass (reps passes), kept when the time per step is lower.
  * The samples' states are left untouched: the timed launches re-read the
  * current time level and overwrite only the other one.  best_us (may be
  * NULL) receives the fastest mean time per step in microseconds.

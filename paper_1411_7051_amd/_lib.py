@@ -82,6 +82,7 @@ _SIG = {
     "lbk_step": (ctypes.c_int, [_P, ctypes.c_int64]),
     "lbk_time": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_int64)]),
     "lbk_steps_per_launch": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_int32)]),
+    "lbk_tile_steps": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_int32)]),
     "lbk_read_macroscopic": (ctypes.c_int, [_P, _P, _P, _P]),
     "lbk_read_populations": (ctypes.c_int, [_P, _P]),
     "lbk_apparent_permeability": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_double)]),

@@ -71,17 +71,25 @@ class Batch:
                                                int(graph_steps)))
 
     def set_pass_mode(self, mode: str = "auto") -> None:
-        """Steps per launch: "two_step", "single" or "auto" (two-step passes
-        for batches of 2^22 nodes and more until ``autotune`` keeps the
-        faster); every choice gives the same states bit for bit."""
+        """Steps per launch: "two_step", "single" or "auto" (tile passes until
+        ``autotune`` keeps the fastest); every choice gives the same states bit
+        for bit."""
         check(_lib.load().lbk_batch_set_pass_mode(self._handle(), _lib.PASS_MODE[mode]))
 
     @property
     def steps_per_launch(self) -> int:
-        """1 or 2: whether steps currently go through the two-step pass."""
+        """1 or 2: whether steps that take no tile passes (``tile_steps``) go
+        through the two-step pass."""
         m, k = ctypes.c_int32(), ctypes.c_int32()
         check(_lib.load().lbk_batch_get_pass_mode(self._handle(), ctypes.byref(m),
                                                   ctypes.byref(k)))
+        return int(k.value)
+
+    @property
+    def tile_steps(self) -> int:
+        """Steps of a whole tile pass, 0 where the batch takes none."""
+        k = ctypes.c_int32()
+        check(_lib.load().lbk_batch_tile_steps(self._handle(), ctypes.byref(k)))
         return int(k.value)
 
     def set_graph_readout(self, on: bool = True) -> None:
@@ -126,9 +134,7 @@ class Batch:
         check(_lib.load().lbk_batch_autotune(self._handle(), int(reps), ctypes.byref(us)))
         if cache:
             tile_x, rows, grid, _ = self.launch
-            k = ctypes.c_int32()
-            check(_lib.load().lbk_batch_tile_steps(self._handle(), ctypes.byref(k)))
-            per_launch = 0 if k.value else self.steps_per_launch
+            per_launch = 0 if self.tile_steps else self.steps_per_launch
             table[sig] = [tile_x, rows, grid, per_launch, float(us.value)]
             tmp = cache + ".tmp"
             with open(tmp, "w") as f:

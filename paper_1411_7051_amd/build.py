@@ -9,10 +9,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbk.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
-SOURCES = ["lbk_kernels.hip", "lbk_tile.hip", "lbk_tile_batch.hip", "lbk_adjoint.hip", "lbk_adjoint_tile.hip",
-           "lbk_api.hip", "lbk_batch.hip",
+SOURCES = ["lbk_kernels.hip", "lbk_tile.hip", "lbk_tile_batch.hip",
+           "lbk_adjoint.hip", "lbk_adjoint_tile.hip", "lbk_api.hip", "lbk_batch.hip",
            "lbk3_kernels.hip", "lbk3_api.hip", "lbk_noalloc.hip"]
-HEADERS = ["lbk_device.h", "lbk_kernels.h", "lbk_sweep.h", "lbk_tile.h", "lbk_adjoint.h", "lbk_adjoint_dev.h", "lbk_host.h", "lbk3_kernels.h"]
+HEADERS = ["lbk_device.h", "lbk_kernels.h", "lbk_sweep.h", "lbk_tile.h",
+           "lbk_adjoint.h", "lbk_adjoint_dev.h", "lbk_host.h", "lbk3_kernels.h"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

@@ -535,6 +535,14 @@ lbk_status lbk_steps_per_launch(const lbk_lattice *lat, int32_t *steps)
     return LBK_OK;
 }
 
+lbk_status lbk_tile_steps(const lbk_lattice *lat, int32_t *steps)
+{
+    if (!lat || !steps)
+        return fail(LBK_ERR_INVALID_ARG, "NULL argument");
+    *steps = tile_pass(lat) ? lat->plan.steps : 0;
+    return LBK_OK;
+}
+
 lbk_status lbk_read_macroscopic(lbk_lattice *lat, float *rho, float *ux, float *uy)
 {
     if (!lat)

@@ -202,7 +202,7 @@ inline int fwd_band3(const lbk_desc &d)
 }
 
 // Lattices from this many nodes on take two-step passes under
-// LBK_PASS_AUTO.  Below it too few waves run to hide the march's latency,
+// LBK_PASS_AUTO with a band set (without one, tile passes).  Below it too few waves run to hide the march's latency,
 // and a level fits the 256 MB on-package cache, so single sweeps are not
 // bound by HBM: FP32 on 1024 x 512, 52 GLUPS with single sweeps, 48-51 with
 // two-step passes; on 1024 x 1024, 61 against 70.  FP16 and BF16, whose
@@ -218,9 +218,9 @@ inline int64_t two_step_nodes(int storage)
 // both passes and settles it per batch.
 constexpr int64_t kTwoStepBatchNodes = (int64_t)1 << 22;
 
-// Whether steps of this lattice go through the two-step pass (and the
-// reverse steps of its gradients through the two-step reverse pass), as
-// pass_mode asks.
+// Whether steps of this lattice, where they take no tile passes, go through
+// the two-step pass (and the reverse steps of its gradients through the
+// two-step reverse pass), as pass_mode asks.
 inline bool two_step_pass(const lbk_lattice *lat)
 {
     const lbk_desc &d = lat->d;
@@ -229,7 +229,7 @@ inline bool two_step_pass(const lbk_lattice *lat)
 }
 
 // Lattices from this many nodes on take three-step passes under
-// LBK_PASS_AUTO.  FP32, against two-step passes: 116.1 against 88.9 GLUPS on
+// LBK_PASS_AUTO with a band set.  FP32, against two-step passes: 116.1 against 88.9 GLUPS on
 // 4096 x 2048, 95.6 against 82.0 on 2048 x 2048, but 81.3 against 93.6 on
 // 2048 x 1024.  FP16: 126.0 against 118.3 on 4096 x 2048, but 104.5 against
 // 110.7 on 2048 x 2048 (bands of 24 rows, shortened there to keep the
@@ -239,8 +239,9 @@ inline int64_t three_step_nodes(int storage)
     return storage == LBK_F32 ? (int64_t)1 << 22 : (int64_t)1 << 23;
 }
 
-// Whether lbk_step advances this lattice three steps per launch (so do its
-// gradients' rebuilding and recording passes; the reverse passes take two).
+// Whether lbk_step, where it takes no tile passes, advances this lattice three
+// steps per launch (so do its gradients' rebuilding and recording passes; the
+// reverse passes take two).
 inline bool three_step_pass(const lbk_lattice *lat)
 {
     const lbk_desc &d = lat->d;

@@ -122,9 +122,17 @@ class Lattice:
     @property
     def steps_per_launch(self) -> int:
         """1 (single sweeps), 2 or 3 (two- or three-step passes), as
-        pass_mode and the lattice's size and storage decide."""
+        pass_mode and the lattice's size and storage decide where no tile
+        passes are taken (``tile_steps``)."""
         n = ctypes.c_int32()
         check(_lib.load().lbk_steps_per_launch(self._handle(), ctypes.byref(n)))
+        return int(n.value)
+
+    @property
+    def tile_steps(self) -> int:
+        """Steps of a whole tile pass (the automatic mode's), 0 without."""
+        n = ctypes.c_int32()
+        check(_lib.load().lbk_tile_steps(self._handle(), ctypes.byref(n)))
         return int(n.value)
 
     # -- read-out
