@@ -13,10 +13,11 @@
 // What bounds it: on a large lattice the bytes of the tiles (152 B a node of a
 // tile and pass of three steps, 64 B per node and step with the halos, at 5.4
 // TB/s); on a small one the launch and the chain of steps, as in the forward
-// pass.  Two rows a wave keep 98 registers, four waves a SIMD.  Measured against
-// the marching pairs (two rows of waves' worth of redundant columns, two waves
-// a SIMD): 49.3 us a step for 61.8 at 2048 x 2048, 14.5 for 24.5 at 2048 x 512;
-// against single steps 2.9 us for 5.2 at 384 x 256, 2.3 for 4.4 at 64 x 32.
+// pass.  Two rows a wave keep 98 registers, four waves a SIMD; at 96 and five
+// waves a SIMD (a few spills) nothing was gained.  Measured against the
+// marching pairs (two waves a SIMD): 49.3 us a step for 61.8 at 2048 x 2048,
+// 181 for 217 at 4096 x 4096, 14.5 for 24.5 at 2048 x 512; against single steps
+// 2.9 us for 5.2 at 384 x 256, 2.3 for 4.4 at 64 x 32.
 // Tiles in the order of rows of tiles: columns of tiles first (1, 2, 4 or 8
 // strips wide) was slower, 53 to 57 us at 2048 x 2048.
 #include "lbk_adjoint_dev.h"

@@ -162,7 +162,7 @@ TilePlan lbk::tile_plan(const int *nx, const int *ny, int n)
 }
 
 // The next launch of `left` >= 1 steps.  Tile passes share the steps evenly
-// (20 steps at up to 6 a launch are four fives); three-step passes leave a
+// (22 steps at up to 5 a launch are two fives and three fours); three-step passes leave a
 // remainder to a two-step pass or a single sweep.  Every pass is bitwise the
 // single sweeps it replaces.
 Pass lbk::next_pass(const lbk_lattice *lat, int64_t left)
