@@ -65,8 +65,8 @@ template <typename T, int BCX, int BCY, bool HIST, int R, int MODEL, bool EDGE>
 __device__ __forceinline__ void tile_advance(const char *__restrict__ src, char *__restrict__ dst,
                                            const Layout &lay, const char *__restrict__ med,
                                            const MLayout &mlay, const Geom &g, const Physics &ph,
-                                           float s, float inv_s, int halo, int steps, int strip,
-                                           int band, float *__restrict__ hist,
+                                           float s, float inv_s, int halo, int org, int steps,
+                                           int strip, int band, float *__restrict__ hist,
                                            uint64_t hist_bytes, Edges *__restrict__ edges)
 {
     const int lane = (int)(threadIdx.x & 63);
@@ -76,22 +76,25 @@ __device__ __forceinline__ void tile_advance(const char *__restrict__ src, char 
     const int nstrips = (g.nx + own_x - 1) / own_x;
     if (strip >= nstrips)
         return; // the whole workgroup
-    const int xr = strip * own_x - halo + lane;
+    // org > 0: that many columns of the outlet's end lie left of the inlet in
+    // strip 0, which then holds both pressure columns.  Nothing is pulled across
+    // this seam, as a pressure column takes its neighbour's pull.
+    const int xr = strip * own_x - org - halo + lane;
     Lanes ln;
     if (BCX == BC_PERIODIC)
         ln.x = (uint32_t)(((xr % g.nx) + g.nx) % g.nx);
-    else
-        ln.x = (uint32_t)(xr < 0 ? 0 : (xr >= g.nx ? g.nx - 1 : xr)); // beyond: unused copies
-    // As in the marching passes, an outlet column at the first lane of a
-    // strip is left to the previous strip, which completes its neighbour's
-    // pull.
-    bool owned = lane >= halo && lane < halo + own_x && xr < g.nx;
-    if (BCX == BC_PRESSURE && xr == g.nx - 1)
+    else // beyond: unused copies
+        ln.x = (uint32_t)(xr < 0 ? (org ? xr + g.nx : 0) : (xr >= g.nx ? g.nx - 1 : xr));
+    // Without the seam, as in the marching passes, an outlet column at the
+    // first lane of a strip is left to the previous strip, which completes its
+    // neighbour's pull.
+    bool owned = lane >= halo && lane < halo + own_x && xr < g.nx - org;
+    if (BCX == BC_PRESSURE && !org && xr == g.nx - 1)
         owned = lane >= halo + 1 && lane <= halo + own_x;
     ln.wxm = BCX == BC_WALL && ln.x == 0;
     ln.wxp = BCX == BC_WALL && ln.x == (uint32_t)g.nx - 1;
     ln.bin = BCX == BC_PRESSURE && xr == 0;
-    ln.bout = BCX == BC_PRESSURE && xr == g.nx - 1;
+    ln.bout = BCX == BC_PRESSURE && xr == (org ? -1 : g.nx - 1);
     ln.has_b = BCX == BC_PRESSURE && any_lane(ln.bin || ln.bout) ? 1 : 0;
     const int y0 = band * own_y, y1 = min(y0 + own_y, g.ny);
     // tile row j is the lattice's row y0 - halo + j; rows beyond a wall
@@ -196,18 +199,18 @@ template <typename T, int BCX, int BCY, bool HIST, int R, int MODEL>
 __device__ __forceinline__ void tile_steps(const char *__restrict__ src, char *__restrict__ dst,
                                            const Layout &lay, const char *__restrict__ med,
                                            const MLayout &mlay, const Geom &g, const Physics &ph,
-                                           float s, float inv_s, int halo, int steps, int strip,
-                                           int band, float *__restrict__ hist,
+                                           float s, float inv_s, int halo, int org, int steps,
+                                           int strip, int band, float *__restrict__ hist,
                                            uint64_t hist_bytes, Edges *__restrict__ edges)
 {
     const int H = (int)(blockDim.x >> 6) * R, top = band * (H - 2 * halo) - halo;
     if (BCY == BC_WALL && (top <= 0 || top + H >= g.ny))
         tile_advance<T, BCX, BCY, HIST, R, MODEL, BCY == BC_WALL>(
-            src, dst, lay, med, mlay, g, ph, s, inv_s, halo, steps, strip, band, hist, hist_bytes,
-            edges);
+            src, dst, lay, med, mlay, g, ph, s, inv_s, halo, org, steps, strip, band, hist,
+            hist_bytes, edges);
     else
         tile_advance<T, BCX, BCY, HIST, R, MODEL, false>(src, dst, lay, med, mlay, g, ph, s,
-                                                         inv_s, halo, steps, strip, band, hist,
+                                                         inv_s, halo, org, steps, strip, band, hist,
                                                          hist_bytes, edges);
 }
 

@@ -12,7 +12,7 @@ __global__ __launch_bounds__(kTileMaxWaves * 64, 8) void tile_kernel(
     extern __shared__ Edges edges[]; // [parity][kTileMaxWaves]
     const int L = xcd_remap(blockIdx.x, gridDim.x);
     const int band = L / strips, strip = L - band * strips;
-    tile_steps<T, BCX, BCY, HIST, R, MODEL>(src, dst, lay, med, mlay, g, ph, s, inv_s, steps,
+    tile_steps<T, BCX, BCY, HIST, R, MODEL>(src, dst, lay, med, mlay, g, ph, s, inv_s, steps, 0,
                                             steps, strip, band, hist, hist_bytes, edges);
 }
 

@@ -37,7 +37,7 @@ def test_boundaries(bcx, bcy, kn):
         check(nx, ny, bcx, bcy, kn=kn)
 
 
-@pytest.mark.parametrize("nx", range(104, 114))
+@pytest.mark.parametrize("nx", [*range(62, 67), *range(104, 114)])
 def test_outlet_columns(nx):
     check(nx, 11, inputs.PRESSURE)
 

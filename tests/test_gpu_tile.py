@@ -106,6 +106,24 @@ def test_batch_tile_bitwise(storage, bcx, bcy, graph):
         assert torch.equal(a.save_state(), s.save_state())
 
 
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+def test_batch_pressure_columns(storage):
+    # more than 1024 tiles: from 64 columns on a sample's pressure columns are in one strip
+    cases = [medium(nx, 3001, seed=nx, bc_y=inputs.WALL, **drive(inputs.PRESSURE))
+             for nx in (3, 63, 64, 65, 84, 85, 108, 111, 112, 113, 140)]
+    out = []
+    for mode in ("single", "auto"):
+        lats = [Lattice(c.eps, c.k, c.kn0, storage=storage, check_every=0, **c.params)
+                for c in cases]
+        b = Batch(lats)
+        b.set_pass_mode(mode)
+        b.step(9)
+        b.step(4)
+        out.append([lat.save_state() for lat in lats])
+    for c, x, y in zip(cases, *out):
+        assert torch.equal(x, y), c.eps.shape
+
+
 def test_batch_tile_large_and_gradient():
     """Two rows a wave (a batch of 2^21 nodes), and a batched gradient whose
     recomputing passes are tile passes."""
