@@ -286,7 +286,8 @@ lbk_status lbk_adjoint_forward(lbk_lattice *lat, int objective, int64_t n_steps,
 /* Gradients of the J of the last lbk_adjoint_forward on this handle (same
  * workspace, no lbk_step or load in between) into device buffers of
  * [ny][nx] float32: dJ_dlnk (required) and dJ_dlnkn0 (NULL to skip it; it
- * is 0 where kn0 = 0).  Leaves the lattice state untouched. */
+ * is 0 where kn0 = 0).  Leaves the lattice state untouched, and may be called
+ * again: the gradients are the same bitwise. */
 lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws_bytes, float *dJ_dlnk,
                                 float *dJ_dlnkn0);
 

@@ -969,7 +969,7 @@ extern "C" lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws
 {
     if (!lat || !ws || !dJ_dlnk)
         return fail(LBK_ERR_INVALID_ARG, "NULL argument");
-    const AdjPlan &P = lat->adj;
+    AdjPlan &P = lat->adj;
     if (!P.valid || P.ws != ws || ws_bytes < P.total)
         return fail(LBK_ERR_INVALID_ARG, "no matching lbk_adjoint_forward for this workspace");
     if (lat->t != P.t0 + P.n)
@@ -1012,12 +1012,14 @@ extern "C" lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws
         int64_t nseg = 1;
         // inner checkpoints of this segment: kept by the forward pass, or
         // rebuilt into the first kept segment's slots (free by now, since
-        // the kept segments are the last ones and reversed first)
+        // the kept segments are the last ones and reversed first; its own are
+        // gone once a pass has done so)
         const int64_t kept = k - (P.k1 - P.keep);
         const size_t inner = P.inner + (size_t)(kept > 0 ? kept : 0) * P.inner_seg;
-        if (P.two_level && kept >= 0) {
+        if (P.two_level && (kept > 0 || (kept == 0 && !P.reused))) {
             nseg = (b - a + P.c2 - 1) / P.c2;
         } else if (P.two_level) {
+            P.reused = true;
             // rebuild the inner checkpoints of this outer segment (the first
             // is the outer one; the last inner segment needs no further state)
             Range range("adjoint rebuild");

@@ -156,6 +156,7 @@ struct BatchAdj {
     int64_t n = 0, c1 = 0, c2 = 0, k1 = 0, k2 = 0;
     int64_t keep = 0; // trailing segments whose inner checkpoints the forward keeps
     bool two_level = false;
+    bool reused = false; // as AdjPlan::reused
     std::vector<AdjPlan> plans;
     std::vector<size_t> base;
     std::vector<int64_t> t0;
@@ -970,6 +971,7 @@ lbk_status lbk_batch_adjoint_forward(lbk_batch *b, int objective, int64_t n_step
                                  A.a1[i], A.a2[i], A.outlet[i]);
     A.objective = objective;
     A.ws = ws;
+    A.reused = false;
     A.valid = true;
     return LBK_OK;
 }
@@ -1084,12 +1086,14 @@ lbk_status lbk_batch_adjoint_backward(lbk_batch *b, void *ws, size_t ws_bytes,
         const int64_t a = k * A.c1, e = std::min(A.n, a + A.c1);
         int64_t nseg = 1;
         // inner checkpoints kept by the forward pass, or rebuilt into the
-        // first kept segment's slots (free by now)
+        // first kept segment's slots (free by now; its own are gone once a
+        // pass has done so)
         const int64_t kept = k - (A.k1 - A.keep);
         const int i0 = (int)((kept > 0 ? kept : 0) * A.k2);
-        if (A.two_level && kept >= 0) {
+        if (A.two_level && (kept > 0 || (kept == 0 && !A.reused))) {
             nseg = (e - a + A.c2 - 1) / A.c2;
         } else if (A.two_level) {
+            A.reused = true;
             // rebuild the inner checkpoints of this outer segment
             Range range("batch adjoint rebuild");
             LevelSel src{ADJ_OUTER, (int)k};

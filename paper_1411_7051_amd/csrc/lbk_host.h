@@ -63,6 +63,9 @@ struct AdjPlan {
     bool two_level;
     int64_t k1, k2, hlen;
     int64_t keep; // trailing outer segments whose inner checkpoints the forward keeps
+    bool reused;  // a backward pass has rebuilt other segments' inner checkpoints
+                  // in the slots of the first kept one: a further pass rebuilds
+                  // that segment's too
     size_t outer, inner, rec, hist, lam, grad, seg, grad2, seg2, total;
     size_t inner_seg; // bytes of one segment's inner checkpoints (k2 levels)
     size_t level_bytes, hist_bytes, lam_bytes;
