@@ -72,12 +72,13 @@ typedef enum lbk_correlation {
  * or one step per sweep.  A multi-step pass reads and writes the state
  * once per pass; it pays off on lattices large enough to fill the device. */
 typedef enum lbk_pass_mode {
-    LBK_PASS_AUTO = 0,     /* tile passes, several steps per launch at every
-                              size (lbk_tile_steps), forward and reverse;
-                              with a band set, marching passes: three-step
-                              from 2^22 nodes (FP32), 2^23 (FP16/BF16),
-                              two-step from 2^20 (FP32), 2^22 (FP16/BF16),
-                              single sweeps below */
+    LBK_PASS_AUTO = 0,     /* tile passes, several steps per launch
+                              (lbk_tile_steps), forward and reverse; with a
+                              band set, or on very wide lattices of a few
+                              rows, marching passes: three-step from 2^22
+                              nodes (FP32), 2^23 (FP16/BF16), two-step from
+                              2^20 (FP32), 2^22 (FP16/BF16), single sweeps
+                              below */
     LBK_PASS_TWO_STEP = 1, /* two-step passes whatever the size */
     LBK_PASS_SINGLE = 2,   /* single sweeps */
     LBK_PASS_THREE_STEP = 3 /* lbk_step: three-step passes whatever the size (a
@@ -167,7 +168,8 @@ lbk_status lbk_time(const lbk_lattice *lat, int64_t *t);
 lbk_status lbk_steps_per_launch(const lbk_lattice *lat, int32_t *steps);
 
 /* Steps of a whole tile pass where lbk_step takes tile passes (pass_mode
- * LBK_PASS_AUTO without a band), 0 where it does not. */
+ * LBK_PASS_AUTO without a band, the lattice not of a few rows and very wide),
+ * 0 where it does not. */
 lbk_status lbk_tile_steps(const lbk_lattice *lat, int32_t *steps);
 
 /* Macroscopic read-out at the current time (Eqs. 16-17 on the post-stream

@@ -158,7 +158,45 @@ TilePlan lbk::tile_plan(const int *nx, const int *ny, int n)
             best = p;
         }
     }
+    best.us = best_us;
     return best;
+}
+
+double lbk::tile_us(const TilePlan &p, int storage, const int *nx, const int *ny, int n)
+{
+    const int H = p.tile.waves * p.tile.rows, own_x = 64 - 2 * p.steps, own_y = H - 2 * p.steps;
+    const double level = 4.0 + 9.0 * elem_size(storage); // bytes of a node's state
+    double bytes = 0;
+    for (int i = 0; i < n; ++i)
+        bytes += (double)tile_strips(nx[i], p) * tile_bands(ny[i], p) *
+                 (64.0 * H * (level + 12.0) + (double)own_x * std::min(own_y, ny[i]) * level);
+    return std::max(p.us, bytes / p.steps / 5.3e6); // 5.3 TB/s
+}
+
+// Whether tile passes lead on a lattice: everywhere but where a single band of
+// the passes they replace covers a lattice of a few rows, which those then march
+// along without recomputing any, while a tile loads 8 to 16 rows for the few it
+// stores.  The predicted times (us a step, n the nodes) are fits to lattices
+// 24,576 to 4,194,304 wide, right within 7% where they decide: us a step, tile
+// passes against the others, 32768 x 1 2.7 / 4.1 and 131072 x 1 5.7 / 4.6 (FP32),
+// 98304 x 3 5.9 / 6.1 and 262144 x 3 12.8 / 10.9 (FP16), 524288 x 2 18.5 / 12.0,
+// 1048576 x 8 68 / 73 and 1048576 x 5 61 / 51 (FP32), 1048576 x 12 98 / 79 and
+// 1048576 x 16 101 / 101 (FP16).
+static bool tiles_lead(const lbk_desc &d, const TilePlan &p)
+{
+    const double n = (double)d.nx * d.ny;
+    const bool f32 = d.storage == LBK_F32;
+    double us = INFINITY;
+    if (n >= (double)three_step_nodes(d.storage)) {
+        if (d.ny < fwd_band3(d))
+            us = 1e-6 * n * (f32 ? 7.5 + 7.5 / d.ny : 6.1 + 8.0 / d.ny);
+    } else if (n >= (double)two_step_nodes(d.storage)) {
+        if (d.ny < fwd_band(d))
+            us = 1.0 + 1e-6 * n * (f32 ? 11.0 : 7.9);
+    } else if (d.ny <= 8) {
+        us = 3.3 + 1e-6 * n * (f32 ? 14.5 : 9.7);
+    }
+    return tile_us(p, d.storage, &d.nx, &d.ny, 1) <= us;
 }
 
 // The next launch of `left` >= 1 steps.  Tile passes share the steps evenly
@@ -449,6 +487,7 @@ lbk_status lbk_create(const lbk_desc *d, const float *eps, const float *k, const
     ph.slip_c = (float)(4.0 - d->slip_b);
     ph.derive();
     lat->plan = tile_plan(&d->nx, &d->ny, 1);
+    lat->tiles_lead = tiles_lead(*d, lat->plan);
 
     char *ws = lat->ws;
     char *med = lat->med();

@@ -1,0 +1,37 @@
+"""Which passes the automatic mode takes: tile passes but on very wide lattices
+of a few rows, where a tile loads many times the rows it stores."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_1411_7051_amd import Lattice, inputs  # noqa: E402
+
+PRESSURE = dict(bc_x=inputs.PRESSURE, rho_in=1.01, rho_out=1.0, init=1, check_every=0)
+
+
+def fields(nx, ny, seed=1):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    r = [torch.rand((ny, nx), generator=g, device="cuda") for _ in range(3)]
+    return 0.2 + 0.5 * r[0], 10 ** (-4 + 3 * r[1]), 0.01 + 0.2 * r[2]
+
+
+# either side of the rule, per pass that tile passes replace (single sweeps, two-
+# and three-step passes), where the measured times differ by a tenth and more
+@pytest.mark.parametrize("nx,ny,storage,tiles", [
+    (32768, 1, "f32", True), (131072, 1, "f32", False), (524288, 1, "f32", False),
+    (262144, 2, "f32", True), (524288, 2, "f32", False), (524288, 3, "f32", False),
+    (524288, 5, "f32", True), (1048576, 3, "f32", False), (1048576, 5, "f32", False),
+    (524288, 13, "f32", True), (32768, 1, "f16", True), (131072, 1, "f16", False),
+    (65536, 2, "f16", True), (262144, 2, "f16", False), (262144, 3, "bf16", False),
+    (524288, 6, "f16", True), (1048576, 4, "f16", False), (1048576, 8, "bf16", False),
+    (1048576, 12, "f16", False), (524288, 24, "f16", True), (3, 524288, "f32", True),
+    (64, 32768, "f16", True)])
+def test_wide_lattices(nx, ny, storage, tiles):
+    f = fields(nx, ny)
+    lat = Lattice(*f, storage=storage, **PRESSURE)
+    assert (lat.tile_steps > 0) == tiles
+    one = Lattice(*f, storage=storage, pass_mode="single", **PRESSURE)
+    assert one.tile_steps == 0
+    assert torch.equal(lat.step(8).save_state(), one.step(8).save_state())
