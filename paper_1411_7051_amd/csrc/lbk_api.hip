@@ -162,7 +162,8 @@ TilePlan lbk::tile_plan(const int *nx, const int *ny, int n)
     return best;
 }
 
-double lbk::tile_us(const TilePlan &p, int storage, const int *nx, const int *ny, int n)
+double lbk::tile_us(const TilePlan &p, int storage, double model, const int *nx,
+                    const int *ny, int n)
 {
     const int H = p.tile.waves * p.tile.rows, own_x = 64 - 2 * p.steps, own_y = H - 2 * p.steps;
     const double level = 4.0 + 9.0 * elem_size(storage); // bytes of a node's state
@@ -170,33 +171,45 @@ double lbk::tile_us(const TilePlan &p, int storage, const int *nx, const int *ny
     for (int i = 0; i < n; ++i)
         bytes += (double)tile_strips(nx[i], p) * tile_bands(ny[i], p) *
                  (64.0 * H * (level + 12.0) + (double)own_x * std::min(own_y, ny[i]) * level);
-    return std::max(p.us, bytes / p.steps / 5.3e6); // 5.3 TB/s
+    return std::max(p.us * model, bytes / p.steps / 5.3e6); // 5.3 TB/s
 }
 
-// Whether tile passes lead on a lattice: everywhere but where a single band of
-// the passes they replace covers a lattice of a few rows, which those then march
-// along without recomputing any, while a tile loads 8 to 16 rows for the few it
-// stores.  The predicted times (us a step, n the nodes) are fits to lattices
-// 24,576 to 4,194,304 wide, right within 7% where they decide: us a step, tile
-// passes against the others, 32768 x 1 2.7 / 4.1 and 131072 x 1 5.7 / 4.6 (FP32),
-// 98304 x 3 5.9 / 6.1 and 262144 x 3 12.8 / 10.9 (FP16), 524288 x 2 18.5 / 12.0,
-// 1048576 x 8 68 / 73 and 1048576 x 5 61 / 51 (FP32), 1048576 x 12 98 / 79 and
-// 1048576 x 16 101 / 101 (FP16).
-static bool tiles_lead(const lbk_desc &d, const TilePlan &p)
+// Whether tile passes lead on a lattice: everywhere but
+//
+// - where a single band of the passes they replace covers a lattice of a few
+//   rows, which those then march along without recomputing any, while a tile
+//   loads 8 to 16 rows for the few it stores.  The predicted times (us a step, n
+//   the nodes) are fits to lattices 24,576 to 4,194,304 wide, right within 8%
+//   where they decide: us a step, tile passes against the others, 32768 x 1
+//   2.7 / 4.1 and 131072 x 1 5.7 / 4.6 (FP32), 98304 x 3 5.9 / 6.1 and 262144 x 3
+//   12.8 / 10.9 (FP16), 524288 x 2 18.5 / 12.0, 1048576 x 8 68 / 73 and
+//   1048576 x 5 61 / 51 (FP32), 1048576 x 12 98 / 79 and 1048576 x 16 101 / 101
+//   (FP16).  The Forchheimer term costs a tile's redundant updates more than a
+//   pass that waits for memory: 262144 x 2 13.8 / 11.1 with it, 10.1 / 10.9
+//   without;
+// - with the Forchheimer term, 16-bit storage and pressure columns (whose strips
+//   then hold their compute units longest) on lattices that single sweeps read
+//   from the on-package cache: 777 x 333 5.7 / 6.5, 512 x 512 5.7 / 5.5,
+//   1024 x 512 9.5 / 7.5, 1024 x 1024 15.1 / 13.9, 1400 x 1400 23.3 / 23.4.
+static bool tiles_lead(const lbk_desc &d, const Physics &ph, const TilePlan &p)
 {
     const double n = (double)d.nx * d.ny;
-    const bool f32 = d.storage == LBK_F32;
+    const bool f32 = d.storage == LBK_F32, forch = ph.feps != 0.0f;
+    if (forch && !f32 && d.bc_x == LBK_BC_PRESSURE && d.ny > 8 && n >= 1 << 18 && n < 3 << 19)
+        return false;
     double us = INFINITY;
     if (n >= (double)three_step_nodes(d.storage)) {
-        if (d.ny < fwd_band3(d))
-            us = 1e-6 * n * (f32 ? 7.5 + 7.5 / d.ny : 6.1 + 8.0 / d.ny);
+        if (d.ny < fwd_band3(d) + forch)
+            us = 1e-6 * n * (f32 ? 7.5 + 7.5 / d.ny : 6.1 + 8.0 / d.ny) *
+                 (!forch ? 1.0 : f32 ? 1.12 : 1.3);
     } else if (n >= (double)two_step_nodes(d.storage)) {
-        if (d.ny < fwd_band(d))
-            us = 1.0 + 1e-6 * n * (f32 ? 11.0 : 7.9);
+        if (d.ny < fwd_band(d) + forch)
+            us = 1.0 + 1e-6 * n * (f32 ? 11.0 : 7.9) * (!forch ? 1.0 : f32 ? 1.08 : 1.2);
     } else if (d.ny <= 8) {
-        us = 3.3 + 1e-6 * n * (f32 ? 14.5 : 9.7);
+        us = std::max(3.7, 3.3 + 1e-6 * n * (f32 ? 14.5 : 9.7));
     }
-    return tile_us(p, d.storage, &d.nx, &d.ny, 1) <= us;
+    const double model = forch ? 1.4 : ph.standard ? 1.0 : 1.05;
+    return tile_us(p, d.storage, model, &d.nx, &d.ny, 1) <= us;
 }
 
 // The next launch of `left` >= 1 steps.  Tile passes share the steps evenly
@@ -487,7 +500,7 @@ lbk_status lbk_create(const lbk_desc *d, const float *eps, const float *k, const
     ph.slip_c = (float)(4.0 - d->slip_b);
     ph.derive();
     lat->plan = tile_plan(&d->nx, &d->ny, 1);
-    lat->tiles_lead = tiles_lead(*d, lat->plan);
+    lat->tiles_lead = tiles_lead(*d, ph, lat->plan);
 
     char *ws = lat->ws;
     char *med = lat->med();

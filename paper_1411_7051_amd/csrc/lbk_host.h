@@ -99,8 +99,10 @@ struct TilePlan {
 };
 // The shape for one launch over n lattices of nx[i] x ny[i] nodes.
 TilePlan tile_plan(const int *nx, const int *ny, int n);
-// Predicted us a step of these tile passes, by arithmetic and bytes.
-double tile_us(const TilePlan &p, int storage, const int *nx, const int *ny, int n);
+// Predicted us a step of these tile passes, by arithmetic (`model` times that of
+// the standard model) and bytes.
+double tile_us(const TilePlan &p, int storage, double model, const int *nx, const int *ny,
+               int n);
 // Tiles that shape cuts one lattice into.
 inline int tile_strips(int nx, const TilePlan &p)
 {
@@ -261,7 +263,7 @@ inline bool three_step_pass(const lbk_lattice *lat)
 // wide lattices of a few rows (tiles_lead), us a step against the passes they
 // replace: 64 x 32 FP32 2.1 / 3.2 (single sweeps), 1024 x 512 6.2 / 10.2, 2048 x 2048 27 / 43 (three-step passes), 4096 x 4096
 // 99 / 128; 4096 x 4096 FP16 96 / 107, with a body force 96 / 99, with the
-// Forchheimer term 141 / 143.  An explicit band asks for the marching passes.
+// Forchheimer term 144 / 145.  An explicit band asks for the marching passes.
 inline bool tile_pass(const lbk_lattice *lat)
 {
     return lat->d.pass_mode == LBK_PASS_AUTO && lat->d.band == 0 && lat->tiles_lead;

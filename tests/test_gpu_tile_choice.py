@@ -1,5 +1,6 @@
 """Which passes the automatic mode takes: tile passes but on very wide lattices
-of a few rows, where a tile loads many times the rows it stores."""
+of a few rows, where a tile loads many times the rows it stores, and on mid-sized lattices
+with the Forchheimer term, 16-bit storage and pressure columns."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -34,4 +35,22 @@ def test_wide_lattices(nx, ny, storage, tiles):
     assert (lat.tile_steps > 0) == tiles
     one = Lattice(*f, storage=storage, pass_mode="single", **PRESSURE)
     assert one.tile_steps == 0
+    assert torch.equal(lat.step(8).save_state(), one.step(8).save_state())
+
+
+# with the Forchheimer term: mid-sized lattices, and wide ones
+@pytest.mark.parametrize("nx,ny,storage,bcx,tiles", [
+    (777, 333, "f16", inputs.PRESSURE, True), (512, 512, "f16", inputs.PRESSURE, False),
+    (1024, 512, "bf16", inputs.PRESSURE, False), (700, 400, "f16", inputs.PRESSURE, False),
+    (1024, 1024, "f16", inputs.PRESSURE, False), (1400, 1400, "bf16", inputs.PRESSURE, True),
+    (1024, 512, "f32", inputs.PRESSURE, True), (1024, 512, "f16", inputs.WALL, True),
+    (1024, 1024, "bf16", inputs.PERIODIC, True), (24576, 1, "f16", inputs.PRESSURE, True),
+    (65536, 1, "f32", inputs.PRESSURE, False), (262144, 2, "f32", inputs.PRESSURE, False),
+    (1048576, 7, "f16", inputs.PRESSURE, False)])
+def test_forchheimer(nx, ny, storage, bcx, tiles):
+    drive = PRESSURE if bcx == inputs.PRESSURE else dict(bc_x=bcx, gx=1e-6, check_every=0)
+    f = fields(nx, ny)
+    lat = Lattice(*f, storage=storage, f_eps=0.5, **drive)
+    assert (lat.tile_steps > 0) == tiles
+    one = Lattice(*f, storage=storage, f_eps=0.5, pass_mode="single", **drive)
     assert torch.equal(lat.step(8).save_state(), one.step(8).save_state())
