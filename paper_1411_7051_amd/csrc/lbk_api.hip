@@ -1016,6 +1016,34 @@ static TilePlan rev_tile_plan(const lbk_lattice *lat)
     return one_row ? TilePlan{{12, 1}, 3} : TilePlan{{8, 2}, 3};
 }
 
+// Whether the automatic mode's reverse steps take tile passes of that plan:
+// everywhere but where the rows its bands have room for are many times the
+// lattice's and the tiles too many to run side by side; the lattice's own rows
+// are then read once instead.  us a step, tile passes against single steps or
+// pairs: 16384 x 1 4.8 / 5.6, 65536 x 1 8.5 / 6.8 and 524288 x 1 45 / 13,
+// 32768 x 4 6.6 / 7.3, 131072 x 4 14.2 / 12.8 and 524288 x 4 56 / 45,
+// 65536 x 5 8.8 / 9.6, 262144 x 5 30 / 30 and 524288 x 5 68 / 55,
+// 262144 x 11 69 / 79 and 524288 x 11 129 / 113, 524288 x 7 72 / 78.  With the
+// Forchheimer term, whose updates cost more, a quarter of unused room is too much
+// (a backward pass, us a step: 131072 x 3 24 / 21, 524288 x 7 154 / 135,
+// 524288 x 13 258 / 206), between walls a sixth (524288 x 5 129 / 114, 524288 x 7
+// 216 / 124).
+static bool rev_tiles_lead(const lbk_lattice *lat, const TilePlan &p)
+{
+    const lbk_desc &d = lat->d;
+    const int own_y = p.tile.waves * p.tile.rows - 2 * p.steps;
+    const int64_t bands = tile_bands(d.ny, p), tiles = tile_strips(d.nx, p) * bands;
+    const int64_t nodes = (int64_t)d.nx * d.ny;
+    const double room = (double)bands * own_y / d.ny;
+    if (lat->ph.feps != 0.0f)
+        return room < (d.bc_y == LBK_BC_WALL ? 1.15 : 1.25) || tiles <= (room < 2.0 ? 2000 : 600);
+    if (room >= 2.5)
+        return tiles <= 600;
+    if (room >= 2.0)
+        return nodes < (int64_t)1 << 21;
+    return room <= 1.6 || nodes < (int64_t)1 << 22;
+}
+
 extern "C" lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws_bytes,
                                            float *dJ_dlnk, float *dJ_dlnkn0)
 {
@@ -1043,8 +1071,9 @@ extern "C" lbk_status lbk_adjoint_backward(lbk_lattice *lat, void *ws, size_t ws
     char *rec[2] = {level(P.rec, 0), level(P.rec, 1)};
     // rebuilt inner checkpoints (no history) and recorded segments take
     // lbk_step's passes, the reverse steps tile passes or pairs likewise
-    const bool tile = tile_pass(lat), two = two_step_pass(lat);
     const TilePlan rev = rev_tile_plan(lat);
+    const bool tile = d.pass_mode == LBK_PASS_AUTO && d.band == 0 && rev_tiles_lead(lat, rev);
+    const bool two = two_step_pass(lat);
     const float a1 = (float)P.a1, a2 = (float)P.a2;
 
     HIP_TRY(hipMemsetAsync(grad, 0, (size_t)d.ny * lat->L.pitch * 8, st));

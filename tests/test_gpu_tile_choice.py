@@ -54,3 +54,30 @@ def test_forchheimer(nx, ny, storage, bcx, tiles):
     assert (lat.tile_steps > 0) == tiles
     one = Lattice(*f, storage=storage, f_eps=0.5, pass_mode="single", **drive)
     assert torch.equal(lat.step(8).save_state(), one.step(8).save_state())
+
+
+@pytest.mark.parametrize("nx,ny", [(16384, 1), (65536, 1), (32768, 4), (131072, 4), (524288, 4),
+                                   (262144, 5), (524288, 5), (524288, 6), (400000, 11)])
+@pytest.mark.parametrize("extra", [{}, dict(f_eps=0.7)])
+def test_reverse_steps_of_wide_lattices(nx, ny, extra):
+    """Either side of the reverse passes' rule: the gradients are those of
+    single steps bitwise, and a backward pass takes no longer than with single
+    sweeps and steps (an eighth is left for noise; the tile passes took 1.3 to
+    2.8 times as long on the widest lattices of one to four rows)."""
+    f = fields(nx, ny)
+    runs = {}
+    for mode in ("single", "auto"):
+        lat = Lattice(*f, pass_mode=mode, **PRESSURE, **extra)
+        _, ws = lat.adjoint_forward(12, "k_app", 12, 12)
+        runs[mode] = (lat, ws, *lat.adjoint_backward(ws, wrt_kn0=True), [])
+    assert torch.equal(runs["single"][2], runs["auto"][2])
+    assert torch.equal(runs["single"][3], runs["auto"][3])
+    for _ in range(25):
+        for lat, ws, _, _, ms in runs.values():
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            lat.adjoint_backward(ws)
+            ev[1].record()
+            torch.cuda.synchronize()
+            ms.append(ev[0].elapsed_time(ev[1]))
+    assert min(runs["auto"][4]) <= 1.125 * min(runs["single"][4])
