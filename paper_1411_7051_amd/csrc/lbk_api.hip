@@ -204,11 +204,11 @@ static bool tiles_lead(const lbk_desc &d, const Physics &ph, const TilePlan &p)
                  (!forch ? 1.0 : f32 ? 1.12 : 1.3);
     } else if (n >= (double)two_step_nodes(d.storage)) {
         if (d.ny < fwd_band(d) + forch)
-            us = 1.0 + 1e-6 * n * (f32 ? 11.0 : 7.9) * (!forch ? 1.0 : f32 ? 1.08 : 1.2);
+            us = 1.0 + 1e-6 * n * (f32 ? 11.0 : 8.0) * (!forch ? 1.0 : f32 ? 1.08 : 1.2);
     } else if (d.ny <= 8) {
         us = std::max(3.7, 3.3 + 1e-6 * n * (f32 ? 14.5 : 9.7));
     }
-    const double model = forch ? 1.4 : ph.standard ? 1.0 : 1.05;
+    const double model = forch ? 1.4 : ph.standard ? 1.0 : 1.03;
     return tile_us(p, d.storage, model, &d.nx, &d.ny, 1) <= us;
 }
 
