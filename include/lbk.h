@@ -349,7 +349,8 @@ lbk_status lbk_batch_get_launch(const lbk_batch *b, int32_t *tile_x, int32_t *ro
  * four 60-column strips by a band of rows of each sample (tile_x, rows and
  * grid apply to single steps only, such as the last of an odd count);
  * LBK_PASS_SINGLE: one step per launch; LBK_PASS_AUTO (the default):
- * tile passes (lbk_batch_tile_steps) until lbk_batch_autotune has timed
+ * tile passes (lbk_batch_tile_steps; not for samples of a few rows, nor for
+ * some batches with the Forchheimer term) until lbk_batch_autotune has timed
  * them against the others and keeps the fastest.  Either way each
  * sample ends bitwise where single steps take it.  Drops recorded graphs
  * when the choice changes.  Batches have no three-step pass:
@@ -362,8 +363,8 @@ lbk_status lbk_batch_get_pass_mode(const lbk_batch *b, int32_t *pass_mode,
                                    int32_t *steps_per_launch);
 
 /* Steps of a whole tile pass when the batch steps in tile passes (the
- * automatic mode, unless lbk_batch_autotune measured another pass faster), 0
- * when it does not. */
+ * automatic mode's choice by the samples' sizes and model, or what
+ * lbk_batch_autotune measured fastest), 0 when it does not. */
 lbk_status lbk_batch_tile_steps(const lbk_batch *b, int32_t *steps);
 
 /* on != 0: every graph replay ends with the per-sample read-out reductions

@@ -77,6 +77,49 @@ TilePlan plan_of(lbk_lattice *const *lats, int n)
     return tile_plan(nx.data(), ny.data(), n);
 }
 
+// Whether tile passes lead on a batch, until the tuner has measured it.  As for
+// a lattice (tiles_lead), they do but
+//
+// - where every sample has a few rows: 64 samples of 8192 x 1 20.5 us a step
+//   against 9.9 in single sweeps (FP32), 8192 x 3 23.7 / 25.5 (FP32) and 24.9 /
+//   18.4 (FP16), 8192 x 5 29.4 / 28.5 (FP16), 2000 x 8 11.4 / 13.6 (FP16); lists
+//   of tiles run 4% over the estimate, and single sweeps pad rows to 256 lanes;
+// - with the Forchheimer term and pressure columns on mid-sized batches with
+//   16-bit storage: two samples of 512 x 512 9.8 / 8.0, eight 28.1 / 26.5, but 16
+//   of 300 x 200 (padded to 512 lanes) 18.0 / 18.8 and three of 1000 x 900 30.6 /
+//   32.5; and on small ones of narrow samples, where most tiles hold a pressure
+//   column: twelve of 150 x 160 8.6 / 8.0 (FP16), 8.2 / 7.5 (FP32).
+bool batch_tiles_lead(lbk_lattice *const *lats, int n, const TilePlan &plan)
+{
+    const lbk_desc &d = lats[0]->d;
+    const bool f32 = d.storage == LBK_F32;
+    bool forch = false, standard = true;
+    int rows = 0;
+    double nodes = 0, lanes = 0;
+    std::vector<int> nx(n), ny(n);
+    for (int i = 0; i < n; ++i) {
+        nx[i] = lats[i]->d.nx;
+        ny[i] = lats[i]->d.ny;
+        nodes += (double)nx[i] * ny[i];
+        lanes += (double)align_up((size_t)nx[i], kBatchMaxTile) * ny[i];
+        rows = std::max(rows, ny[i]);
+        forch = forch || lats[i]->ph.feps != 0.0f;
+        standard = standard && lats[i]->ph.standard;
+    }
+    if (rows > 8) {
+        const bool padded = lanes > 1.5 * nodes;
+        if (!forch || d.bc_x != LBK_BC_PRESSURE || nodes < 1 << 18)
+            return true;
+        return nodes < 1 << 19 ? f32 && !padded : f32 || padded || nodes > 1 << 21;
+    }
+    const double us =
+        nodes >= kTwoStepBatchNodes
+            ? 1.0 + 1e-6 * nodes * (f32 ? 11.0 : 8.0) * (!forch ? 1.0 : f32 ? 1.08 : 1.2)
+            : 2.3 + 1e-6 * lanes * (f32 ? 14.5 : 9.7);
+    const double model = forch ? 1.4 : standard ? 1.0 : 1.03;
+    return 1.04 * tile_us(plan, d.storage, model, nx.data(), ny.data(), n) <= us;
+}
+
 int64_t tiles_in(const lbk_lattice *l, const TilePlan &p)
 {
     return (int64_t)tile_strips(l->d.nx, p) * tile_bands(l->d.ny, p);
@@ -235,6 +278,7 @@ struct lbk_batch {
     int tuned;             // -1: not tuned; else the tuner's choice of pass (AUTO):
                            // PASS_ONE, PASS_TWO or PASS_TILE
     int standard;          // every sample runs the standard model (MODEL_STD)
+    bool tiles_lead;       // whether AUTO takes tile passes while not tuned
     SampleDesc *host_desc; // pinned staging, [4][n]: sweep, read-out, two-step pass, tiles
     double *host_res;      // pinned, [n][MAC_SLOTS]
     int grid, graph_steps;
@@ -255,13 +299,13 @@ struct lbk_batch {
     const lbk_desc &d0() const { return lats[0]->d; }
     SampleDesc *desc_tile() const { return reinterpret_cast<SampleDesc *>(ws + B.desc_tile); }
     int *map_tile() const { return reinterpret_cast<int *>(ws + B.map_tile); }
-    // whether steps go through tile passes: the automatic mode unless the
-    // tuner measured another pass faster (a batch of 16 samples 256 to 1536
+    // whether steps go through tile passes: in the automatic mode the tuner's
+    // choice, else where batch_tiles_lead has them lead (a batch of 16 samples 256 to 1536
     // wide: FP16 94 us a step against 106 in two-step passes, FP32 90 against
     // 145; of twelve FP32 samples 64 to 256 wide 7.2 against 9.3 in single steps)
     bool tile() const
     {
-        return pass_mode == LBK_PASS_AUTO && (tuned < 0 || tuned == PASS_TILE);
+        return pass_mode == LBK_PASS_AUTO && (tuned < 0 ? tiles_lead : tuned == PASS_TILE);
     }
     // whether the batch counts as one that steps in pairs: what the calls
     // report, its passes where it takes no tile passes, and its reverse steps
@@ -551,6 +595,7 @@ lbk_status lbk_batch_create(lbk_lattice *const *lats, int32_t n, void *workspace
     b->standard = 1;
     for (int i = 0; i < n; ++i)
         b->standard = b->standard && lats[i]->ph.standard;
+    b->tiles_lead = batch_tiles_lead(lats, n, b->B.plan);
     int64_t sweep2_tiles = 0, tile_tiles = 0;
     if ((s = upload_map(b, kReadShape, b->map_read(), b->tile0_read, read_tiles)) != LBK_OK ||
         (s = upload_map(b, Shape{kStrip2, 0}, b->map_sweep2(), b->tile0_sweep2,

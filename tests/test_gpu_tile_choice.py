@@ -7,7 +7,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-from paper_1411_7051_amd import Lattice, inputs  # noqa: E402
+from paper_1411_7051_amd import Batch, Lattice, inputs  # noqa: E402
 
 PRESSURE = dict(bc_x=inputs.PRESSURE, rho_in=1.01, rho_out=1.0, init=1, check_every=0)
 
@@ -81,3 +81,22 @@ def test_reverse_steps_of_wide_lattices(nx, ny, extra):
             torch.cuda.synchronize()
             ms.append(ev[0].elapsed_time(ev[1]))
     assert min(runs["auto"][4]) <= 1.125 * min(runs["single"][4])
+
+
+@pytest.mark.parametrize("n,nx,ny,storage,f_eps,tiles", [
+    (64, 4096, 1, "f32", 0.0, False), (64, 8192, 2, "f32", 0.0, False),
+    (64, 8192, 3, "f16", 0.0, False), (64, 8192, 4, "f32", 0.0, True),
+    (64, 2000, 8, "f16", 0.0, True), (256, 100, 8, "f32", 0.0, True),
+    (64, 8192, 3, "f32", 0.5, False), (64, 16384, 8, "bf16", 0.5, False),
+    (12, 150, 160, "f32", 0.5, False), (12, 150, 160, "f32", 0.0, True),
+    (2, 512, 512, "f16", 0.5, False), (2, 512, 512, "f32", 0.5, True),
+    (16, 300, 200, "bf16", 0.5, True), (3, 1000, 900, "f16", 0.5, True)])
+def test_batches(n, nx, ny, storage, f_eps, tiles):
+    fs = [fields(nx, ny, i) for i in range(n)]
+    lats = [Lattice(*f, storage=storage, f_eps=f_eps, **PRESSURE) for f in fs]
+    b = Batch(lats)
+    assert (b.tile_steps > 0) == tiles
+    b.step(7)
+    for f, lat in list(zip(fs, lats))[::max(1, n // 4)]:
+        one = Lattice(*f, storage=storage, f_eps=f_eps, pass_mode="single", **PRESSURE)
+        assert torch.equal(lat.save_state(), one.step(7).save_state())
