@@ -52,29 +52,34 @@ __device__ __forceinline__ NodeFwd node_fwd(const Physics &ph, float rho, float 
     // hardware reciprocals, as in the sweep's velocity solve
     n.ie = M == REV_STD ? e : inv_eps(e);
     n.rinv = __builtin_amdgcn_rcpf(rho);
-    // f_c = den / num, as in the sweep, and nd = den num Kn f_c'(Kn) / (Kn f_c).
+    // f_c = den / num, as in the sweep, and ndr = num f_c'(Kn) / f_c.
     // For Eqs. 6-7, f_c = P1 P2 with P1 = p1/a, a = t + 0.170, t = Kn^0.4348,
     // p1 = a + 1.358 t Kn, and P2 = p2/q, p2 = 1 + (4 - b) Kn, q = 1 - b Kn:
     // P1' = 1.358 t (t + 1.4348 * 0.170)/a^2 and P2' = 4/q^2, so
     // f_c'/f_c = 1.358 t (t + 0.243916)/(a p1) + 4/(q p2), over the common
-    // denominator num den = a q p1 p2.  For Eqs. 4-5, f_c' = 4.
+    // denominator num den = a q p1 p2: one reciprocal, r = 1 / den.  r goes into
+    // each product before the large factors meet, so that nothing overflows
+    // before den itself does (~ Kn^2.43, from Kn = 3e15 on).  For Eqs. 4-5,
+    // f_c' = 4.
     const float kn = M == REV_STD ? kn0 * n.rinv
                                   : (ph.kn_local ? kn0 * (ph.rho_ref * n.rinv) : kn0);
-    float num = 1.0f, den = 1.0f, nd = 0.0f;
+    float num = 1.0f, den = 1.0f, r = 1.0f, ndr = 0.0f;
     if (M == REV_STD || ph.corr == CORR_BKC) {
         const float t = fc_pow(kn);
         fc_bkc(ph, kn, t, num, den);
+        r = __builtin_amdgcn_rcpf(den);
         const float a = t + 0.170f, tt = 1.358f * t;
         const float p1 = a + tt * kn, p2 = 1.0f + ph.slip_c * kn, q = 1.0f + ph.slip_nb * kn;
-        nd = tt * (t + 0.243916f) * (q * p2) + 4.0f * (a * p1);
+        ndr = tt * (t + 0.243916f) * q * (p2 * r) + 4.0f * a * (p1 * r);
     } else if (ph.corr == CORR_KLINKENBERG) {
         fc_parts_t(ph, kn, 0.0f, num, den);
-        nd = 4.0f;
+        r = __builtin_amdgcn_rcpf(den);
+        ndr = 4.0f * r;
     }
-    const float r = __builtin_amdgcn_rcpf(den), dn = drag * num;
+    const float dn = drag * num;
     n.A = dn * r; // drag / f_c
-    // dA/d ln kn0 = -A Kn f_c'(Kn) / f_c = -drag Kn nd / den^2
-    n.dA_dlnkn = -(kn * (nd * r)) * (drag * r);
+    // dA/d ln kn0 = -A Kn f_c'(Kn) / f_c = -drag Kn ndr / den
+    n.dA_dlnkn = -(kn * ndr * r) * drag;
     float vx = jx * n.rinv, vy = jy * n.rinv, egx = 0.0f, egy = 0.0f;
     if (M != REV_STD) {
         egx = e * ph.gx;
