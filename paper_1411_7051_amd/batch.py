@@ -105,11 +105,20 @@ class Batch:
 
     def signature(self) -> str:
         """Key of this batch's shape for the tuning cache: device, storage,
-        boundary kinds and the sorted sample sizes."""
+        boundary kinds, the sorted sample sizes, what of the model decides the
+        kernels' cost, and the passes that the tuner chooses from (an entry
+        measured among others does not answer)."""
         l0 = self.lattices[0]
+        descs = [l.desc for l in self.lattices]
         sizes = sorted((l.nx, l.ny) for l in self.lattices)
+        forchheimer = any(d.f_eps != 0.0 for d in descs)
+        # the model with kernels of its own: second-order correlation, Darcy
+        # drag, local Kn quoted at density 1, no body force
+        standard = all(d.correlation == 0 and d.f_eps == 0.0 and d.kn_local and d.rho_ref == 1.0
+                       and d.gx == 0.0 and d.gy == 0.0 for d in descs)
         key = json.dumps([torch.cuda.get_device_name(self.device), int(l0.desc.storage),
-                          int(l0.desc.bc_x), int(l0.desc.bc_y), sizes])
+                          int(l0.desc.bc_x), int(l0.desc.bc_y), sizes, forchheimer, standard,
+                          ["single", "two_step", "tile"]])
         return hashlib.sha1(key.encode()).hexdigest()[:16]
 
     def autotune(self, reps: int = 10, cache: Optional[str] = None) -> float:
@@ -129,7 +138,10 @@ class Batch:
                 tile_x, rows, grid, per_launch, _ = entry
                 self.set_launch(tile_x, rows, grid, self.launch[3])
                 self.set_pass_mode({0: "auto", 2: "two_step"}.get(per_launch, "single"))
-                return float("nan")
+                # tile passes that the automatic mode would not take untuned
+                # are set by the tuner alone: measure again
+                if per_launch != 0 or self.tile_steps:
+                    return float("nan")
         us = ctypes.c_double()
         check(_lib.load().lbk_batch_autotune(self._handle(), int(reps), ctypes.byref(us)))
         if cache:
