@@ -589,9 +589,9 @@ __device__ __forceinline__ bool adj_tile(const AdjSampleDesc *__restrict__ sampl
 {
     const int t = xcd_remap_a(blockIdx.x, gridDim.x);
     sd = samples[tile_sample[t]];
-    const int rel = t - sd.tile0;
-    const int ty = rel / sd.tpr;
-    x = (uint32_t)(rel - ty * sd.tpr) * blockDim.x + threadIdx.x;
+    const int rel = t - sd.one.tile0;
+    const int ty = rel / sd.one.tpr;
+    x = (uint32_t)(rel - ty * sd.one.tpr) * blockDim.x + threadIdx.x;
     y0 = ty * rows;
     y1 = min(y0 + rows, sd.g.ny);
     return x < (uint32_t)sd.g.nx;
@@ -621,8 +621,8 @@ __global__ __launch_bounds__(256) void batch_adjoint_kernel(
 
 // Two reverse steps of every sample, lam[lam_in] -> lam[lam_in ^ 1], the
 // histories in slots hist_slot (the later step) and hist_slot - 1: tiles of
-// four strips by `band` rows (the batch's two-step tiling: tile0 / tpr give
-// a sample's first tile and its groups of four strips per band).
+// four strips by `band` rows (the batch's two-step tiling: sd.two gives a
+// sample's first tile and its groups of four strips per band).
 template <int BCX, int BCY, bool KN, bool FC>
 __global__ __launch_bounds__(256) void batch_adjoint2_kernel(
     const AdjSampleDesc *__restrict__ samples, const int *__restrict__ tile_sample, int band,
@@ -630,9 +630,9 @@ __global__ __launch_bounds__(256) void batch_adjoint2_kernel(
 {
     const int t = xcd_remap_a(blockIdx.x, gridDim.x);
     const AdjSampleDesc sd = samples[tile_sample[t]];
-    const int rel = t - sd.tile0;
-    const int bnd = rel / sd.tpr;
-    const int strip = (rel - bnd * sd.tpr) * 4 + (int)(threadIdx.x >> 6);
+    const int rel = t - sd.two.tile0;
+    const int bnd = rel / sd.two.tpr;
+    const int strip = (rel - bnd * sd.two.tpr) * 4 + (int)(threadIdx.x >> 6);
     const float *mu_in = lam_in ? sd.lam[1] : sd.lam[0];
     float *mu_out = lam_in ? sd.lam[0] : sd.lam[1];
     const char *h = reinterpret_cast<const char *>(sd.hist);

@@ -214,8 +214,7 @@ struct BatchAdj {
 size_t batch_adj_place(BatchAdj &A, int64_t keep)
 {
     const int n = (int)A.plans.size();
-    // descriptor tables: the sweep's tiling, the two-step tiling, the tiles
-    size_t o = align_up((size_t)3 * n * sizeof(AdjSampleDesc), 256);
+    size_t o = align_up((size_t)n * sizeof(AdjSampleDesc), 256); // the descriptor table
     for (int i = 0; i < n; ++i) {
         AdjPlan &P = A.plans[i];
         P.total = P.inner + (size_t)(keep > 1 ? keep : 1) * P.inner_seg;
@@ -1039,9 +1038,9 @@ lbk_status lbk_batch_adjoint_backward(lbk_batch *b, void *ws, size_t ws_bytes,
     }
     char *w = static_cast<char *>(ws);
     hipStream_t st = b->stream;
-    // descriptor tables of this pass: the sweep's tiling (one workgroup per
-    // tile), then the same descriptors over the two-step tiling and the tiles
-    std::vector<AdjSampleDesc> h(3 * (size_t)b->n);
+    // descriptor table of this pass, with each tiling that its launches walk
+    // (single steps: one workgroup per tile)
+    std::vector<AdjSampleDesc> h((size_t)b->n);
     for (int i = 0; i < b->n; ++i) {
         lbk_lattice *l = b->lats[i];
         const AdjPlan &P = A.plans[i];
@@ -1072,16 +1071,9 @@ lbk_status lbk_batch_adjoint_backward(lbk_batch *b, void *ws, size_t ws_bytes,
         sd.a1 = (float)A.a1[i];
         sd.a2 = (float)A.a2[i];
         sd.outlet = A.outlet[i];
-        sd.tile0 = (int)b->tile0_sweep[i];
-        sd.tpr = tiles_per_row(l->d.nx, b->shape.tile_x);
-        AdjSampleDesc &s2 = h[(size_t)b->n + i];
-        s2 = sd;
-        s2.tile0 = (int)b->tile0_sweep2[i];
-        s2.tpr = groups_of(l->d.nx);
-        AdjSampleDesc &s3 = h[(size_t)2 * b->n + i];
-        s3 = sd;
-        s3.tile0 = (int)b->tile0_tile[i];
-        s3.tpr = tile_strips(l->d.nx, b->B.plan);
+        sd.one = {(int)b->tile0_sweep[i], tiles_per_row(l->d.nx, b->shape.tile_x)};
+        sd.two = {(int)b->tile0_sweep2[i], groups_of(l->d.nx)};
+        sd.tile = {(int)b->tile0_tile[i], tile_strips(l->d.nx, b->B.plan)};
     }
     AdjSampleDesc *table = reinterpret_cast<AdjSampleDesc *>(w + A.table);
     HIP_TRY(hipMemcpyAsync(table, h.data(), h.size() * sizeof(AdjSampleDesc),
@@ -1096,7 +1088,6 @@ lbk_status lbk_batch_adjoint_backward(lbk_batch *b, void *ws, size_t ws_bytes,
     // reverse steps in pairs (bitwise the same) when the batch counts as one
     // that steps that way
     const bool two = b->two();
-    const AdjSampleDesc *table2 = table + b->n;
     const int nt2 = (int)b->B.sweep2_tiles, band = band2_of(d.storage);
     // the next recomputing launch of `left` steps, as lbk_batch_step takes
     // them; returns its steps in n
@@ -1105,10 +1096,10 @@ lbk_status lbk_batch_adjoint_backward(lbk_batch *b, void *ws, size_t ws_bytes,
         if (n == 1)
             return rec(src, dst, slot);
         if (b->tile())
-            return launch_batch_rec_tile(d.storage, d.bc_x, d.bc_y, table + 2 * (size_t)b->n,
+            return launch_batch_rec_tile(d.storage, d.bc_x, d.bc_y, table,
                                          b->map_tile(), (int)b->B.tile_tiles, b->B.plan.tile,
                                          b->B.plan.steps, n, b->standard, src, dst, slot, st);
-        return launch_batch_rec_sweep2(d.storage, d.bc_x, d.bc_y, table2, b->map_sweep2(), nt2,
+        return launch_batch_rec_sweep2(d.storage, d.bc_x, d.bc_y, table, b->map_sweep2(), nt2,
                                        band, src, dst, slot, st);
     };
     int fc = 0;
@@ -1119,7 +1110,7 @@ lbk_status lbk_batch_adjoint_backward(lbk_batch *b, void *ws, size_t ws_bytes,
                                     fc, st);
     };
     auto reverse2 = [&](int lam_in, int slot) {
-        return launch_batch_adjoint2(d.bc_x, d.bc_y, table2, b->map_sweep2(), nt2, band, lam_in,
+        return launch_batch_adjoint2(d.bc_x, d.bc_y, table, b->map_sweep2(), nt2, band, lam_in,
                                      slot, knf, fc, st);
     };
     HIP_TRY(launch_batch_grad(table, map, nt, tx, rows, 0, knf, st));

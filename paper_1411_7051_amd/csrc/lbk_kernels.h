@@ -171,6 +171,9 @@ hipError_t launch_rescale(int storage, char *state, const Layout &lay, const Geo
 // tile list.
 enum { ADJ_CUR = 0, ADJ_OUTER = 1, ADJ_INNER = 2, ADJ_REC = 3 };
 struct AdjSampleDesc {
+    struct Tiling {
+        int tile0, tpr; // a sample's first tile; tiles per row of tiles
+    };
     char *region[4];
     uint64_t level_bytes;
     float *hist;
@@ -185,7 +188,8 @@ struct AdjSampleDesc {
     Geom g;
     Physics ph;
     float s, inv_s, a1, a2;
-    int outlet, tile0, tpr;
+    int outlet;
+    Tiling one, two, tile; // of the single steps, the two-step passes, the tile passes
 };
 
 // A level of a batched gradient's sample: region ADJ_* and index.

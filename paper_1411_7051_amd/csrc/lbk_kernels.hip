@@ -475,9 +475,9 @@ __global__ __launch_bounds__(kBatchMaxTile) void batch_rec_sweep_kernel(
 {
     const int t = xcd_remap(blockIdx.x, gridDim.x);
     const AdjSampleDesc sd = samples[tile_sample[t]];
-    const int rel = t - sd.tile0;
-    const int ty = rel / sd.tpr;
-    const uint32_t x = (uint32_t)(rel - ty * sd.tpr) * blockDim.x + threadIdx.x;
+    const int rel = t - sd.one.tile0;
+    const int ty = rel / sd.one.tpr;
+    const uint32_t x = (uint32_t)(rel - ty * sd.one.tpr) * blockDim.x + threadIdx.x;
     if (x >= (uint32_t)sd.g.nx)
         return;
     // selects, not an indexed read: the descriptor stays in registers
@@ -508,9 +508,9 @@ __global__ __launch_bounds__(kBlock) void batch_rec_sweep2_kernel(
 {
     const int t = xcd_remap(blockIdx.x, gridDim.x);
     const AdjSampleDesc sd = samples[tile_sample[t]];
-    const int rel = t - sd.tile0;
-    const int bnd = rel / sd.tpr;
-    const int strip = (rel - bnd * sd.tpr) * (kBlock / 64) + (int)(threadIdx.x >> 6);
+    const int rel = t - sd.two.tile0;
+    const int bnd = rel / sd.two.tpr;
+    const int strip = (rel - bnd * sd.two.tpr) * (kBlock / 64) + (int)(threadIdx.x >> 6);
     auto region = [&](int r) {
         return r == ADJ_CUR ? sd.region[0]
                             : (r == ADJ_OUTER ? sd.region[1]

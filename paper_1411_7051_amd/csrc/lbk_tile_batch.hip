@@ -29,8 +29,8 @@ __global__ __launch_bounds__(kTileMaxWaves * 64, 8) void batch_rec_tile_kernel(
     extern __shared__ Edges edges[];
     const int t = xcd_remap(blockIdx.x, gridDim.x);
     const AdjSampleDesc sd = samples[tile_sample[t]];
-    const int rel = t - sd.tile0;
-    const int band = rel / sd.tpr, strip = rel - band * sd.tpr;
+    const int rel = t - sd.tile.tile0;
+    const int band = rel / sd.tile.tpr, strip = rel - band * sd.tile.tpr;
     auto region = [&](int r) {
         return r == ADJ_CUR ? sd.region[0]
                             : (r == ADJ_OUTER ? sd.region[1]
