@@ -100,3 +100,38 @@ def test_batches(n, nx, ny, storage, f_eps, tiles):
     for f, lat in list(zip(fs, lats))[::max(1, n // 4)]:
         one = Lattice(*f, storage=storage, f_eps=f_eps, pass_mode="single", **PRESSURE)
         assert torch.equal(lat.save_state(), one.step(7).save_state())
+
+
+# the steps of a whole tile pass at sizes that select each of its shapes (8, 12
+# and 16 waves of one or two rows); the tests of bitwise equality compare the
+# automatic mode with single sweeps at these sizes, so this is what they test
+SHAPES = [(3, 1, 3), (64, 32, 3), (117, 23, 3), (70, 41, 3), (130, 37, 3), (200, 160, 4),
+          (384, 256, 4), (256, 256, 5), (300, 230, 5), (509, 511, 3), (777, 333, 3),
+          (1024, 512, 5), (1030, 1021, 4), (1111, 1025, 5)]
+
+
+@pytest.mark.parametrize("nx,ny,steps", SHAPES)
+@pytest.mark.parametrize("storage", ["f32", "f16", "bf16"])
+def test_steps_of_a_pass(nx, ny, steps, storage):
+    f = fields(nx, ny)
+    assert Lattice(*f, storage=storage, **PRESSURE).tile_steps == steps
+    for bcx in (inputs.PERIODIC, inputs.WALL):
+        lat = Lattice(*f, storage=storage, bc_x=bcx, bc_y=inputs.WALL, gx=1e-6, f_eps=0.7)
+        assert lat.tile_steps == steps
+    for mode in ("single", "two_step", "three_step"):
+        assert Lattice(*f, storage=storage, pass_mode=mode, **PRESSURE).tile_steps == 0
+    assert Lattice(*f, storage=storage, band=8, **PRESSURE).tile_steps == 0
+
+
+@pytest.mark.parametrize("sizes,steps", [
+    ([(33, 7), (300, 41), (59, 130), (130, 64), (3, 2), (517, 90)], 4),
+    ([(1200, 900), (700, 1500)], 4),
+    ([(nx, 3001) for nx in (3, 63, 64, 65, 84, 85, 108, 111, 112, 113, 140)], 4)])
+def test_steps_of_a_batch_pass(sizes, steps):
+    b = Batch([Lattice(*fields(nx, ny), **PRESSURE) for nx, ny in sizes])
+    assert b.tile_steps == steps
+    for mode in ("single", "two_step"):
+        b.set_pass_mode(mode)
+        assert b.tile_steps == 0
+    b.set_pass_mode("auto")
+    assert b.tile_steps == steps
