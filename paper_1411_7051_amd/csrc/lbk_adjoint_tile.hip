@@ -15,11 +15,11 @@
 // TB/s); on a small one the launch and the chain of steps, as in the forward
 // pass.  Two rows a wave keep 98 registers, four waves a SIMD; at 96 and five
 // waves a SIMD (a few spills) nothing was gained.  Measured against the
-// marching pairs (two waves a SIMD): 49.3 us a step for 61.8 at 2048 x 2048,
-// 181 for 217 at 4096 x 4096, 14.5 for 24.5 at 2048 x 512; against single steps
-// 2.9 us for 5.2 at 384 x 256, 2.3 for 4.4 at 64 x 32.
+// marching pairs (two waves a SIMD): 50 us a step for 60 at 2048 x 2048, 179 for
+// 216 at 4096 x 4096, 14.6 for 24 at 2048 x 512 (22 in single steps); against
+// single steps 2.9 us for 5.5 at 384 x 256, 2.2 for 4.4 at 64 x 32.
 // Tiles in the order of rows of tiles: columns of tiles first (1, 2, 4 or 8
-// strips wide) was slower, 53 to 57 us at 2048 x 2048.
+// strips wide) was slower, 55 to 57 us at 2048 x 2048 where rows took 50.
 #include "lbk_adjoint_dev.h"
 
 namespace lbk {

@@ -213,18 +213,16 @@ static bool tiles_lead(const lbk_desc &d, const Physics &ph, const TilePlan &p)
 }
 
 // The next launch of `left` >= 1 steps.  Tile passes share the steps evenly
-// (22 steps at up to 5 a launch are two fives and three fours); three-step passes leave a
-// remainder to a two-step pass or a single sweep.  Every pass is bitwise the
-// single sweeps it replaces.
+// (22 steps at up to 5 a launch are two fives and three fours; a whole pass has
+// three steps or more, so none gets one); three-step passes leave a remainder to
+// a two-step pass or a single sweep.  Every pass is bitwise the single sweeps it
+// replaces.
 Pass lbk::next_pass(const lbk_lattice *lat, int64_t left)
 {
     if (left > 1 && tile_pass(lat)) {
         const TilePlan &p = lat->plan;
         const int64_t launches = (left + p.steps - 1) / p.steps;
-        const int steps = (int)((left + launches - 1) / launches);
-        if (steps > 1)
-            return Pass{PASS_TILE, steps, p.tile};
-        return Pass{PASS_ONE, 1, {}};
+        return Pass{PASS_TILE, (int)((left + launches - 1) / launches), p.tile};
     }
     if (left > 2 && three_step_pass(lat))
         return Pass{PASS_THREE, 3, {}};

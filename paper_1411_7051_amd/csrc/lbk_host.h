@@ -76,9 +76,10 @@ struct AdjPlan {
 
 // A handle's read-out results on the host: eight sums and a mark per sum in
 // coherent pinned memory (a slot of a small pool: allocating and freeing
-// pinned memory took longer than the rest of a small lattice's creation).  The finish kernel writes a sum, then its mark; the
-// host polls the marks, which spares a small lattice the copy of the sums
-// and the wait for the stream (together longer than the read-out itself).
+// pinned memory took longer than the rest of a small lattice's creation).  The
+// finish kernel writes a sum, then its mark; the host polls the marks, which
+// spares a small lattice the copy of the sums and the wait for the stream
+// (together longer than the read-out itself).
 struct HostSums {
     double *sums = nullptr;
     uint64_t *done = nullptr;
@@ -211,12 +212,12 @@ inline int fwd_band3(const lbk_desc &d)
 }
 
 // Lattices from this many nodes on take two-step passes under
-// LBK_PASS_AUTO with a band set (without one, tile passes).  Below it too few waves run to hide the march's latency,
-// and a level fits the 256 MB on-package cache, so single sweeps are not
-// bound by HBM: FP32 on 1024 x 512, 52 GLUPS with single sweeps, 48-51 with
-// two-step passes; on 1024 x 1024, 61 against 70.  FP16 and BF16, whose
-// single sweeps move half the bytes, switch later: 93 against 85 GLUPS on
-// 2048 x 1024, 104 against 111 on 2048 x 2048.
+// LBK_PASS_AUTO where they take no tile passes (tile_pass).  Below it too few
+// waves run to hide the march's latency, and a level fits the 256 MB on-package
+// cache, so single sweeps are not bound by HBM: FP32 on 1024 x 512, 52 GLUPS with
+// single sweeps, 48-51 with two-step passes; on 1024 x 1024, 61 against 70.  FP16
+// and BF16, whose single sweeps move half the bytes, switch later: 93 against 85
+// GLUPS on 2048 x 1024, 104 against 111 on 2048 x 2048.
 inline int64_t two_step_nodes(int storage)
 {
     return storage == LBK_F32 ? (int64_t)1 << 20 : (int64_t)1 << 22;
@@ -238,9 +239,9 @@ inline bool two_step_pass(const lbk_lattice *lat)
 }
 
 // Lattices from this many nodes on take three-step passes under
-// LBK_PASS_AUTO with a band set.  FP32, against two-step passes: 116.1 against 88.9 GLUPS on
-// 4096 x 2048, 95.6 against 82.0 on 2048 x 2048, but 81.3 against 93.6 on
-// 2048 x 1024.  FP16: 126.0 against 118.3 on 4096 x 2048, but 104.5 against
+// LBK_PASS_AUTO where they take no tile passes.  FP32, against two-step passes:
+// 116.1 against 88.9 GLUPS on 4096 x 2048, 95.6 against 82.0 on 2048 x 2048, but
+// 81.3 against 93.6 on 2048 x 1024.  FP16: 126.0 against 118.3 on 4096 x 2048, but 104.5 against
 // 110.7 on 2048 x 2048 (bands of 24 rows, shortened there to keep the
 // device filled).
 inline int64_t three_step_nodes(int storage)
@@ -260,10 +261,11 @@ inline bool three_step_pass(const lbk_lattice *lat)
 
 // Whether the automatic mode advances this lattice in tile passes (several
 // steps per launch, launch_tile).  They lead at every size and model but on very
-// wide lattices of a few rows (tiles_lead), us a step against the passes they
-// replace: 64 x 32 FP32 2.1 / 3.2 (single sweeps), 1024 x 512 6.2 / 10.2, 2048 x 2048 27 / 43 (three-step passes), 4096 x 4096
-// 99 / 128; 4096 x 4096 FP16 96 / 107, with a body force 96 / 99, with the
-// Forchheimer term 144 / 145.  An explicit band asks for the marching passes.
+// wide lattices of a few rows and in some Forchheimer runs (tiles_lead), us a step
+// against the passes they replace: 64 x 32 FP32 2.0 / 3.0 (single sweeps), 1024 x
+// 512 6.2 / 10.0, 2048 x 2048 27 / 40 (three-step passes), 4096 x 4096 95 / 124;
+// 4096 x 4096 FP16 95 / 106, with a body force 101 / 106, with the Forchheimer
+// term 140 / 142.  An explicit band asks for the marching passes.
 inline bool tile_pass(const lbk_lattice *lat)
 {
     return lat->d.pass_mode == LBK_PASS_AUTO && lat->d.band == 0 && lat->tiles_lead;

@@ -94,7 +94,7 @@ hipError_t launch_sweep3x(int storage, int bcx, int bcy, const char *src, char *
                           const Physics &ph, float s, float inv_s, int band, float *hist1,
                           float *hist2, float *hist3, hipStream_t st);
 
-// Shape of a tile pass: workgroups of `waves` waves with `rows` (1, 2 or 4)
+// Shape of a tile pass: workgroups of `waves` waves with `rows` (1 or 2)
 // rows each, 64 columns wide.
 constexpr int kTileMaxWaves = 16;
 struct Tile {

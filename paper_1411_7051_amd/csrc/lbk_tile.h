@@ -19,20 +19,22 @@
 // Each step is the node update of the single sweep on values rounded as a
 // store would round them, so K steps are bitwise K single sweeps.
 //
-// What bounds it: on lattices that fill the device, the vector issue (the
-// counters show the vector units active 98% of the busy time on 4096 x 4096;
-// 16 x 2 rows and K = 4 make 1.29 updates per node and step), with eight waves
-// per SIMD: FP32 99 us a step there against 128 in three-step marching passes
-// (three waves per SIMD), 176 in two-step passes and 237 in single sweeps, FP16
-// 97 against 115, 128 and 150; on small ones a launch's fixed 4 us.  Two rows
+// What bounds it: on lattices that fill the device, the vector issue (on
+// 4096 x 4096 85 to 86% of the issue slots at FP32, beside 4.8 TB/s of HBM
+// traffic, 96 to 97% at FP16 and 99% at BF16; 16 x 2 rows and K = 4 make 1.30
+// updates per node and step), with eight waves per SIMD: FP32 95 us a step there
+// against 124 in three-step marching passes (three waves per SIMD), 174 in
+// two-step passes and 234 in single sweeps, FP16 95 against 106, 123 and 149 (one
+// device; another took 99 and 97); on small ones a launch's fixed 4 us.  Two rows
 // a wave are what 64 registers hold (with three or four the device runs half
 // the waves, which measured slower at every size).  What an update does not
 // need is kept out of it: a row beyond the rows still wanted is skipped, LDS
 // addresses are constants of the code (the two buffers' steps are unrolled),
 // only tiles at a wall carry the bounce-back selects and only waves that hold a
-// pressure column the exchange with its neighbour (119 -> 99 us in all with
-// the next).  MODEL_STD, the default model under a pressure drive, is compiled
-// apart: about 135 instead of 155 vector instructions an update.
+// pressure column the exchange with its neighbour (a sixth of the time in all,
+// with the next).  MODEL_STD, the default model under a pressure drive, is
+// compiled apart: 148 vector instructions an update at FP32, loads and stores of
+// the tile included.
 #pragma once
 
 #include "lbk_sweep.h"
