@@ -151,8 +151,8 @@ lbk_status lbk_create(const lbk_desc *d, const float *eps, const float *k,
 /* Release the handle (not the workspace).  NULL is accepted. */
 lbk_status lbk_destroy(lbk_lattice *lat);
 
-/* Advance n >= 0 time steps of Eq. 12: in the automatic mode as few tile
- * passes as lbk_tile_steps allows, of as equal a length as n permits; else one
+/* Advance n >= 0 time steps of Eq. 12: where lbk_tile_steps is not 0 as few
+ * tile passes as it allows, of as equal a length as n permits; else one
  * fused sweep launch per step, or per two or three steps in multi-step passes
  * (lbk_steps_per_launch), what remains of n in a shorter pass. */
 lbk_status lbk_step(lbk_lattice *lat, int64_t n);

@@ -71,9 +71,10 @@ class Batch:
                                                int(graph_steps)))
 
     def set_pass_mode(self, mode: str = "auto") -> None:
-        """Steps per launch: "two_step", "single" or "auto" (tile passes until
-        ``autotune`` keeps the fastest); every choice gives the same states bit
-        for bit."""
+        """Steps per launch: "two_step", "single" or "auto" (tile passes, but
+        for samples of a few rows and some batches with the Forchheimer term,
+        until ``autotune`` keeps the fastest); every choice gives the same
+        states bit for bit."""
         check(_lib.load().lbk_batch_set_pass_mode(self._handle(), _lib.PASS_MODE[mode]))
 
     @property

@@ -130,7 +130,8 @@ class Lattice:
 
     @property
     def tile_steps(self) -> int:
-        """Steps of a whole tile pass (the automatic mode's), 0 without."""
+        """Steps of a whole tile pass where the automatic mode takes them, 0
+        where steps go by ``steps_per_launch``."""
         n = ctypes.c_int32()
         check(_lib.load().lbk_tile_steps(self._handle(), ctypes.byref(n)))
         return int(n.value)
